@@ -43,6 +43,23 @@ namespace {
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// A set of tiles of the time-blocked kernels: steps per launch at most (0:
+// single-step kernels), large region, number of tiles.
+struct Blocks {
+    int ms = 0, big = 0, n_tiles = 0;
+    long long n_entries = 0;  // list entries at most
+    size_t off_tile = 0, off_list = 0;
+    int ex() const { return big ? 64 : 32; }
+    int ey() const { return big ? 32 : 16; }
+    int tx() const { return ex() - 2 * ms; }
+    int ty() const { return ey() - 2 * ms; }
+    // nodes along one axis of n nodes within ms of the tile of t nodes at v
+    int extent(int v, int n, int t, bool periodic) const {
+        const int lo = v - ms, hi = std::min(v + t, n) + ms;
+        return periodic ? hi - lo : std::min(hi, n) - std::max(lo, 0);
+    }
+};
+
 // Device workspace layout of one problem.
 struct Layout {
     int q = 9, D = 2, n_inst = 0;
@@ -50,6 +67,7 @@ struct Layout {
     int R = 1;                // resident segments: the last R segments' states are kept by the forward
     int frames = 1, stride = 1;   // loss frames: the states after steps T - (frames - 1 - m) stride
     int n_tiles = 0, n_ftiles = 0;
+    Blocks fwd, adj;          // time-blocked kernels of the forward and of the adjoint steps
     long long total_poff = 0, total_nodes = 0, total_face = 0, total_words = 0;
     long long S = 0;          // floats per state buffer
     int n_states = 0;
@@ -133,6 +151,41 @@ long long count_fluid(const lbm_instance &S) {
     return c;
 }
 
+// Steps per launch and region of the time-blocked kernels (D2Q9; a D3Q19
+// halo would outweigh its tile).  `nodes` counts all instances, solid nodes
+// included: the more nodes, the more blocks share a CU and the more the
+// repeated halo work costs, so the steps per launch fall.  The lines lie where
+// the next setting became faster; us per step at T = 120, porosity 0.7 and
+// empty, on 64 x 32, 128 x 64 | 200 x 100 | 300 x 200 | 512 x 256 lattices:
+//   forward 6 steps 1.5 - 1.6 | 1.64 | 2.2 - 2.4, 5 steps 1.7 | 1.75 | 2.2 - 2.3 |
+//   3.2 - 3.6, 4 steps 1.9 | 1.95 | 2.4 - 2.5 | 3.0 - 3.1;
+//   adjoint 6 steps 1.9 | 2.0 | 3.7, 5 steps 2.1 | 2.1 | 2.6 - 2.8 | 5.1 - 5.7,
+//   4 steps 2.3 | 2.3 | 2.8 - 3.0 | 4.6 - 5.0.
+// Above 200000 nodes the forward takes the large region with 5 steps (800 x
+// 320: 3.6 us, small region with 3 steps 3.4; 1024 x 512: 5.1 against 5.7; 8 x
+// 1024 x 512: 24.7 against 33 single-step).  The adjoint stays in the small
+// region with 3 steps (800 x 320: 6.5 us, single-step 8.0) up to 400000 nodes;
+// beyond, its registers leave too few wavefronts (1024 x 512: 11.8 against
+// 11.7; 3 x 1024 x 512: 31.7 against 26.0) and it runs single steps.
+void plan_blocks(Layout &L, long long nodes, int bcx, int bcy) {
+    if (L.q != 9) return;
+    const int small = nodes <= 32000 ? 6 : nodes <= 100000 ? 5 : 4;
+    L.fwd.big = nodes > 200000;
+    L.fwd.ms = L.fwd.big ? 5 : small;
+    L.adj.ms = nodes <= 200000 ? small : nodes <= 400000 ? 3 : 0;
+    for (Blocks *B : {&L.fwd, &L.adj}) {
+        if (!B->ms) continue;
+        for (const InstDev &I : L.inst) {
+            long long lx = 0, ly = 0;     // region nodes of all tiles = (sum of widths) x (sum of heights)
+            int tx = 0, ty = 0;
+            for (int x = 0; x < I.nx; x += B->tx(), ++tx) lx += B->extent(x, I.nx, B->tx(), bcx == LBM_BC_PERIODIC);
+            for (int y = 0; y < I.ny; y += B->ty(), ++ty) ly += B->extent(y, I.ny, B->ty(), bcy == LBM_BC_PERIODIC);
+            B->n_tiles += tx * ty;
+            B->n_entries += lx * ly;
+        }
+    }
+}
+
 void plan(const lbm_problem *p, Layout &L) {
     L.q = p->lattice;
     L.D = L.q == 9 ? 2 : 3;
@@ -183,6 +236,7 @@ void plan(const lbm_problem *p, Layout &L) {
     L.total_nodes = node;
     L.total_face = face;
     L.total_words = words;
+    plan_blocks(L, node, p->bc_x, p->bc_y);
     L.S = (long long)L.q * poff;
     L.n_states = 3 + (L.tape ? (L.n_seg - 1) + L.R * (L.K - 1) + 2 : 0);
     size_t o = 0;
@@ -200,8 +254,20 @@ void plan(const lbm_problem *p, Layout &L) {
     L.off_part_res = take(sizeof(double) * 2 * L.n_tiles);
     L.off_red = take(sizeof(double) * 2 * p->n_inst);
     L.off_fblk = take(sizeof(lbm::FTileDesc) * std::max(1, L.n_ftiles));
-    L.off_u2 = take(sizeof(float) * node * L.D);
-    L.off_seed = take(sizeof(float) * node * L.D);
+    // the forward and the adjoint kernels share one set of tiles where they are alike
+    for (Blocks *B : {&L.fwd, &L.adj}) {
+        if (B == &L.adj && B->ms == L.fwd.ms && B->big == L.fwd.big) {
+            *B = L.fwd;
+            continue;
+        }
+        B->off_tile = take(sizeof(lbm::MTileDesc) * B->n_tiles);
+        B->off_list = take(B->ms ? sizeof(uint2) * (B->n_entries + B->ex() * B->ey()) : 0);
+    }
+    // the residual's snapshot and the caller's seed; while an adjoint runs, their 2 D floats per
+    // node also hold dL/dtau of adjoint steps (dtau_slot)
+    L.off_u2 = take(sizeof(float) * std::max(node, poff) * L.D);
+    L.off_seed = L.off_u2 + sizeof(float) * std::max(node, poff) * L.D;
+    take(sizeof(float) * std::max(node, poff) * L.D);
     L.off_flag = take(sizeof(unsigned));
     L.state_bytes = align_up(sizeof(float) * (size_t)L.S, 256);
     L.off_states = o;
@@ -216,6 +282,7 @@ struct lbm_handle {
     hipStream_t stream = nullptr;
     char *ws = nullptr;
     lbm::Geo G{};
+    lbm::BlockGeo fwd{}, adj{};
     std::vector<InstDev> hinst;
     std::vector<float> h_face_in, h_face_out;
     std::vector<double> h_red, h_grad;
@@ -224,7 +291,7 @@ struct lbm_handle {
     float *cur = nullptr, *prev = nullptr;
     long long cur_steps = 0;          // steps taken since the initial state
     bool fwd_taped = false, adjoint_done = false, resident_valid = false;
-    float *nu_last = nullptr;         // nu^1 after the adjoint
+    float *nu_last = nullptr;         // nu^1 after the adjoint (the same buffer in every sweep of a handle)
     std::vector<double> tau;          // parameters of the taped forward
     // timing
     bool timing = false;
@@ -249,6 +316,7 @@ struct lbm_handle {
     // after a taped forward; the reverse sweep recomputes the other segments into region 0,
     // or into regions 0 and 1 in turn when the recompute runs beside the adjoint
     float *seg(int r, int j) const { return state(3 + (L.n_seg - 1) + r * (L.K - 1) + (j - 1)); }
+    bool is_pp(const float *s) const { return s == pp(0) || s == pp(1); }
     float *nu(int k) const { return state(3 + (L.n_seg - 1) + L.R * (L.K - 1) + k); }
     template <class T> T *at(size_t off) const { return (T *)(ws + off); }
 };
@@ -312,11 +380,16 @@ double elapsed(lbm_handle *h, int a, int b) {
     return ms;
 }
 
-// tape: dst is a tape state (a checkpoint or a segment state), read again
-// only by the reverse sweep, long after it would have left the cache.
-int step(lbm_handle *h, const float *src, float *dst, hipStream_t s, bool tape = false) {
-    HIP_TRY(lbm::launch_step(h->L.q, h->G, src, dst, h->at<float>(h->L.off_face_in),
-                             h->at<float>(h->L.off_face_out), tape, s));
+// Steps of one launch at most (1 without the time-blocked kernels).
+int run_length(const lbm_handle *h) { return std::max(1, h->L.fwd.ms); }
+
+// The steps of r from src.  A state other than the ping-pong pair is a tape
+// state (a checkpoint or a segment state), read again only by the reverse
+// sweep, long after it would have left the cache.
+int steps(lbm_handle *h, const float *src, const lbm::StepRun &r, hipStream_t s) {
+    const float *fin = h->at<float>(h->L.off_face_in), *fout = h->at<float>(h->L.off_face_out);
+    if (h->L.fwd.ms) HIP_TRY(lbm::launch_steps(h->G, h->fwd, src, r, fin, fout, s));
+    else HIP_TRY(lbm::launch_step(h->G, src, r.dst[0], fin, fout, !h->is_pp(r.dst[0]), s));
     return LBM_OK;
 }
 
@@ -470,6 +543,21 @@ int lbm_init(lbm_handle **out, const lbm_problem *p, void *d_workspace, size_t b
             e.r1 = (int)(w1 / I.words);
         }
     }
+    std::vector<lbm::MTileDesc> tiles[2];
+    for (int k = 0; k < 2; ++k) {
+        const Blocks &B = k ? L.adj : L.fwd;
+        if (!B.ms || (k && B.off_tile == L.fwd.off_tile)) continue;
+        int at = 0;
+        for (int b = 0; b < L.n_inst; ++b)
+            for (int y = 0; y < h->hinst[b].ny; y += B.ty())
+                for (int x = 0; x < h->hinst[b].nx; x += B.tx()) {
+                    lbm::MTileDesc e{};
+                    e.b = b; e.x0 = x; e.y0 = y; e.list = at;
+                    at += B.extent(x, h->hinst[b].nx, B.tx(), p->bc_x == LBM_BC_PERIODIC) *
+                          B.extent(y, h->hinst[b].ny, B.ty(), p->bc_y == LBM_BC_PERIODIC);
+                    tiles[k].push_back(e);
+                }
+    }
     auto cp = [&](size_t off, const void *src, size_t n) -> int {
         if (!n) return LBM_OK;
         HIP_TRY(hipMemcpyAsync(h->ws + off, src, n, hipMemcpyHostToDevice, h->stream));
@@ -479,6 +567,8 @@ int lbm_init(lbm_handle **out, const lbm_problem *p, void *d_workspace, size_t b
     if ((e = cp(L.off_inst, h->hinst.data(), sizeof(InstDev) * L.n_inst)) ||
         (e = cp(L.off_mask, rw.data(), sizeof(uint2) * rw.size())) ||
         (e = cp(L.off_fblk, fblk.data(), sizeof(lbm::FTileDesc) * fblk.size())) ||
+        (e = cp(L.fwd.off_tile, tiles[0].data(), sizeof(lbm::MTileDesc) * tiles[0].size())) ||
+        (e = cp(L.adj.off_tile, tiles[1].data(), sizeof(lbm::MTileDesc) * tiles[1].size())) ||
         (e = cp(L.off_roi, roi.data(), sizeof(float) * roi.size())) ||
         (e = cp(L.off_target, target.data(), sizeof(float) * target.size()))) {
         delete h;
@@ -498,6 +588,16 @@ int lbm_init(lbm_handle **out, const lbm_problem *p, void *d_workspace, size_t b
     h->G.nt = 2 * L.state_bytes > ((size_t)256 << 20);
     h->G.fblk = h->at<lbm::FTileDesc>(L.off_fblk);
     hipError_t he = lbm::launch_init_eq(L.q, h->G, h->init(), nullptr, nullptr, h->stream);
+    for (int k = 0; k < 2 && he == hipSuccess; ++k) {
+        const Blocks &B = k ? L.adj : L.fwd;
+        lbm::BlockGeo &T = k ? h->adj : h->fwd;
+        T.ms = B.ms; T.big = B.big; T.n_tiles = B.n_tiles;
+        T.tile = h->at<lbm::MTileDesc>(B.off_tile);
+        T.list = h->at<uint2>(B.off_list);
+        if (!tiles[k].empty())
+            he = lbm::launch_build_tiles(h->G, T, h->at<lbm::MTileDesc>(B.off_tile), h->at<uint2>(B.off_list),
+                                         h->stream);
+    }
     if (he == hipSuccess) he = hipStreamSynchronize(h->stream);
     if (he != hipSuccess) {
         delete h;
@@ -560,18 +660,6 @@ int lbm_get_populations(lbm_handle *h, int which, float *d_out) {
     return fail(LBM_EINVAL, "unknown population kind %d", which);
 }
 
-// Destination of step t of the forward pass.  With a tape, F^{cK} goes to
-// checkpoint c and the states of the last R segments go straight to their
-// regions of the segment store, so the reverse sweep does not recompute them.
-static float *fwd_dst(lbm_handle *h, int t, int record_tape) {
-    const Layout &L = h->L;
-    if (record_tape && t < L.T) {
-        const int c = t / L.K, j = t % L.K, r = c - (L.n_seg - L.R);
-        return j == 0 ? h->ckpt(c) : (r >= 0 ? h->seg(r, j) : h->pp(t & 1));
-    }
-    return h->pp(t & 1);
-}
-
 // Loss frame of the state after step t, or -1: frames sit at
 // T - (frames - 1 - m) stride, m = 0 .. frames - 1.
 static int frame_of(const Layout &L, int t) {
@@ -585,21 +673,51 @@ static const float *frame_target(lbm_handle *h, int m) {
     return h->at<float>(h->L.off_target) + (size_t)m * h->L.total_poff * h->L.D;
 }
 
+// The launches of a forward pass.  With a tape, F^{cK} goes to checkpoint c
+// and the states of the last R segments go straight to their regions of the
+// segment store, so the reverse sweep does not recompute them; the other
+// states stay in the launch, or go to the ping-pong buffer that the launch
+// does not read.  F^{T-1}, and the states of loss frames before T, end a launch.
+struct ForwardLaunch {
+    const float *src;
+    lbm::StepRun run;
+    int t;                    // step of the last state
+};
+static std::vector<ForwardLaunch> forward_launches(lbm_handle *h, int record_tape) {
+    const Layout &L = h->L;
+    std::vector<ForwardLaunch> out;
+    const float *src = h->init();
+    for (int t = 0; t < L.T;) {
+        int n = std::min(run_length(h), t < L.T - 1 ? L.T - 1 - t : 1);
+        for (int s = 1; s < n; ++s)
+            if (frame_of(L, t + s) >= 0) n = s;
+        ForwardLaunch f{src, lbm::StepRun{}, t + n};
+        f.run.n = n;
+        for (int s = 1; s <= n; ++s) {
+            const int c = (t + s) / L.K, j = (t + s) % L.K, r = c - (L.n_seg - L.R);
+            float *&dst = f.run.dst[s - 1];
+            if (record_tape && t + s < L.T) dst = j == 0 ? h->ckpt(c) : (r >= 0 ? h->seg(r, j) : nullptr);
+            if (s == n && !dst) dst = src == h->pp(0) ? h->pp(1) : h->pp(0);
+        }
+        src = f.run.dst[n - 1];
+        out.push_back(f);
+        t += n;
+    }
+    return out;
+}
+
 // The steps of a forward pass; the frames of a time-windowed loss before T
 // add their partial sums as the pass goes (the frame at T is added by
 // lbm_forward when a loss is asked for).
-static int enqueue_forward(lbm_handle *h, int record_tape, hipStream_t s) {
+static int enqueue_forward(lbm_handle *h, const std::vector<ForwardLaunch> &launches, hipStream_t s) {
     const Layout &L = h->L;
-    const float *src = h->init();
-    for (int t = 1; t <= L.T; ++t) {
-        float *dst = fwd_dst(h, t, record_tape);
-        int rc = step(h, src, dst, s, dst != h->pp(0) && dst != h->pp(1));
+    for (const ForwardLaunch &f : launches) {
+        int rc = steps(h, f.src, f.run, s);
         if (rc) return rc;
-        const int m = t < L.T ? frame_of(L, t) : -1;
+        const int m = f.t < L.T ? frame_of(L, f.t) : -1;
         if (m >= 0)
-            HIP_TRY(lbm::launch_loss(L.q, h->G, dst, h->at<float>(L.off_roi), frame_target(h, m), h->P.loss_kind,
-                                     h->at<double>(L.off_part_loss), m > 0, s));
-        src = dst;
+            HIP_TRY(lbm::launch_loss(L.q, h->G, f.run.dst[f.run.n - 1], h->at<float>(L.off_roi), frame_target(h, m),
+                                     h->P.loss_kind, h->at<double>(L.off_part_loss), m > 0, s));
     }
     return LBM_OK;
 }
@@ -614,12 +732,13 @@ int lbm_forward(lbm_handle *h, const lbm_params *prm, int record_tape, double *l
     h->fwd_taped = h->adjoint_done = false;
     const int T = L.T;
     if ((rc = record(h, 0))) return rc;
-    if (h->timing) rc = enqueue_forward(h, record_tape, h->stream);
-    else rc = with_graph(h, h->g_fwd[record_tape], [&](hipStream_t s) { return enqueue_forward(h, record_tape, s); });
+    const std::vector<ForwardLaunch> fl = forward_launches(h, record_tape);
+    if (h->timing) rc = enqueue_forward(h, fl, h->stream);
+    else rc = with_graph(h, h->g_fwd[record_tape], [&](hipStream_t s) { return enqueue_forward(h, fl, s); });
     if (rc) return rc;
     if ((rc = record(h, 1))) return rc;
-    h->cur = fwd_dst(h, T, record_tape);
-    h->prev = T >= 2 ? fwd_dst(h, T - 1, record_tape) : h->init();
+    h->cur = fl.back().run.dst[0];                  // the last launch is the step to T
+    h->prev = const_cast<float *>(fl.back().src);
     h->cur_steps = T;
     if (record_tape) {
         h->fwd_taped = true;
@@ -667,38 +786,79 @@ static int enqueue_reverse(lbm_handle *h, bool resident, const float *seed, hipS
     HIP_TRY(lbm::launch_fill_u32(flag, 1, 0u, s));
     const int n_seg = L.n_seg;
     int ev = 0, rc;
+    int nu = 0;                               // the adjoint state of the last launch
+    // Time-blocked adjoint launches: dL/dtau per node of a launch's steps, held
+    // until the next launch adds it, in slots of one float per fluid node: nine
+    // in the ping-pong buffer that does not hold F^T, four in the snapshot and
+    // seed arrays (the seed has been read by then); even launches take the
+    // first slots, odd ones those from L.adj.ms on.
+    float *spare = h->cur == h->pp(0) ? h->pp(1) : h->pp(0);
+    auto dtau_slot = [&](int k) {
+        return k < 9 ? spare + (size_t)k * L.total_poff : h->at<float>(L.off_u2) + (size_t)(k - 9) * L.total_poff;
+    };
+    lbm::AdjRun run{};
+    int parity = 0;
     // adjoint steps of segment c, reading its states from region r
     auto adjoint_segment = [&](int c, int r, hipStream_t st) -> int {
         const int t0 = c * K, t1 = std::min(t0 + K, T);
-        for (int k = t1; k > t0; --k) {
-            const float *Fprev = k - 1 - t0 == 0 ? h->ckpt(c) : h->seg(r, k - 1 - t0);
-            float *nu_out = h->nu(k & 1);
+        auto tape = [&](int t) { return t == t0 ? h->ckpt(c) : h->seg(r, t - t0); };
+        auto frame = [&](int k) { const int m = frame_of(L, k); return m >= 0 ? frame_target(h, m) : nullptr; };
+        const float *roi = h->at<float>(L.off_roi);
+        for (int k = t1; k > t0;) {
             if (k == T) {
-                HIP_TRY(lbm::launch_adj_seed(q, h->G, Fprev, nu_out, fin, fout, gin, gout,
-                                             h->at<float>(L.off_roi), frame_target(h, L.frames - 1),
-                                             h->P.loss_kind, seed, st));
-            } else {
-                const int m = frame_of(L, k);
-                HIP_TRY(lbm::launch_adj_step(q, h->G, Fprev, h->nu((k + 1) & 1), nu_out, fin, fout, gin, gout,
-                                             dpart, h->at<float>(L.off_roi), m >= 0 ? frame_target(h, m) : nullptr,
-                                             h->P.loss_kind, st));
+                HIP_TRY(lbm::launch_adj_seed(q, h->G, tape(k - 1), h->nu(nu), fin, fout, gin, gout, roi,
+                                             frame_target(h, L.frames - 1), h->P.loss_kind, seed, st));
+                --k;
+                continue;
             }
+            if (L.adj.ms) {
+                run.target = frame(k);              // a loss frame's step is a launch of its own
+                run.n_prev = run.n;
+                for (int s = 0; s < run.n; ++s) run.prev[s] = run.dtau[s];
+                run.n = run.target ? 1 : std::min(L.adj.ms, k - t0);
+                for (int s = 1; s < run.n; ++s)
+                    if (frame(k - s)) run.n = s;
+                for (int s = 0; s < run.n; ++s) {
+                    run.Fprev[s] = tape(k - 1 - s);
+                    run.dtau[s] = dtau_slot(parity * L.adj.ms + s);
+                }
+                parity ^= 1;
+                HIP_TRY(lbm::launch_adj_steps(h->G, h->adj, run, h->nu(nu), h->nu(nu ^ 1), fin, fout, gin, gout, dpart,
+                                              roi, h->P.loss_kind, st));
+                k -= run.n;
+            } else {
+                HIP_TRY(lbm::launch_adj_step(q, h->G, tape(k - 1), h->nu(nu), h->nu(nu ^ 1), fin, fout, gin, gout,
+                                             dpart, roi, frame(k), h->P.loss_kind, st));
+                --k;
+            }
+            nu ^= 1;
         }
         return LBM_OK;
     };
     // Recomputes segment c into region r; a segment followed by a checkpoint
-    // then takes one more step with the same kernel into a scratch state (the
-    // ping-pong buffer that does not hold F^T), compared bit for bit with
-    // that checkpoint (a mismatch raises the flag that lbm_grad reports).
-    float *scratch = h->pp(1 - (T & 1));
+    // then takes one more step with the same kernel, whose state is compared
+    // bit for bit with that checkpoint (a mismatch raises the flag that
+    // lbm_grad reports): inside the launch, or from the spare ping-pong buffer.
     auto recompute_segment = [&](int c, int r, hipStream_t st) -> int {
         const int t0 = c * K, t1 = std::min(t0 + K, T);
-        for (int j = 1; j < t1 - t0; ++j)
-            if ((rc = step(h, j == 1 ? h->ckpt(c) : h->seg(r, j - 1), h->seg(r, j), st, true))) return rc;
-        if (c + 1 < n_seg) {
-            if ((rc = step(h, t1 - t0 > 1 ? h->seg(r, t1 - t0 - 1) : h->ckpt(c), scratch, st))) return rc;
-            HIP_TRY(lbm::launch_compare(q, h->G, scratch, h->ckpt(c + 1), flag, st));
+        const bool verify = c + 1 < n_seg;
+        const int last = verify ? t1 - t0 : t1 - t0 - 1;
+        for (int j = 0; j < last;) {
+            lbm::StepRun f{};
+            f.n = std::min(run_length(h), last - j);
+            for (int s = 1; s <= f.n; ++s) f.dst[s - 1] = j + s < t1 - t0 ? h->seg(r, j + s) : nullptr;
+            if (verify && j + f.n == last) {
+                if (L.fwd.ms) {
+                    f.check = h->ckpt(c + 1);
+                    f.flag = flag;
+                } else {
+                    f.dst[f.n - 1] = spare;
+                }
+            }
+            if ((rc = steps(h, j == 0 ? h->ckpt(c) : h->seg(r, j), f, st))) return rc;
+            j += f.n;
         }
+        if (verify && !L.fwd.ms) HIP_TRY(lbm::launch_compare(h->G, spare, h->ckpt(c + 1), flag, st));
         return LBM_OK;
     };
     auto kept = [&](int k) { return resident && k < L.R; };          // k-th segment of the sweep, c = n_seg - 1 - k
@@ -751,7 +911,11 @@ static int enqueue_reverse(lbm_handle *h, bool resident, const float *seed, hipS
     }
     // anti-bounce-back: the faces' density also entered g^1, through F^0
     if (L.T >= 1 && h->P.bc_x == LBM_BC_ABB)
-        HIP_TRY(lbm::launch_abb_grad0(q, h->G, h->init(), h->nu(1), fin, fout, gin, gout, s));
+        HIP_TRY(lbm::launch_abb_grad0(q, h->G, h->init(), h->nu(nu), fin, fout, gin, gout, s));
+    run.n_prev = run.n;
+    for (int s2 = 0; s2 < run.n; ++s2) run.prev[s2] = run.dtau[s2];
+    HIP_TRY(lbm::launch_dtau_sums(h->G, run, dpart, s));
+    h->nu_last = h->nu(nu);
     return LBM_OK;
 }
 
@@ -787,7 +951,6 @@ int lbm_adjoint(lbm_handle *h, const float *d_seed_du) {
     }
     // recomputed segments overwrite regions 0 and 1; with every segment resident nothing is recomputed
     h->resident_valid = (resident && L.R == L.n_seg) || L.n_seg == 1;
-    h->nu_last = h->nu(1);
     h->adjoint_done = true;
     h->prev = nullptr;  // the segment store that held F^{T-1} has been reused
     return LBM_OK;
@@ -835,21 +998,28 @@ int lbm_grad(lbm_handle *h, double *d_rho_in, double *d_tau, double *d_rho_out) 
 }
 
 // One residual chunk: check_every steps from src over the ping-pong
-// buffers (pp0, pp1, pp0, ...), then the residual partial sums of the two-step
+// buffers, the last two states in pp0 and pp1, then the residual partial sums of the two-step
 // mean of the last two states against the snapshot of the previous check
 // (the first chunk takes the snapshot of the initial state first).
 static int enqueue_chunk(lbm_handle *h, const float *src, bool first, int check_every, hipStream_t s) {
     const Layout &L = h->L;
     float *snap = h->at<float>(L.off_u2);
     if (first) HIP_TRY(lbm::launch_macro(L.q, h->G, src, nullptr, nullptr, snap, s));
-    const float *prev = nullptr;
-    for (int k = 0; k < check_every; ++k) {
-        float *dst = h->pp(k & 1);
-        int rc = step(h, src, dst, s);
+    // launches of nearly equal length that alternate between the buffers and end
+    // in pp0 (an odd number of them from pp1), then one step to pp1
+    const int len = run_length(h);
+    int m = (check_every - 1 + len - 1) / len;
+    if (src == h->pp(1) && m % 2 == 0) ++m;
+    for (int j = 1, t = 0; j <= m + 1; ++j) {
+        lbm::StepRun run{};
+        run.n = j <= m ? (int)((long long)(check_every - 1) * j / m) - t : 1;
+        run.dst[run.n - 1] = j <= m ? h->pp((m - j) & 1) : h->pp(1);
+        int rc = steps(h, src, run, s);
         if (rc) return rc;
-        prev = src;
-        src = dst;
+        src = run.dst[run.n - 1];
+        t += run.n;
     }
+    const float *prev = h->pp(0);
     HIP_TRY(lbm::launch_residual(L.q, h->G, src, prev, snap, h->at<double>(L.off_part_res), s));
     HIP_TRY(lbm::launch_reduce(h->at<InstDev>(L.off_inst), L.n_inst, h->at<double>(L.off_part_res), 2, 0,
                                h->at<double>(L.off_red), s));

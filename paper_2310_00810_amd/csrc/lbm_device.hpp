@@ -130,6 +130,43 @@ struct FTileDesc {
     int w0, w1, b, r0, r1, pad0, pad1, pad2;
 };
 
+// Time-blocked D2Q9 kernels: a region of 32 x 16 (big: 64 x 32) nodes per
+// block, i.e. a tile with a halo of ms nodes, ms = steps per launch at most.  Per tile: instance, first column and row, and the number of the
+// list's nodes within distance d of the tile.
+constexpr int MS_MAX = 6;
+struct MTileDesc {
+    int b, x0, y0;
+    int list;              // first entry of the tile's list
+    int cnt[MS_MAX + 1];
+    int pad[5];
+};
+struct BlockGeo {
+    int ms, big, n_tiles;
+    const MTileDesc *tile;
+    const uint2 *list;
+};
+
+// One launch of up to MS_MAX steps: dst[s] receives the state after step s + 1
+// (nullptr: the state stays in LDS); check (nullable): a state that the last
+// one must equal bit for bit, else *flag = 1.
+struct StepRun {
+    float *dst[MS_MAX];
+    int n;
+    const float *check;
+    unsigned *flag;
+};
+// One launch of up to MS_MAX adjoint steps k, k - 1, ...: the tape states
+// F^{k-1} of those steps and where each step's dL/dtau per node goes; target
+// (nullable): the loss frame on g^k of a launch of one step.  The launch also
+// adds the n_prev steps of the launch before, in prev, to the partials.
+struct AdjRun {
+    const float *Fprev[MS_MAX];
+    float *dtau[MS_MAX];
+    const float *target;
+    int n, n_prev;
+    const float *prev[MS_MAX];
+};
+
 struct Geo {
     const InstDev *inst;
     int n_inst;
@@ -714,10 +751,10 @@ __device__ inline void own_velocity(__amdgpu_buffer_rsrc_t r, int plane, unsigne
 // step.  With E_i = 1 + (u.c_i)^2/(2 cs^4) - u.u/(2 cs^2) and rho_w = 1 + drho_b,
 //   g_i = -F_opp(i) + 2 w_i rho_w E_i - 2 w_i = -F_opp(i) + 2 w_i (drho_b + rho_w (E_i - 1)).
 // in / out select the inlet (unknowns c_x = +1) or outlet (c_x = -1).
+// usq = u.u (an argument, so that a caller can fix how it is rounded).
 template <int Q>
-__device__ inline void abb(float (&g)[Q], bool in, bool out, float drho_b, const float (&uF)[3]) {
+__device__ inline void abb(float (&g)[Q], bool in, bool out, float drho_b, const float (&uF)[3], float usq) {
     using V = Vel<Q>;
-    const float usq = uF[0] * uF[0] + uF[1] * uF[1] + uF[2] * uF[2];
     const float rw = 1.0f + drho_b;
 #pragma unroll
     for (int p = 1; p < Q; ++p) {
@@ -728,6 +765,11 @@ __device__ inline void abb(float (&g)[Q], bool in, bool out, float drho_b, const
         g[p] = in ? e - g[p] : g[p];
         g[m] = out ? e - g[m] : g[m];
     }
+}
+
+template <int Q>
+__device__ inline void abb(float (&g)[Q], bool in, bool out, float drho_b, const float (&uF)[3]) {
+    abb<Q>(g, in, out, drho_b, uF, uF[0] * uF[0] + uF[1] * uF[1] + uF[2] * uF[2]);
 }
 
 // Transpose of the anti-bounce-back closure that built g^{k+1} at this node
@@ -766,6 +808,129 @@ __device__ inline float abb_adj(float (&lam)[Q], bool in, bool out, float drho_b
                          (V::cz(j) ? V::cz(j) * Vz : 0.f) - Vu);
     return gb;
 }
+
+// D2Q9 collision (BGK or MRT) of the gathered populations g with moments m.
+__device__ inline void collide(const Geo &G, float om, const Moments &m, const float (&g)[9], float (&f)[9]) {
+    float feq[9];
+    feq_all<9>(m, feq);
+    if (G.coll == COLL_MRT) {
+        float d[9], r[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) d[i] = g[i] - feq[i];
+        mrt_relax(d, G.mrt, om, r);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) f[i] = g[i] - r[i];
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < 9; ++i) f[i] = g[i] + om * (feq[i] - g[i]);
+}
+
+// Transpose of the D2Q9 collision at the populations g (moments m) applied to
+// lam = S^T nu^{k+1}, as k_adj_step computes it: a = C'(g)^T lam; returns
+// dL/dtau of the node.  Which product of a sum is fused is spelled out where
+// the compiler's choice would depend on the surrounding code, so that both
+// kernels round alike.
+__device__ inline float collide_adj(const Geo &G, float omega, float inv_tau2, const Moments &m, const float (&g)[9],
+                                    const float (&lam)[9], float (&a)[9]) {
+    using V = Vel<9>;
+    float dtau = 0.f;
+    float mu[9];
+    const bool mrt = G.coll == COLL_MRT;
+    if (mrt) {
+        mrt_relax(lam, G.mrt, omega, mu);
+        float y7 = 0.f, y8 = 0.f, d7 = 0.f, d8 = 0.f, feq[9];
+        feq_all<9>(m, feq);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            const float dq = g[i] - feq[i];
+            if (mrt_m(7, i)) { y7 += mrt_m(7, i) * lam[i]; d7 += mrt_m(7, i) * dq; }
+            if (mrt_m(8, i)) { y8 += mrt_m(8, i) * lam[i]; d8 += mrt_m(8, i) * dq; }
+        }
+        dtau = (y7 * d7 / (float)mrt_norm(7) + y8 * d8 / (float)mrt_norm(8)) * inv_tau2;
+    }
+    if (!mrt) {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) mu[q] = lam[q];
+    }
+    float S0 = 0.f, Sx = 0.f, Sy = 0.f, Sxx = 0.f, Syy = 0.f, Sxy = 0.f;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+        const int cx = V::cx(q), cy = V::cy(q);
+        const float wl = V::w(q) * mu[q];
+        S0 += wl;
+        if (cx) { Sx += cx * wl; Sxx += wl; }
+        if (cy) { Sy += cy * wl; Syy += wl; }
+        if (cx && cy) Sxy += cx * cy * wl;
+        if (!mrt) dtau += lam[q] * g[q];
+    }
+    const float ux = m.ux, uy = m.uy;
+    const float usq = fmaf(ux, ux, uy * uy);
+    const float S2ux = fmaf(Sxy, uy, Sxx * ux), S2uy = fmaf(Sxy, ux, Syy * uy);
+    const float uSu = fmaf(uy, S2uy, ux * S2ux);
+    const float A1 = 1.5f * usq * S0 - 4.5f * uSu;
+    const float A = S0 + A1;
+    const float Bx = 3.0f * Sx + 9.0f * S2ux - 3.0f * ux * S0;
+    const float By = 3.0f * Sy + 9.0f * S2uy - 3.0f * uy * S0;
+    if (!mrt) dtau = (dtau - (m.drho * S0 + m.rho * (A1 + ux * Bx + uy * By))) * inv_tau2;
+    const float om = mrt ? 1.0f : omega, om1 = 1.0f - omega;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+        const float eq = A + (V::cx(i) ? V::cx(i) * Bx : 0.f) + (V::cy(i) ? V::cy(i) * By : 0.f);
+        a[i] = mrt ? lam[i] - mu[i] + eq : om1 * lam[i] + om * eq;
+    }
+    return dtau;
+}
+
+// dl/du at one node for the built-in loss; returns l.
+template <int D>
+__device__ inline float loss_node(int kind, float wgt, const float *u, const float *t, float *dldu) {
+    if (kind == LOSS_NORM) {
+        float nu2 = 0.f, nt2 = 0.f;
+#pragma unroll
+        for (int a = 0; a < D; ++a) { nu2 += u[a] * u[a]; nt2 += t[a] * t[a]; }
+        const float nu = sqrtf(nu2), nt = sqrtf(nt2);
+        const float d = nu - nt;
+        const float c = nu > 0.f ? 2.0f * wgt * d / nu : 0.f;
+#pragma unroll
+        for (int a = 0; a < D; ++a) dldu[a] = c * u[a];
+        return wgt * d * d;
+    }
+    float l = 0.f;
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        const float d = u[a] - t[a];
+        l += d * d;
+        dldu[a] = 2.0f * wgt * d;
+    }
+    return wgt * l;
+}
+
+// Adds dl/dg of one loss frame (target: the node's target components, `plane`
+// apart) at a node with moments m to a.
+template <int Q>
+__device__ inline void seed_adj(const float *__restrict__ target, long long plane, float wgt, int kind,
+                                const Moments &m, float (&a)[Q]) {
+    using V = Vel<Q>;
+    constexpr int D = V::D;
+    const float u[3] = {m.ux, m.uy, m.uz};
+    float tg[3] = {0.f, 0.f, 0.f}, dldu[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+    for (int d = 0; d < D; ++d) tg[d] = target[(long long)d * plane];
+    loss_node<D>(kind, wgt, u, tg, dldu);
+    const float inv = 1.0f / m.rho;
+#pragma unroll
+    for (int i = 0; i < Q; ++i)
+        a[i] += inv * (dldu[0] * (V::cx(i) - m.ux) + dldu[1] * (V::cy(i) - m.uy) +
+                       (D == 3 ? dldu[2] * (V::cz(i) - m.uz) : 0.f));
+}
+
+// True when some lane of the wavefront sits on an inlet or outlet face: the
+// step and seed kernels skip the (branch-free) Zou-He closure in wavefronts
+// without face nodes, most of them in rows much wider than a wavefront.  The
+// adjoint step keeps it unconditional: with the branch it spills registers
+// and ran 20 % slower.
+__device__ inline bool wave_has_face(bool face) { return __builtin_amdgcn_ballot_w64(face) != 0; }
 
 // Wavefront (64-lane) sum in FP64.
 __device__ inline double wave_sum(double v) {

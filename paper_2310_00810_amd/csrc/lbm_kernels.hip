@@ -31,13 +31,6 @@ namespace lbm {
     __syncthreads();                                                        \
     const FLane n = fluid_lane(G, I, t, L)
 
-// True when some lane of the wavefront sits on an inlet or outlet face: the
-// step and seed kernels skip the (branch-free) Zou-He closure in wavefronts
-// without face nodes, most of them in rows much wider than a wavefront.  The
-// adjoint step keeps it unconditional: with the branch it spills registers
-// and ran 20 % slower.
-__device__ inline bool wave_has_face(bool face) { return __builtin_amdgcn_ballot_w64(face) != 0; }
-
 // Face density of a node on a Zou-He face (issued before the gathers).
 template <int BCX>
 __device__ inline float face_density(const InstDev &I, const FLane &n, bool in, bool out,
@@ -60,6 +53,7 @@ __device__ inline void face_unknown_adjoints(__amdgpu_buffer_rsrc_t rn, int plan
         if (V::cx(i) != 0 && (V::cx(i) > 0 ? in : out)) nuo[i] = bload(rn, own + (unsigned)(i * plane) * 4u);
 }
 
+// One step of a D3Q19 problem (D2Q9 steps are time-blocked: k_steps).
 // NTM: 0 default cache policy, 1 non-temporal stores (a destination that no
 // later step reads while it could still be cached: a tape state, or any
 // state when two exceed the Infinity Cache), 2 non-temporal gathers too
@@ -89,17 +83,6 @@ __global__ void __launch_bounds__(FT) k_step(Geo G, const float *__restrict__ sr
     const unsigned own = (unsigned)n.id * 4u;
     float feq[Q];
     feq_all<Q>(m, feq);
-    if constexpr (Q == 9) {
-        if (G.coll == COLL_MRT) {
-            float d[9], r[9];
-#pragma unroll
-            for (int i = 0; i < 9; ++i) d[i] = g[i] - feq[i];
-            mrt_relax(d, G.mrt, om, r);
-#pragma unroll
-            for (int i = 0; i < 9; ++i) bstore<(NTM >= 1)>(rd, g[i] - r[i], own, plane_off(i, plane));
-            return;
-        }
-    }
 #pragma unroll
     for (int i = 0; i < Q; ++i) bstore<(NTM >= 1)>(rd, g[i] + om * (feq[i] - g[i]), own, plane_off(i, plane));
 }
@@ -122,30 +105,6 @@ __global__ void __launch_bounds__(FT) k_compare(Geo G, const float *__restrict__
 }
 
 // -------------------------------------------------------- loss functions --
-// dl/du at one node for the built-in loss; returns l.
-template <int D>
-__device__ inline float loss_node(int kind, float wgt, const float *u, const float *t, float *dldu) {
-    if (kind == LOSS_NORM) {
-        float nu2 = 0.f, nt2 = 0.f;
-#pragma unroll
-        for (int a = 0; a < D; ++a) { nu2 += u[a] * u[a]; nt2 += t[a] * t[a]; }
-        const float nu = sqrtf(nu2), nt = sqrtf(nt2);
-        const float d = nu - nt;
-        const float c = nu > 0.f ? 2.0f * wgt * d / nu : 0.f;
-#pragma unroll
-        for (int a = 0; a < D; ++a) dldu[a] = c * u[a];
-        return wgt * d * d;
-    }
-    float l = 0.f;
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-        const float d = u[a] - t[a];
-        l += d * d;
-        dldu[a] = 2.0f * wgt * d;
-    }
-    return wgt * l;
-}
-
 template <int Q>
 __device__ inline Moments load_moments(const float *__restrict__ F, const InstDev &I, int id) {
     float g[Q];
@@ -593,6 +552,14 @@ static inline dim3 grid_of(const Geo &G) { return dim3((unsigned)G.n_tiles); }
 static inline dim3 fgrid_of(const Geo &G) { return dim3((unsigned)G.n_ftiles); }
 
 // Fluid-tile kernels take the x boundary kind as a template parameter.
+#define DISPATCH_BCX19(bcx, CALL)                                                          \
+    do {                                                                                   \
+        if (bcx == BC_PRESSURE) CALL(19, BC_PRESSURE);                                     \
+        else if (bcx == BC_PERIODIC) CALL(19, BC_PERIODIC);                                \
+        else if (bcx == BC_WALL) CALL(19, BC_WALL);                                        \
+        else if (bcx == BC_ABB) CALL(19, BC_ABB);                                          \
+        else CALL(19, BC_VELOCITY);                                                        \
+    } while (0)
 #define DISPATCH_BCX(q, bcx, CALL)                                                         \
     do {                                                                                   \
         if (q == 9) {                                                                      \
@@ -602,36 +569,30 @@ static inline dim3 fgrid_of(const Geo &G) { return dim3((unsigned)G.n_ftiles); }
             else if (bcx == BC_ABB) CALL(9, BC_ABB);                                       \
             else CALL(9, BC_VELOCITY);                                                     \
         } else {                                                                           \
-            if (bcx == BC_PRESSURE) CALL(19, BC_PRESSURE);                                 \
-            else if (bcx == BC_PERIODIC) CALL(19, BC_PERIODIC);                            \
-            else if (bcx == BC_WALL) CALL(19, BC_WALL);                                    \
-            else if (bcx == BC_ABB) CALL(19, BC_ABB);                                      \
-            else CALL(19, BC_VELOCITY);                                                    \
+            DISPATCH_BCX19(bcx, CALL);                                                     \
         }                                                                                  \
     } while (0)
 
-hipError_t launch_step(int q, const Geo &G, const float *src, float *dst, const float *fin,
-                       const float *fout, bool tape, hipStream_t s) {
+hipError_t launch_step(const Geo &G, const float *src, float *dst, const float *fin, const float *fout, bool tape,
+                       hipStream_t s) {
     if (G.n_ftiles == 0) return hipSuccess;
-    // beyond the Infinity Cache every step streams, and D3Q19 gathers read
-    // non-temporal too (D2Q9 ones do not: other blocks reread their
-    // neighbouring rows' lines); a step into the tape streams its stores
-    const int ntm = G.nt ? (q == 19 ? 2 : 1) : (tape ? 1 : 0);
+    // beyond the Infinity Cache every step streams, gathers included; a step
+    // into the tape streams its stores
+    const int ntm = G.nt ? 2 : (tape ? 1 : 0);
 #define CALL(Q, B)                                                                                 \
     do {                                                                                           \
         if (ntm == 2) hipLaunchKernelGGL((k_step<Q, B, 2>), fgrid_of(G), dim3(FT), 0, s, G, src, dst, fin, fout); \
         else if (ntm == 1) hipLaunchKernelGGL((k_step<Q, B, 1>), fgrid_of(G), dim3(FT), 0, s, G, src, dst, fin, fout); \
         else hipLaunchKernelGGL((k_step<Q, B, 0>), fgrid_of(G), dim3(FT), 0, s, G, src, dst, fin, fout); \
     } while (0)
-    DISPATCH_BCX(q, G.bcx, CALL);
+    DISPATCH_BCX19(G.bcx, CALL);
 #undef CALL
     return hipGetLastError();
 }
 
-hipError_t launch_compare(int q, const Geo &G, const float *a, const float *b, unsigned *flag, hipStream_t s) {
+hipError_t launch_compare(const Geo &G, const float *a, const float *b, unsigned *flag, hipStream_t s) {
     if (G.n_ftiles == 0) return hipSuccess;
-    if (q == 9) hipLaunchKernelGGL(k_compare<9>, fgrid_of(G), dim3(FT), 0, s, G, a, b, flag);
-    else hipLaunchKernelGGL(k_compare<19>, fgrid_of(G), dim3(FT), 0, s, G, a, b, flag);
+    hipLaunchKernelGGL(k_compare<19>, fgrid_of(G), dim3(FT), 0, s, G, a, b, flag);
     return hipGetLastError();
 }
 

@@ -5,10 +5,11 @@
 
 namespace lbm {
 
-hipError_t launch_step(int q, const Geo &G, const float *src, float *dst, const float *fin,
-                       const float *fout, bool tape, hipStream_t s);
-// Sets *flag = 1 if states a and b differ in any population of a fluid node.
-hipError_t launch_compare(int q, const Geo &G, const float *a, const float *b, unsigned *flag, hipStream_t s);
+// One step of a D3Q19 problem.
+hipError_t launch_step(const Geo &G, const float *src, float *dst, const float *fin, const float *fout, bool tape,
+                       hipStream_t s);
+// Sets *flag = 1 if D3Q19 states a and b differ in any population of a fluid node.
+hipError_t launch_compare(const Geo &G, const float *a, const float *b, unsigned *flag, hipStream_t s);
 // acc: add to the partials (the later frames of a time-windowed loss).
 hipError_t launch_loss(int q, const Geo &G, const float *F, const float *roi, const float *target,
                        int kind, double *part, int acc, hipStream_t s);
@@ -26,6 +27,17 @@ hipError_t launch_adj_final(int q, const Geo &G, const float *nu_in, const float
 // Anti-bounce-back faces: adds dL/d(drho_b) of the closure that built g^1.
 hipError_t launch_abb_grad0(int q, const Geo &G, const float *F0, const float *nu1, const float *fin,
                             const float *fout, double *gin, double *gout, hipStream_t s);
+// Builds the node lists and counts of T's tiles (b, x0, y0 and list set).
+hipError_t launch_build_tiles(const Geo &G, const BlockGeo &T, MTileDesc *tiles, uint2 *list, hipStream_t s);
+// Time-blocked D2Q9 steps: st.n steps from src; st.n adjoint steps k, k - 1, ...
+// from nu_in to nu_out; the partials per fluid tile of dL/dtau of the n_prev
+// steps in st.prev.
+hipError_t launch_steps(const Geo &G, const BlockGeo &T, const float *src, const StepRun &st, const float *fin,
+                        const float *fout, hipStream_t s);
+hipError_t launch_adj_steps(const Geo &G, const BlockGeo &T, const AdjRun &st, const float *nu_in, float *nu_out,
+                            const float *fin, const float *fout, double *gin, double *gout, double *dtau_part,
+                            const float *roi, int kind, hipStream_t s);
+hipError_t launch_dtau_sums(const Geo &G, const AdjRun &st, double *dtau_part, hipStream_t s);
 hipError_t launch_init_eq(int q, const Geo &G, float *F, const float *drho, const float *u,
                           hipStream_t s);
 hipError_t launch_convert(int q, const Geo &G, float *F, float *dense, int to_state, hipStream_t s);
