@@ -26,13 +26,30 @@ __device__ __host__ inline float bf2f(uint16_t v) {
     return c.f;
 }
 
-// float -> bf16, round to nearest even (NaN kept quiet).
-__device__ __host__ inline uint16_t f2bf(float f) {
-    union { uint32_t u; float f; } c;
-    c.f = f;
-    if ((c.u & 0x7f800000u) == 0x7f800000u && (c.u & 0x007fffffu)) return (uint16_t)((c.u >> 16) | 0x40);
-    const uint32_t r = c.u + 0x7fffu + ((c.u >> 16) & 1u);
-    return (uint16_t)(r >> 16);
+// float -> bf16, round to nearest even (NaN kept quiet): v_cvt_pk_bf16_f32,
+// which equals the integer form x + 0x7fff + (bit 16 of x) >> 16 for every
+// float (all 2^32 compared); two values cost one instruction instead of 14.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ inline uint32_t f2bf2(float lo, float hi) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
+}
+__device__ inline uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
+
+// 8 BF16 values of a 16-byte vector as floats, and back.
+__device__ inline void unpack8(uint4 v, float (&f)[8]) {
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        f[2 * k] = bf2f((uint16_t)(w[k] & 0xffffu));
+        f[2 * k + 1] = bf2f((uint16_t)(w[k] >> 16));
+    }
+}
+__device__ inline uint4 pack8(const float (&f)[8]) {
+    uint32_t w[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[k] = f2bf2(f[2 * k], f[2 * k + 1]);
+    return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
 constexpr int BM = 64, BN = 64;          // weight-gradient output tile (rows x K entries)
@@ -320,7 +337,7 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a, float *__restrict__ pa
                 }
                 uint32_t pw[4];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) pw[k] = (uint32_t)f2bf(v[2 * k]) | ((uint32_t)f2bf(v[2 * k + 1]) << 16);
+                for (int k = 0; k < 4; ++k) pw[k] = f2bf2(v[2 * k], v[2 * k + 1]);
                 *(uint4 *)dst = make_uint4(pw[0], pw[1], pw[2], pw[3]);
             } else {
                 for (int k = 0; k < a.ncols - c; ++k) {
@@ -356,174 +373,232 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a, float *__restrict__ pa
         }
 }
 
-// 3 x 3 convolution of a 2D layer whose input channels come in chunks of 32
-// (a last, shorter chunk is zero-filled), on tiles of 8 x 32 pixels (the
-// image sizes must be multiples of those).  Per
-// chunk, the tile's input patch with its one-pixel halo (10 x 34 pixels) and
-// the chunk's weights of all 9 taps are staged in LDS once; the 9 taps then
-// read their MFMA operands from LDS, so each input pixel crosses L2 about
-// 1.3 times instead of 9.  Four wavefronts take two tile rows (64 pixels) each
-// and all TN output columns.  The epilogue stages the tile in the same LDS and
-// stores 8 channels of a pixel with one 16-byte write.
-constexpr int HY = 8, HX = 32, HPX = HX + 2, HP = (HY + 2) * HPX;   // tile rows, columns, patch
-constexpr int HC = 32;                                               // chunk channels (64-byte LDS rows)
+// 3 x 3 (3 x 3 x 3) convolution on image rows (the plane sizes must be
+// multiples of 8 x 32 pixels; input channels in chunks of 32, a last, shorter
+// chunk zero-filled).  Per chunk a block's input patch of 8 x 32 pixels with
+// its one-pixel halo is staged in LDS once.
+//
+// A wavefront computes WY rows x 16 columns x 32 output channels.  It holds the
+// 9 taps' weights of the chunk in registers and walks down the patch: the
+// fragment of input row yi at column offset dx serves output rows yi, yi - 1
+// and yi - 2 (taps dy = 0, 1, 2), so 3 (WY + 2) fragments feed its 18 WY MFMAs
+// (9 WY fragments with one per tap and output row).  Every output still adds
+// its taps in the order dy, dx, chunk by chunk.
+//
+// The weights are the A operand (rows = output channels) and row r of the
+// 16-row tile j stands for channel 8 (r >> 2) + 4 j + (r & 3), so that a lane
+// ends up with 8 consecutive channels of one pixel and stores them with one
+// 16-byte write straight from its accumulators.
+//
+// Bound by memory at 32 channels (16 x 256^2, 32 -> 32: 32.5 us, 4.1 TB/s),
+// by LDS reads and the two barriers of a stage above (64 -> 32: 64.5 us, 600
+// TFLOP/s; 64^2, 256 -> 128: 39.8 us, 970 TFLOP/s).  A fragment per tap and
+// output row with the output staged through LDS took 75 us (64 -> 32) and 97
+// us instead of 50 us (32 -> 64).
+constexpr int HY = 8, HX = 32, HPX = HX + 2;         // tile rows and columns, patch columns
+constexpr int HP = (HY + 2) * HPX;                   // patch pixels
+constexpr int HC = 32;                               // chunk channels
+constexpr int HS = HC + 8;                           // LDS row stride of the patch: rows padded by 16 B, so that 16
+                                                     // consecutive rows spread over all banks and taps are constant
+                                                     // offsets
 
-// Half-word offset of 16-byte granule g (0..3) of LDS row `row` in the halo
-// kernel's patch and weight tiles: the granules of a row are XOR-swizzled by
-// (row >> 2) & 3, so the 16 consecutive rows that an MFMA operand read
-// touches (one granule each) and the 4 rows x 4 granules of a staging write
-// fall on 16 distinct 16-byte bank groups.
-__device__ inline int hsw(int row, int g) { return row * HC + ((g ^ ((row >> 2) & 3)) << 3); }
+// Loads through a buffer resource: an offset past its range reads 0, which
+// stands for the zero padding.
+constexpr unsigned OOB = 0xFFFFFF00u;
+__device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const uint16_t *p, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)p, (short)0, (int)bytes, 0x00020000);
+}
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+__device__ inline uint4 bload16(__amdgpu_buffer_rsrc_t r, unsigned off) {
+    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+// The same load straight to LDS: lane l of the wavefront fills the 16 bytes at
+// dst + 16 l (dst uniform).  Complete after lds_wait() and a barrier.
+__device__ inline void bload16_lds(__amdgpu_buffer_rsrc_t r, uint16_t *dst, unsigned off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)dst, 16, off, 0, 0, 0);
+}
+__device__ inline void lds_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// In 3D a block takes one 8 x 32 tile of one plane z and, per chunk, runs
-// the same staging and 9 taps for each of the three input planes z - 1, z,
-// z + 1 (taps dz * 9 + dy * 3 + dx), skipping planes outside the volume.
-template <int TN, int DIMS>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_conv3x3_halo(ConvArgs a) {
-    constexpr int WNT = TN / 16;
-    constexpr int PATCH = HP * HC, WTS = 9 * TN * HC;
-    constexpr int TL = TN + 4;
-    constexpr int ELEMS = PATCH + WTS > 2 * 256 * TL ? PATCH + WTS : 2 * 256 * TL;
-    __shared__ __align__(16) uint16_t sm[ELEMS];
-    uint16_t *P = sm, *Wl = sm + PATCH;
+// Blocks take TN output channels: 64 (two column halves x two channel halves,
+// WY = 8), or 32 (two column halves x two row halves, WY = 4), and walk over
+// `per` consecutive tiles: the next stage's patch, of this tile or of the next
+// one, is loaded while the current stage multiplies.  A stage is a (chunk,
+// input plane) pair: in 3D a tile stays on one plane z and, per chunk, takes
+// the input planes z - 1, z, z + 1 in turn (taps dz * 9 + dy * 3 + dx), skipping
+// planes outside the volume.  RES: a 2D layer of one chunk, whose weights stay
+// in registers throughout; else every stage's weights pass through LDS, where
+// the next stage's are loaded (straight from memory) as soon as all wavefronts
+// have read the current ones.
+// PLAIN: BF16 output, overwritten.
+template <int TN, int DIMS, bool RES, bool PLAIN>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_conv3x3_rows(ConvArgs a, int per) {
+    constexpr int WY = TN == 32 ? 4 : 8;
+    __shared__ __align__(16) uint16_t P[HP * HS];
+    __shared__ __align__(16) uint16_t Wl[9 * TN * HC];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int tiles_x = a.w / HX, tiles_y = a.h / HY;
-    int bt = blockIdx.x;
-    const int tx = bt % tiles_x;
-    bt /= tiles_x;
-    const int ty = bt % tiles_y;
-    bt /= tiles_y;
-    const int z = DIMS == 3 ? bt % a.d : 0, b = DIMS == 3 ? bt / a.d : bt;
-    const int n0 = blockIdx.y * TN, y0 = ty * HY, x0 = tx * HX;
-    f32x4 acc[4][WNT];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < WNT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // Stages are (chunk, input plane) pairs; a plane outside the volume adds
-    // nothing and is skipped (block-uniform).  A stage's patch and weights
-    // are loaded into registers in one batch (every load in flight at once)
-    // while the previous stage multiplies, then written to LDS.
+    const int tiles_x = a.w / HX, tiles_y = a.h / HY, tiles_n = (a.ncols + TN - 1) / TN;
+    const int tiles = tiles_x * tiles_y * a.n * a.d;
+    // blocks of one XCD (every eighth) take neighbouring runs of tiles; the channel tiles of a run are adjacent
+    const int nb = (int)gridDim.x, q8 = nb >> 3, r8 = nb & 7, xcd = (int)blockIdx.x & 7;
+    const int bt = xcd * q8 + (xcd < r8 ? xcd : r8) + ((int)blockIdx.x >> 3);
+    const int n0 = (bt % tiles_n) * TN;
+    const int i0 = (bt / tiles_n) * per, i1 = min(i0 + per, tiles);
+    if (i0 >= i1) return;
+    const int wx = (wave & 1) * 16, wy = TN == 32 ? (wave >> 1) * WY : 0, wn = TN == 32 ? 0 : (wave >> 1) * 32;
     constexpr int NDZ = DIMS == 3 ? 3 : 1;
-    constexpr int NPL = (HP * 4 + 255) / 256, NWL = (9 * TN * 4 + 255) / 256;
-    const int nst = ((a.cin + HC - 1) / HC) * NDZ;          // a last chunk of fewer channels is zero-filled
-    auto plane_ok = [&](int st) { return DIMS == 2 || (unsigned)(z + st % NDZ - 1) < (unsigned)a.d; };
+    constexpr int NPL = (HP * 4 + 255) / 256;
+    const int nst = ((a.cin + HC - 1) / HC) * NDZ;    // stages of a tile
+    const int g8 = (t & 3) * 8;                       // the thread's channels of a pixel
+    int tx = 0, ty = 0, z = 0, b = 0;                 // the tile being loaded
+    auto place = [&](int i) {
+        tx = i % tiles_x;
+        i /= tiles_x;
+        ty = i % tiles_y;
+        i /= tiles_y;
+        z = DIMS == 3 ? i % a.d : 0;
+        b = DIMS == 3 ? i / a.d : i;
+    };
     auto next_stage = [&](int st) {
-        do ++st; while (st < nst && !plane_ok(st));
+        do ++st; while (DIMS == 3 && st < nst && (unsigned)(z + st % NDZ - 1) >= (unsigned)a.d);
         return st;
     };
-    uint4 pv[NPL], wv[NWL];
-    auto load = [&](int st) {
-        const int c0 = (st / NDZ) * HC, dz = st % NDZ;
-        const int zz = DIMS == 3 ? z + dz - 1 : 0, tap0 = DIMS == 3 ? dz * 9 : 0;
+    uint4 pv[NPL];
+    auto load_patch = [&](int st) {
+        const int c0 = (st / NDZ) * HC, zz = DIMS == 3 ? z + st % NDZ - 1 : 0;
+        const int y0 = ty * HY - 1, x0 = tx * HX - 1;  // the patch's first pixel
+        const uint16_t *in = a.in + ((((long long)b * a.d + zz) * a.h + y0) * a.w + x0) * a.in_cs + a.in_co + c0;
+        const __amdgpu_buffer_rsrc_t r = rsrc_of(in, (unsigned)(((HY + 1) * a.w + HPX) * a.in_cs) * 2u);
+        const bool con = c0 + g8 < a.cin;
 #pragma unroll
         for (int k = 0; k < NPL; ++k) {
-            const int e = t + 256 * k;
-            const int pp = e >> 2, g8 = (e & 3) * 8;
+            const int pp = (t >> 2) + 64 * k;
             const int py = pp / HPX, px = pp - py * HPX;
-            const int yy = y0 + py - 1, xx = x0 + px - 1;
-            pv[k] = make_uint4(0, 0, 0, 0);
-            if (e < HP * 4 && c0 + g8 < a.cin && (unsigned)yy < (unsigned)a.h && (unsigned)xx < (unsigned)a.w)
-                pv[k] = *(const uint4 *)(a.in + ((((long long)b * a.d + zz) * a.h + yy) * a.w + xx) * a.in_cs +
-                                         a.in_co + c0 + g8);
-        }
-#pragma unroll
-        for (int k = 0; k < NWL; ++k) {
-            const int e = t + 256 * k;
-            const int g8 = (e & 3) * 8, r = e >> 2;
-            const int tap = r / TN, n = r - tap * TN;
-            wv[k] = make_uint4(0, 0, 0, 0);
-            if (e < 9 * TN * 4 && c0 + g8 < a.cin && n0 + n < a.ncols)
-                wv[k] = *(const uint4 *)(a.wt + (long long)(n0 + n) * a.K + (tap0 + tap) * a.cin + c0 + g8);
+            const bool on = con && pp < HP && (unsigned)(y0 + py) < (unsigned)a.h && (unsigned)(x0 + px) < (unsigned)a.w;
+            pv[k] = bload16(r, on ? (unsigned)((py * a.w + px) * a.in_cs + g8) * 2u : OOB);
         }
     };
-    int st = plane_ok(0) ? 0 : next_stage(0);
-    if (st < nst) load(st);
-    for (; st < nst;) {
-        __syncthreads();                                   // the previous stage's operand reads are done
+    // The stage's weights to LDS: 64-byte rows (tap, then the rows of the 16-row tiles in operand order), whose
+    // 16-byte granules are XOR-swizzled by bits of the row so that an operand read spreads over all banks.
+    auto load_weights = [&](int st) {
+        const int c0 = (st / NDZ) * HC, off = n0 * a.K + (DIMS == 3 ? (st % NDZ) * 9 * a.cin : 0) + c0;
+        // channels past ncols lie past the range
+        const __amdgpu_buffer_rsrc_t r = rsrc_of(a.wt + off, (unsigned)(a.ncols * a.K - off) * 2u);
 #pragma unroll
-        for (int k = 0; k < NPL; ++k) {
-            const int e = t + 256 * k;
-            if (e < HP * 4) *(uint4 *)&P[hsw(e >> 2, e & 3)] = pv[k];
+        for (int k = 0; k < (9 * TN * 4 + 255) / 256; ++k) {
+            const int base = (4 * k + wave) * 64;
+            if (base >= 9 * TN * 4) break;
+            const int row = (base + lane) >> 2, g = ((lane & 3) ^ ((row >> 2) & 3)) * 8;
+            const int tap = row / TN, q = row - tap * TN;
+            const int n = (q & ~31) + ((q & 15) >> 2) * 8 + ((q >> 4) & 1) * 4 + (q & 3);
+            bload16_lds(r, Wl + base * 8, c0 + g < a.cin ? (unsigned)(n * a.K + tap * a.cin + g) * 2u : OOB);
         }
+    };
+    // the lane's granule of weight row (tap 0, tile 0) and of patch pixel (yi, dx) = (0, 0)
+    const uint16_t *wl = Wl + (wn + (lane & 15)) * HC + (((lane >> 4) ^ ((lane >> 2) & 3)) << 3);
+    const uint16_t *pl = P + (wy * HPX + wx + (lane & 15)) * HS + (lane >> 4) * 8;
+    bf16x8 wf[9][2];
+    auto read_weights = [&] {
 #pragma unroll
-        for (int k = 0; k < NWL; ++k) {
-            const int e = t + 256 * k;
-            if (e < 9 * TN * 4) *(uint4 *)&Wl[hsw(e >> 2, e & 3)] = wv[k];
-        }
+        for (int tap = 0; tap < 9; ++tap)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) wf[tap][j] = as_bf16x8(*(const uint4 *)(wl + (tap * TN + 16 * j) * HC));
+    };
+    f32x4 acc[WY][2];
+#pragma unroll
+    for (int i = 0; i < WY; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int c = n0 + wn + (lane >> 4) * 8;          // the lane's output channels
+    const bool relu = (a.flags & FLAG_RELU) != 0;
+    place(i0);
+    int i = i0, st = next_stage(-1);
+    load_patch(st);
+    load_weights(st);
+    if (RES) {
+        lds_wait();
         __syncthreads();
-        const int nx = next_stage(st);
-        if (nx < nst) load(nx);
-        st = nx;
-#pragma unroll 1
-        for (int tap = 0; tap < 9; ++tap) {
-            const int dy = tap / 3, dx = tap - dy * 3;       // tap (dx - 1, dy - 1) reads patch (+dx, +dy)
-            bf16x8 fb[WNT];
-#pragma unroll
-            for (int j = 0; j < WNT; ++j)
-                fb[j] = as_bf16x8(*(const uint4 *)&Wl[hsw(tap * TN + j * 16 + (lane & 15), lane >> 4)]);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int pr = 2 * wave + (i >> 1), pc = (i & 1) * 16 + (lane & 15);
-                const bf16x8 fa = as_bf16x8(*(const uint4 *)&P[hsw((pr + dy) * HPX + pc + dx, lane >> 4)]);
-#pragma unroll
-                for (int j = 0; j < WNT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fb[j], acc[i][j], 0, 0, 0);
-            }
-        }
+        read_weights();
     }
-    __syncthreads();                                       // the last stage's operand reads are done
-    // epilogue: tile pixel p = row * 32 + column, staged as floats in the same LDS
-    float *T = reinterpret_cast<float *>(sm);
+    while (true) {
+        if (!RES) lds_wait();                         // this stage's weights
+        __syncthreads();                              // the previous stage's operand reads are done
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+        for (int k = 0; k < NPL; ++k)
+            if ((t >> 2) + 64 * k < HP) *(uint4 *)&P[((t >> 2) + 64 * k) * HS + g8] = pv[k];
+        if (!RES) read_weights();
+        __syncthreads();
+        // the next stage, of this tile or of the next one
+        const int y = ty * HY + wy, x = tx * HX + wx + (lane & 15);
+        const long long m0 = (((long long)b * a.d + z) * a.h + y) * a.w + x;
+        st = next_stage(st);
+        const bool last = st >= nst;
+        if (last && ++i < i1) {
+            place(i);
+            st = next_stage(-1);
+        }
+        if (i < i1) {
+            load_patch(st);
+            if (!RES) load_weights(st);
+        }
+        // the fragments of row yi + 1 are read while row yi multiplies (left alone, the compiler reads each
+        // fragment right before its use and waits for it)
+        bf16x8 f[2][3];
+        auto read_row = [&](int yi) {
 #pragma unroll
-        for (int j = 0; j < WNT; ++j) {
-            const int cl = j * 16 + (lane & 15), c = n0 + cl;
-            const float bias = a.bias && c < a.ncols ? a.bias[c] : 0.f;
+            for (int dx = 0; dx < 3; ++dx) f[yi & 1][dx] = as_bf16x8(*(const uint4 *)(pl + (yi * HPX + dx) * HS));
+        };
+        read_row(0);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int p = (2 * wave + (i >> 1)) * HX + (i & 1) * 16 + (lane >> 4) * 4 + q;
-                float v = acc[i][j][q] + bias;
-                if (a.flags & FLAG_RELU) v = v > 0.f ? v : 0.f;
-                T[p * TL + cl] = v;
+        for (int yi = 0; yi < WY + 2; ++yi) {
+            if (yi + 1 < WY + 2) read_row(yi + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+                for (int dy = 0; dy < 3; ++dy) {
+                    const int o = yi - dy;
+                    if (o < 0 || o >= WY) continue;
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[o][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[dy * 3 + dx][j], f[yi & 1][dx], acc[o][j], 0, 0, 0);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (!last) continue;
+        // 8 channels of pixel (y + r, x) per lane
+        if (c < a.ncols) {
+            float bias[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            if (a.bias)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) bias[k] = a.bias[c + k];
+#pragma unroll
+            for (int r = 0; r < WY; ++r) {
+                const long long o = (m0 + (long long)r * a.w) * a.out_cs + a.out_co + c;
+                float v[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    v[k] = acc[r][k >> 2][k & 3] + bias[k];
+                    v[k] = relu && !(v[k] > 0.f) ? 0.f : v[k];
+                }
+                if (!PLAIN && a.out32) {
+                    float *dst = a.out32 + o;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) dst[k] = (a.flags & FLAG_ACC) ? dst[k] + v[k] : v[k];
+                    continue;
+                }
+                uint16_t *dst = a.out + o;
+                if (!PLAIN && (a.flags & FLAG_ACC)) {
+                    float old[8];
+                    unpack8(*(const uint4 *)dst, old);
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) v[k] += old[k];
+                }
+                *(uint4 *)dst = pack8(v);
             }
         }
-    __syncthreads();
-    constexpr int CG = TN / 8;
-    for (int e = t; e < 256 * CG; e += 256) {
-        const int p = e / CG, cl = (e - p * CG) * 8, c = n0 + cl;
-        if (c >= a.ncols) continue;
-        const long long m = (((long long)b * a.d + z) * a.h + y0 + p / HX) * a.w + x0 + (p % HX);
-        const float *src = &T[p * TL + cl];
-        const long long o = m * a.out_cs + a.out_co + c;
-        const int nk = a.ncols - c < 8 ? a.ncols - c : 8;
-        if (a.out32) {
-            float *dst = a.out32 + o;
-            for (int k = 0; k < nk; ++k) dst[k] = (a.flags & FLAG_ACC) ? dst[k] + src[k] : src[k];
-            continue;
-        }
-        uint16_t *dst = a.out + o;
-        if (nk == 8) {
-            float v[8];
+        if (i >= i1) break;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = src[k];
-            if (a.flags & FLAG_ACC) {
-                const uint4 old = *(const uint4 *)dst;
-                const uint32_t ow[4] = {old.x, old.y, old.z, old.w};
-#pragma unroll
-                for (int k = 0; k < 8; ++k) v[k] += bf2f((uint16_t)(ow[k >> 1] >> (16 * (k & 1))));
-            }
-            uint32_t pw[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) pw[k] = (uint32_t)f2bf(v[2 * k]) | ((uint32_t)f2bf(v[2 * k + 1]) << 16);
-            *(uint4 *)dst = make_uint4(pw[0], pw[1], pw[2], pw[3]);
-        } else {
-            for (int k = 0; k < nk; ++k) {
-                float v = src[k];
-                if (a.flags & FLAG_ACC) v += bf2f(dst[k]);
-                dst[k] = f2bf(v);
-            }
-        }
+        for (int r = 0; r < WY; ++r) acc[r][0] = acc[r][1] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 }
 
@@ -1033,21 +1108,6 @@ __global__ void k_pool_bwd(const uint16_t *__restrict__ in, int in_cs, int in_co
 // The same two passes on 8 channels of a pixel per thread with 16-byte
 // accesses (channel counts, strides and offsets multiples of 8, 16-byte
 // aligned buffers); per channel the same operations in the same order.
-__device__ inline void unpack8(uint4 v, float (&f)[8]) {
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        f[2 * k] = bf2f((uint16_t)(w[k] & 0xffffu));
-        f[2 * k + 1] = bf2f((uint16_t)(w[k] >> 16));
-    }
-}
-__device__ inline uint4 pack8(const float (&f)[8]) {
-    uint32_t w[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) w[k] = (uint32_t)f2bf(f[2 * k]) | ((uint32_t)f2bf(f[2 * k + 1]) << 16);
-    return make_uint4(w[0], w[1], w[2], w[3]);
-}
-
 __global__ void __launch_bounds__(256) k_pool_fwd8(const uint16_t *__restrict__ in, int in_cs, int in_co,
                                                    uint16_t *__restrict__ out, int out_cs, int out_co, int n, int d,
                                                    int h, int w, int C, int dims) {
@@ -1310,7 +1370,8 @@ static bool halo_ok(const ConvArgs &a) {
     return (a.dims == 2 || a.dims == 3) && a.ks == 3 && !(a.flags & (FLAG_S2D | FLAG_D2S)) && a.cin % 8 == 0 &&
            a.h % HY == 0 &&
            a.w % HX == 0 && ((a.in_cs | a.in_co | a.out_cs | a.out_co) & 7) == 0 && ((uintptr_t)a.in & 15) == 0 &&
-           (ob & 15) == 0;
+           (ob & 15) == 0 && 18LL * a.w * a.in_cs < (1LL << 31) && (long long)a.ncols * a.K < (1LL << 31) &&
+           a.M < (1LL << 31);
 }
 
 // Sum of the K splits of a convolution, in split order, then the epilogue
@@ -1338,7 +1399,7 @@ __global__ void __launch_bounds__(256) k_conv_reduce(ConvArgs a, const float *__
 // K splits for a convolution whose output tiles are too few to fill the
 // GPU (the deep, low-resolution layers, whose long K loop would run on a
 // few CUs): enough splits for about 1024 blocks, each at least 4 K steps of
-// 64; 1 when the layer has 512 tiles or more, or takes the halo kernel.
+// 64; 1 when the layer has 512 tiles or more, or takes the row kernel.
 static long long conv_tiles(const ConvArgs &a) {
     return (long long)blocks(a.M, 64) * (a.ncols <= 32 ? 1 : (a.ncols + 63) / 64);
 }
@@ -1373,17 +1434,31 @@ hipError_t conv_split(const ConvArgs &a, float *part, int S, hipStream_t s) {
 }
 
 hipError_t conv(const ConvArgs &a, hipStream_t s) {
-    // the halo kernel holds 2 - 3 blocks per CU: below 512 blocks the im2col kernel fills the chip better
-    const long long tiles = halo_ok(a) ? (long long)a.n * a.d * (a.h / HY) * (a.w / HX) : 0;
+    // the row kernel holds 2 blocks per CU: below 512 tiles of 8 x 32 pixels the im2col kernel fills the chip better
     if (conv_halo(a)) {
-        const dim3 grid((unsigned)tiles, a.ncols <= 32 ? 1u : (unsigned)((a.ncols + 63) / 64));
+        const int tn = a.ncols <= 32 ? 32 : 64, tiles_n = (a.ncols + tn - 1) / tn;
+        const long long tiles = (long long)a.n * a.d * (a.h / HY) * (a.w / HX);
+        const bool res = a.dims == 2 && a.cin <= HC;
+        const bool plain = !a.out32 && !(a.flags & FLAG_ACC);
+        // two blocks per CU, each walking over as many tiles as that leaves it
+        const int runs = (512 + tiles_n - 1) / tiles_n, per = (int)((tiles + runs - 1) / runs);
+        const dim3 grid((unsigned)((tiles + per - 1) / per * tiles_n));
+#define CALL(TN, DIMS, RES)                                                                                     \
+    do {                                                                                                        \
+        if (plain) hipLaunchKernelGGL((k_conv3x3_rows<TN, DIMS, RES, true>), grid, dim3(256), 0, s, a, per);    \
+        else hipLaunchKernelGGL((k_conv3x3_rows<TN, DIMS, RES, false>), grid, dim3(256), 0, s, a, per);         \
+    } while (0)
         if (a.dims == 3) {
-            if (a.ncols <= 32) hipLaunchKernelGGL((k_conv3x3_halo<32, 3>), grid, dim3(256), 0, s, a);
-            else hipLaunchKernelGGL((k_conv3x3_halo<64, 3>), grid, dim3(256), 0, s, a);
+            if (tn == 32) CALL(32, 3, false);
+            else CALL(64, 3, false);
+        } else if (tn == 32) {
+            if (res) CALL(32, 2, true);
+            else CALL(32, 2, false);
         } else {
-            if (a.ncols <= 32) hipLaunchKernelGGL((k_conv3x3_halo<32, 2>), grid, dim3(256), 0, s, a);
-            else hipLaunchKernelGGL((k_conv3x3_halo<64, 2>), grid, dim3(256), 0, s, a);
+            if (res) CALL(64, 2, true);
+            else CALL(64, 2, false);
         }
+#undef CALL
         return hipGetLastError();
     }
     if (a.ncols <= 32) {

@@ -128,6 +128,34 @@ def test_conv_forward_bf16_relu_and_accumulate(dims, ks, grid, cin, cout):
     assert np.all(np.abs(got[..., cout:] - exp) <= 2 ** -7 * np.abs(exp) + 1e-5)
 
 
+# edges of the 3 x 3 row kernel: tile counts that the blocks' runs do not divide, a last chunk of 8
+# channels, 8 channels past a 64-channel tile, one chunk (weights kept in registers) and several, 2D
+# and 3D, both channel tiles, all four forms of the output in a channel slice of wider tensors
+ROWS = [(2, (9, 1, 104, 160), 24, 8), (2, (9, 1, 104, 160), 32, 40), (2, (7, 1, 160, 128), 72, 72),
+        (2, (7, 1, 160, 128), 40, 32), (3, (3, 5, 120, 96), 8, 24), (3, (3, 5, 120, 96), 40, 72)]
+
+
+@pytest.mark.parametrize("dims,grid,cin,cout", ROWS)
+def test_row_kernel_edges(dims, grid, cin, cout):
+    rng = np.random.default_rng(5)
+    C = C_()
+    x = bf(rng.standard_normal(grid + (cin + 16,)))
+    W = bf(rng.standard_normal((cout, 3 ** dims, cin)) / np.sqrt(cin * 3 ** dims))
+    b = rng.standard_normal(cout).astype(np.float32)
+    old = bf(rng.standard_normal(grid + (cout + 16,)))
+    ref = N.conv_fwd(x[..., 8:8 + cin], W, b.astype(np.float64), 3, dims)
+    for flags in (C.NN_RELU, C.NN_ACCUMULATE):
+        exp = np.maximum(ref, 0) if flags == C.NN_RELU else old[..., 8:8 + cout] + ref
+        for out32 in (True, False):
+            out = torch.from_numpy(old).float().cuda() if out32 else dev_bf(old)
+            conv_call(dev_bf(x), dev_bf(W.reshape(cout, -1)), torch.from_numpy(b).cuda(), 3, dims, cout, flags=flags,
+                      out32=out32, cin=cin, in_co=8, out=out, out_co=8)
+            got = out.double().cpu().numpy()
+            assert np.array_equal(got[..., :8], old[..., :8]) and np.array_equal(got[..., 8 + cout:], old[..., 8 + cout:])
+            # FP32 accumulation over up to 1080 products of unit-variance sums; BF16 outputs add one rounding
+            assert np.all(np.abs(got[..., 8:8 + cout] - exp) <= (0 if out32 else 2 ** -7) * np.abs(exp) + 1e-5)
+
+
 @pytest.mark.parametrize("dims,ks,grid,cin,cout", CASES)
 def test_conv_input_gradient(dims, ks, grid, cin, cout):
     rng = np.random.default_rng(3)
