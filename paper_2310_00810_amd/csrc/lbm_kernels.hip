@@ -25,11 +25,28 @@ namespace lbm {
 #define FLUID_PROLOGUE()                                                    \
     constexpr int D = Vel<Q>::D;                                            \
     __shared__ TileLds L;                                                   \
-    const FTile t = fluid_tile<D>(G, xcd_tile(blockIdx.x, gridDim.x));      \
+    const FTile t = fluid_tile<D>(G, xcd_tile(blockIdx.x, G.n_ftiles));     \
     const InstDev &I = G.inst[t.b];                                         \
     if (t.staged) stage_windows<D>(G, I, t, L);                             \
     __syncthreads();                                                        \
     const FLane n = fluid_lane(G, I, t, L)
+
+// The step and adjoint-step kernels take what their prologue and first loads
+// need as leading scalars, which arrive in registers with the wavefront: read
+// from the argument block, they put a scalar load before every chain (a step
+// of a 64^3 sphere box, bound by that chain: 8.9 -> 8.3 us; at 256^3, 468 us,
+// nothing).  bc = bcy | bcz << 8.
+__device__ inline Geo geo_of(const FTileDesc *fblk, const InstDev *inst, const uint2 *rw, int n_ftiles, int bc) {
+    Geo G{};
+    G.fblk = fblk;
+    G.inst = inst;
+    G.rw = rw;
+    G.n_ftiles = n_ftiles;
+    G.bcy = bc & 255;
+    G.bcz = bc >> 8;
+    return G;
+}
+static int packed_bc(const Geo &G) { return G.bcy | G.bcz << 8; }
 
 // Face density of a node on a Zou-He face (issued before the gathers).
 template <int BCX>
@@ -59,10 +76,12 @@ __device__ inline void face_unknown_adjoints(__amdgpu_buffer_rsrc_t rn, int plan
 // state when two exceed the Infinity Cache), 2 non-temporal gathers too
 // (D3Q19 states beyond the Infinity Cache).
 template <int Q, int BCX, int NTM>
-__global__ void __launch_bounds__(FT) k_step(Geo G, const float *__restrict__ src,
-                                             float *__restrict__ dst,
+__global__ void __launch_bounds__(FT) k_step(const FTileDesc *__restrict__ fblk, const InstDev *__restrict__ inst,
+                                             const uint2 *__restrict__ rw, int n_ftiles, int bc,
+                                             const float *__restrict__ src, float *__restrict__ dst,
                                              const float *__restrict__ face_in,
                                              const float *__restrict__ face_out) {
+    const Geo G = geo_of(fblk, inst, rw, n_ftiles, bc);
     FLUID_PROLOGUE();
     if (!n.active) return;
     const bool in = density_faces(BCX) && n.x == 0, out = density_faces(BCX) && n.x == I.nx - 1;
@@ -207,7 +226,9 @@ __global__ void __launch_bounds__(FT) k_adj_seed(Geo G, const float *__restrict_
 //   A   = sum_k lam_k dfeq_k/drho = S0 (1 + 1.5 u.u) - 4.5 u.S2.u,
 //   B_a = sum_k lam_k dfeq_k/dj_a = 3 S_a + 9 (S2 u)_a - 3 u_a S0.
 template <int Q, int BCX, bool SEED, bool NT>
-__global__ void __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(6))) k_adj_step(Geo G, const float *__restrict__ Fprev,
+__global__ void __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(6))) k_adj_step(const FTileDesc *__restrict__ fblk, const InstDev *__restrict__ inst,
+                                                 const uint2 *__restrict__ rw, int n_ftiles, int bc,
+                                                 const float *__restrict__ Fprev,
                                                  const float *__restrict__ nu_in,
                                                  float *__restrict__ nu_out,
                                                  const float *__restrict__ face_in,
@@ -216,7 +237,8 @@ __global__ void __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(6))) k_
                                                  double *__restrict__ grad_out,
                                                  double *__restrict__ dtau_part,
                                                  const float *__restrict__ roi,
-                                                 const float *__restrict__ target, int kind) {
+                                                 const float *__restrict__ target, int kind, Geo GM) {
+    const Geo G = geo_of(fblk, inst, rw, n_ftiles, bc);   // GM: the collision model (D2Q9)
     using V = Vel<Q>;
     __shared__ double red[4];
     FLUID_PROLOGUE();
@@ -259,10 +281,10 @@ __global__ void __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(6))) k_
         // symmetric), with dL/dtau from the two stress rates only
         float mu[Q];
         bool mrt = false;
-        if constexpr (Q == 9) mrt = G.coll == COLL_MRT;
+        if constexpr (Q == 9) mrt = GM.coll == COLL_MRT;
         if constexpr (Q == 9) {
             if (mrt) {
-                mrt_relax(lam, G.mrt, I.omega, mu);
+                mrt_relax(lam, GM.mrt, I.omega, mu);
                 float y7 = 0.f, y8 = 0.f, d7 = 0.f, d8 = 0.f, feq[9];
                 feq_all<Q>(m, feq);
 #pragma unroll
@@ -579,11 +601,12 @@ hipError_t launch_step(const Geo &G, const float *src, float *dst, const float *
     // beyond the Infinity Cache every step streams, gathers included; a step
     // into the tape streams its stores
     const int ntm = G.nt ? 2 : (tape ? 1 : 0);
+#define PRE G.fblk, G.inst, G.rw, G.n_ftiles, packed_bc(G)
 #define CALL(Q, B)                                                                                 \
     do {                                                                                           \
-        if (ntm == 2) hipLaunchKernelGGL((k_step<Q, B, 2>), fgrid_of(G), dim3(FT), 0, s, G, src, dst, fin, fout); \
-        else if (ntm == 1) hipLaunchKernelGGL((k_step<Q, B, 1>), fgrid_of(G), dim3(FT), 0, s, G, src, dst, fin, fout); \
-        else hipLaunchKernelGGL((k_step<Q, B, 0>), fgrid_of(G), dim3(FT), 0, s, G, src, dst, fin, fout); \
+        if (ntm == 2) hipLaunchKernelGGL((k_step<Q, B, 2>), fgrid_of(G), dim3(FT), 0, s, PRE, src, dst, fin, fout); \
+        else if (ntm == 1) hipLaunchKernelGGL((k_step<Q, B, 1>), fgrid_of(G), dim3(FT), 0, s, PRE, src, dst, fin, fout); \
+        else hipLaunchKernelGGL((k_step<Q, B, 0>), fgrid_of(G), dim3(FT), 0, s, PRE, src, dst, fin, fout); \
     } while (0)
     DISPATCH_BCX19(G.bcx, CALL);
 #undef CALL
@@ -622,17 +645,18 @@ hipError_t launch_adj_step(int q, const Geo &G, const float *Fprev, const float 
 #define CALL(Q, B)                                                                                 \
     do {                                                                                           \
         if (target)                                                                                \
-            hipLaunchKernelGGL((k_adj_step<Q, B, true, false>), fgrid_of(G), dim3(FT), 0, s, G, Fprev, nu_in, \
-                               nu_out, fin, fout, gin, gout, dtau_part, roi, target, kind);         \
+            hipLaunchKernelGGL((k_adj_step<Q, B, true, false>), fgrid_of(G), dim3(FT), 0, s, PRE, Fprev, nu_in, \
+                               nu_out, fin, fout, gin, gout, dtau_part, roi, target, kind, G);      \
         else if (G.nt)                                                                             \
-            hipLaunchKernelGGL((k_adj_step<Q, B, false, true>), fgrid_of(G), dim3(FT), 0, s, G, Fprev, nu_in, \
-                               nu_out, fin, fout, gin, gout, dtau_part, roi, target, kind);         \
+            hipLaunchKernelGGL((k_adj_step<Q, B, false, true>), fgrid_of(G), dim3(FT), 0, s, PRE, Fprev, nu_in, \
+                               nu_out, fin, fout, gin, gout, dtau_part, roi, target, kind, G);      \
         else                                                                                       \
-            hipLaunchKernelGGL((k_adj_step<Q, B, false, false>), fgrid_of(G), dim3(FT), 0, s, G, Fprev, nu_in, \
-                               nu_out, fin, fout, gin, gout, dtau_part, roi, target, kind);         \
+            hipLaunchKernelGGL((k_adj_step<Q, B, false, false>), fgrid_of(G), dim3(FT), 0, s, PRE, Fprev, nu_in, \
+                               nu_out, fin, fout, gin, gout, dtau_part, roi, target, kind, G);      \
     } while (0)
     DISPATCH_BCX(q, G.bcx, CALL);
 #undef CALL
+#undef PRE
     return hipGetLastError();
 }
 
