@@ -194,17 +194,20 @@ __device__ inline long long out_index(const ConvArgs &a, long long m, int c, int
 // splits and applies the epilogue).
 template <int TBM, int TBN, bool SPLIT = false>
 __global__ void __launch_bounds__(256) k_conv(ConvArgs a, float *__restrict__ part = nullptr, int sper = 0) {
-    constexpr int KB = 64, LD = KB + 8;             // LDS rows padded by 16 B
+    constexpr int KB = 64;
     constexpr int WM = TBM / 2, WN = TBN / 2;
     constexpr int TI = WM / 16, TJ = WN / 16;
     constexpr int AL = TBM * 8 / 256, BL = TBN * 8 / 256;   // 16-byte loads per thread
-    __shared__ uint16_t As[2][TBM][LD];
-    __shared__ uint16_t Bs[2][TBN][LD];
+    __shared__ __align__(16) uint16_t S[2 * (TBM + TBN) * KB];
+    auto As = reinterpret_cast<uint16_t(*)[TBM][KB]>(S);
+    auto Bs = reinterpret_cast<uint16_t(*)[TBN][KB]>(S + 2 * TBM * KB);
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int wm = wave & 1, wn = wave >> 1;
     const long long m0 = (long long)blockIdx.x * TBM;
     const int n0 = blockIdx.y * TBN;
     const int kq = (t & 7) * 8;
+    // 128-byte LDS rows; granules exchanged by (row >> 1) & 7 for the same reason as in granule()
+    const int kw = ((t & 7) ^ ((t >> 4) & 7)) * 8;
     // rows of the im2col tile this thread loads: t / 8 + 32 l; their pixels are fixed
     Row row[AL];
 #pragma unroll
@@ -224,9 +227,9 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a, float *__restrict__ pa
     };
     auto stash = [&](int buf) {
 #pragma unroll
-        for (int l = 0; l < AL; ++l) *(uint4 *)&As[buf][(t >> 3) + 32 * l][kq] = ra[l];
+        for (int l = 0; l < AL; ++l) *(uint4 *)&As[buf][(t >> 3) + 32 * l][kw] = ra[l];
 #pragma unroll
-        for (int l = 0; l < BL; ++l) *(uint4 *)&Bs[buf][(t >> 3) + 32 * l][kq] = rb[l];
+        for (int l = 0; l < BL; ++l) *(uint4 *)&Bs[buf][(t >> 3) + 32 * l][kw] = rb[l];
     };
     f32x4 acc[TI][TJ];
 #pragma unroll
@@ -243,7 +246,7 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a, float *__restrict__ pa
         if (s + 1 < steps) load((s + 1) * KB);
 #pragma unroll
         for (int kh = 0; kh < KB; kh += 32) {
-            const int kr = kh + (lane >> 4) * 8;
+            const int kr = (((kh >> 3) + (lane >> 4)) ^ ((lane >> 1) & 7)) * 8;
             bf16x8 fb[TJ];
 #pragma unroll
             for (int j = 0; j < TJ; ++j) fb[j] = as_bf16x8(*(const uint4 *)&Bs[buf][wn * WN + j * 16 + (lane & 15)][kr]);
@@ -277,12 +280,12 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a, float *__restrict__ pa
     const int cr = d2s ? a.ncols >> a.dims : a.ncols;      // D2S: columns sub * cr + co
     const uintptr_t base = a.out32 ? (uintptr_t)a.out32 : (uintptr_t)a.out;
     if (((a.out_cs | a.out_co) & 7) == 0 && (!d2s || (cr & 7) == 0) && (base & 15) == 0) {
-        // the tile goes through LDS (the A buffers are free after the last barrier) so that each
+        // the tile goes through LDS (the buffers are free after the last barrier) so that each
         // thread stores 8 consecutive channels of a pixel (of the fine pixel for D2S, whose
         // 8-column groups stay inside one sub-pixel) with 16-byte writes
         constexpr int TL = TBN + 4;
-        static_assert(TBM * TL * 4 <= (int)sizeof(As), "epilogue tile must fit in the A buffers");
-        float *T = reinterpret_cast<float *>(&As[0][0][0]);
+        static_assert(TBM * TL * 4 <= (int)sizeof(S), "epilogue tile must fit in the buffers");
+        float *T = reinterpret_cast<float *>(S);
 #pragma unroll
         for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -391,16 +394,18 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a, float *__restrict__ pa
 // 16-byte write straight from its accumulators.
 //
 // Bound by memory at 32 channels (16 x 256^2, 32 -> 32: 32.5 us, 4.1 TB/s),
-// by LDS reads and the two barriers of a stage above (64 -> 32: 64.5 us, 600
-// TFLOP/s; 64^2, 256 -> 128: 39.8 us, 970 TFLOP/s).  A fragment per tap and
-// output row with the output staged through LDS took 75 us (64 -> 32) and 97
-// us instead of 50 us (32 -> 64).
+// by the two barriers of a stage above (64 -> 32: 57.7 us, 670 TFLOP/s; 64^2,
+// 256 -> 128: 37.4 us, 1035 TFLOP/s).  A fragment per tap and output row with
+// the output staged through LDS took 75 us (64 -> 32) and 97 us instead of 48
+// us (32 -> 64).
 constexpr int HY = 8, HX = 32, HPX = HX + 2;         // tile rows and columns, patch columns
 constexpr int HP = (HY + 2) * HPX;                   // patch pixels
 constexpr int HC = 32;                               // chunk channels
-constexpr int HS = HC + 8;                           // LDS row stride of the patch: rows padded by 16 B, so that 16
-                                                     // consecutive rows spread over all banks and taps are constant
-                                                     // offsets
+// 16-byte granule of channels 8 g .. 8 g + 7 in the 64-byte LDS row of pixel (or weight row) r.  A 16-byte operand
+// read serves the lanes 0-3, 12-15, 20-23, 24-27 at a time, then 4-7, 8-11, 16-19, 28-31, and so on: with this
+// exchange the 16 rows they touch, at whichever row they start, cover all 64 banks (rows padded to 80 bytes met
+// every bank twice: 8.8 instead of 4.4 cycles a read).
+__device__ inline int granule(int r, int g) { return g ^ ((r >> 1) & 2); }
 
 // Loads through a buffer resource: an offset past its range reads 0, which
 // stands for the zero padding.
@@ -435,7 +440,7 @@ template <int TN, int DIMS, bool RES, bool PLAIN>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 k_conv3x3_rows(ConvArgs a, int per) {
     constexpr int WY = TN == 32 ? 4 : 8;
-    __shared__ __align__(16) uint16_t P[HP * HS];
+    __shared__ __align__(16) uint16_t P[HP * HC];
     __shared__ __align__(16) uint16_t Wl[9 * TN * HC];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int tiles_x = a.w / HX, tiles_y = a.h / HY, tiles_n = (a.ncols + TN - 1) / TN;
@@ -479,8 +484,7 @@ k_conv3x3_rows(ConvArgs a, int per) {
             pv[k] = bload16(r, on ? (unsigned)((py * a.w + px) * a.in_cs + g8) * 2u : OOB);
         }
     };
-    // The stage's weights to LDS: 64-byte rows (tap, then the rows of the 16-row tiles in operand order), whose
-    // 16-byte granules are XOR-swizzled by bits of the row so that an operand read spreads over all banks.
+    // The stage's weights to LDS: rows (tap, then the rows of the 16-row tiles in operand order).
     auto load_weights = [&](int st) {
         const int c0 = (st / NDZ) * HC, off = n0 * a.K + (DIMS == 3 ? (st % NDZ) * 9 * a.cin : 0) + c0;
         // channels past ncols lie past the range
@@ -489,15 +493,20 @@ k_conv3x3_rows(ConvArgs a, int per) {
         for (int k = 0; k < (9 * TN * 4 + 255) / 256; ++k) {
             const int base = (4 * k + wave) * 64;
             if (base >= 9 * TN * 4) break;
-            const int row = (base + lane) >> 2, g = ((lane & 3) ^ ((row >> 2) & 3)) * 8;
+            const int row = (base + lane) >> 2, g = granule(row, lane & 3) * 8;
             const int tap = row / TN, q = row - tap * TN;
             const int n = (q & ~31) + ((q & 15) >> 2) * 8 + ((q >> 4) & 1) * 4 + (q & 3);
             bload16_lds(r, Wl + base * 8, c0 + g < a.cin ? (unsigned)(n * a.K + tap * a.cin + g) * 2u : OOB);
         }
     };
-    // the lane's granule of weight row (tap 0, tile 0) and of patch pixel (yi, dx) = (0, 0)
-    const uint16_t *wl = Wl + (wn + (lane & 15)) * HC + (((lane >> 4) ^ ((lane >> 2) & 3)) << 3);
-    const uint16_t *pl = P + (wy * HPX + wx + (lane & 15)) * HS + (lane >> 4) * 8;
+    // the lane's granules of weight row (tap 0, tile 0) and of the patch pixels (0, dx)
+    const uint16_t *wl = Wl + (wn + (lane & 15)) * HC + granule(lane & 15, lane >> 4) * 8;
+    const uint16_t *pl[3];
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx) {
+        const int px = wx + (lane & 15) + dx;
+        pl[dx] = P + (wy * HPX + px) * HC + granule(px, lane >> 4) * 8;
+    }
     bf16x8 wf[9][2];
     auto read_weights = [&] {
 #pragma unroll
@@ -523,8 +532,10 @@ k_conv3x3_rows(ConvArgs a, int per) {
         if (!RES) lds_wait();                         // this stage's weights
         __syncthreads();                              // the previous stage's operand reads are done
 #pragma unroll
-        for (int k = 0; k < NPL; ++k)
-            if ((t >> 2) + 64 * k < HP) *(uint4 *)&P[((t >> 2) + 64 * k) * HS + g8] = pv[k];
+        for (int k = 0; k < NPL; ++k) {
+            const int pp = (t >> 2) + 64 * k;
+            if (pp < HP) *(uint4 *)&P[pp * HC + granule(pp % HPX, t & 3) * 8] = pv[k];
+        }
         if (!RES) read_weights();
         __syncthreads();
         // the next stage, of this tile or of the next one
@@ -545,7 +556,7 @@ k_conv3x3_rows(ConvArgs a, int per) {
         bf16x8 f[2][3];
         auto read_row = [&](int yi) {
 #pragma unroll
-            for (int dx = 0; dx < 3; ++dx) f[yi & 1][dx] = as_bf16x8(*(const uint4 *)(pl + (yi * HPX + dx) * HS));
+            for (int dx = 0; dx < 3; ++dx) f[yi & 1][dx] = as_bf16x8(*(const uint4 *)(pl[dx] + yi * HPX * HC));
         };
         read_row(0);
 #pragma unroll
@@ -768,15 +779,16 @@ __global__ void __launch_bounds__(256) k_wgrad(ConvArgs a, const uint16_t *__res
         }
 }
 
-// Weight gradient of a 2D 3 x 3 convolution from halo-staged patches.  The
-// generic kernel above gathers the im2col matrix, i.e. every input pixel 9
-// times, and transposes it in registers.  Here a stage is a patch of
-// PH x PW = 128 pixels of one image: its G rows and its input pixels with
-// the one-pixel halo are copied into LDS once, pixel-major as they lie in
-// memory (16-byte chunks, no transposes), and the nine taps are LDS row
-// offsets of the same halo tile.  The MFMA operands, which run over pixels
-// (the contraction index), come out of LDS through the gfx950 transposing
-// read ds_read_b64_tr_b16.
+// Weight gradient of a 3 x 3 (x 3) convolution on image rows.  The generic
+// kernel above gathers the im2col matrix, i.e. every input pixel 9 times, and
+// transposes it in registers.  Here a group of wavefronts walks down a strip
+// of 32 columns: the rows of the input (with one column of halo on each side)
+// and of G are copied into LDS once, pixel-major as they lie in memory, and
+// the MFMA operands, which run over the 32 pixels of a row (the contraction
+// index), come out of LDS through the gfx950 transposing read
+// ds_read_b64_tr_b16.  The three operands of G's last rows stay in registers,
+// so that an input row's operand at column offset dx serves the taps dy = 0,
+// 1, 2 at once: 2 + 3 operands are read for 18 MFMAs (11 with one per tap).
 //
 // Lane layout of that read: in each group of 16 lanes, lane 4e + c names the
 // 8-byte block holding columns 4c .. 4c + 3 of row e, and lane i receives
@@ -784,12 +796,6 @@ __global__ void __launch_bounds__(256) k_wgrad(ConvArgs a, const uint16_t *__res
 // or column l & 15, K entries 8 (l >> 4) .. + 7) is the pair of reads
 // h = 0, 1 in which lane 16 G + 4 e + c names K entry 8 G + 4 h + e, column
 // block c.
-//
-// Block: RB = 32 WR rows x CB = 16 WC input channels x all 9 taps; wavefront
-// w takes 32 rows (two m tiles) x 16 channels (one n tile) x the taps of
-// its group (4 / (WR WC) groups split the 9 taps).  blockIdx.z takes a
-// contiguous range of `per` patches.  A layer of 8 input channels runs as a
-// 16-channel tile whose upper 8 channels are staged as zeros and not stored.
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef short v8s __attribute__((ext_vector_type(8)));
 __device__ inline v4s lds_tr(const uint16_t *p) {
@@ -800,165 +806,238 @@ __device__ inline bf16x8 tr_operand(const uint16_t *p0, const uint16_t *p1) {
     return __builtin_bit_cast(bf16x8, v);
 }
 
-// The MFMAs of one stage for taps T0 .. T1 - 1: x0 / x1 and g0 / g1 are the
-// lane's read addresses (h = 0, 1) for the patch's first 32 pixels; the
-// other 32-pixel chunks and the taps are constant offsets.
-template <int PW, int XS, int GS, int T0, int T1, int NTAP>
-__device__ inline void wgrad_halo_stage(const uint16_t *x0, const uint16_t *x1, const uint16_t *g0,
-                                        const uint16_t *g1, f32x4 (&acc)[NTAP][2]) {
-    constexpr int HW = PW + 2;
-#pragma unroll
-    for (int kc = 0; kc < 4; ++kc) {
-        const int go = kc * 32 * GS, xo = kc * (32 / PW) * HW * XS;
-        bf16x8 fa[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) fa[i] = tr_operand(g0 + go + 16 * i, g1 + go + 16 * i);
-#pragma unroll
-        for (int tap = T0; tap < T1; ++tap) {
-            const int o = xo + ((tap / 3 - 1) * HW + tap % 3 - 1) * XS;
-            const bf16x8 fb = tr_operand(x0 + o, x1 + o);
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-                acc[tap - T0][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb, acc[tap - T0][i], 0, 0, 0);
-        }
-    }
-}
+// Block: RB = 32 WR rows x CB = 16 WC input channels x the 9 taps of one plane
+// offset; a wavefront takes 32 rows (two m tiles) x 16 channels x 9 taps, and
+// WK = 8 / (WR WC) groups of WR x WC wavefronts walk over different strips.  Their
+// sums meet in LDS at the end: one block of 8 wavefronts per CU leaves half the
+// partials of two blocks of 4.  PW = 16 (planes at most 16 columns wide): the
+// 32 columns of a strip are those of two planes.  A strip is cut into segments
+// of `len` rows; walker v (block part z, group k: v = z WK + k) takes the
+// segments v per .. v per + per - 1.  Step k of a segment that starts at row y0
+// meets input row y0 - 1 + k with rows y0 + k, y0 + k - 1 and y0 + k - 2 of G;
+// G reads 0 outside the segment, the input outside the plane.  WG_NR steps are
+// staged at a time: the next ones are loaded while the current ones multiply,
+// and go to the other LDS buffer.
+//
+// A pixel is a 64-byte row of LDS (32 channels; wider blocks stack such slabs);
+// its two 16-channel halves trade places in every second run of 8 pixels, so
+// that the 32 lanes that a transposing read serves at a time (4 pixels each of
+// two runs, 32 bytes a pixel) cover all 64 banks.  A layer of 8 input channels
+// keeps 16-byte rows and computes its 8 channels twice.
+//
+// 16 x 256^2, 32 -> 32: 29 us (4.6 TB/s; sum of the partials 4 us), bound by
+// memory; 16 x 64^2, 128 -> 128: 27 us, of which 12 us are the launch, the first
+// loads and the partials and the rest the stages (twice their MFMA time); with
+// an operand per tap and 128-pixel patches, one launch per plane offset and
+// 400 - 630 blocks' partials, these layers took 47 and 40 us with their sums,
+// and 2 x 64^3, 64 -> 32, 172 us instead of 71 us.  Six steps a stage: the same.
+constexpr int WG_NR = 3;
+struct WgradWalk { int len, pieces, per, sps, z; };   // segment rows, segments per strip, segments per walker,
+                                                      // stages per segment, block parts
 
-template <int PW, int WR, int WC>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_wgrad_halo(ConvArgs a, const uint16_t *__restrict__ g, int g_cs,
-                                                    int g_co, int rows, float *__restrict__ part, int per,
-                                                    int dz) {
-    constexpr int PH = 128 / PW, HW = PW + 2, HP = (PH + 2) * HW;
-    constexpr int RB = 32 * WR, CB = 16 * WC, WT = 4 / (WR * WC);
-    constexpr int NTAP = (9 + WT - 1) / WT;
-    constexpr int XS = CB + 8, GS = RB + 8;              // LDS row strides (halfwords), rows padded by 16 B
-    constexpr int XCH = CB / 8, GCH = RB / 8;            // 16-byte chunks per pixel
-    constexpr int XN = (HP * XCH + 255) / 256, GN = 128 * GCH / 256;
-    static_assert(WT == 1 || WT == 2 || WT == 4, "taps split over 1, 2 or 4 wavefront groups");
-    __shared__ __align__(16) uint16_t Xs[HP * XS];
-    __shared__ __align__(16) uint16_t Gs[128 * GS];
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int wr = wave % WR, wc = (wave / WR) % WC, wt = wave / (WR * WC);
-    const int r0 = blockIdx.x * RB, ci0 = blockIdx.y * CB;
-    const int npx = (a.w + PW - 1) / PW, npy = (a.h + PH - 1) / PH;
-    const int pb = blockIdx.z * per, pe = min(pb + per, a.n * a.d * npx * npy);
-    // the lane's transposing-read addresses for the first 32 pixels
-    const int G = lane >> 4, e = (lane >> 2) & 3, c = lane & 3;
-    const uint16_t *xr[2], *gr[2];
+template <int PW, int WR, int WC, bool C8>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+k_wgrad_rows(ConvArgs a, const uint16_t *__restrict__ g, int g_cs, int g_co, int rows, float *__restrict__ part,
+             WgradWalk wk) {
+    constexpr int NR = WG_NR, SP = 32 / PW, HW = PW + 2, HT = SP * HW;   // strips side by side, LDS row of the input
+    constexpr int RB = 32 * WR, CB = C8 ? 8 : 16 * WC, WK = 8 / (WR * WC), TG = 512 / WK;
+    constexpr int XS = C8 ? 8 : 32, XCH = CB / 8, GCH = RB / 8;          // LDS pixel (halfwords), 16-byte chunks
+    constexpr int XE = NR * HT * XCH, GE = NR * 32 * GCH;                // chunks of a stage
+    constexpr int XN = (XE + TG - 1) / TG, GN = (GE + TG - 1) / TG;
+    constexpr int XB = NR * HT * CB, GB = NR * 32 * RB + (WR > 1 ? 64 : 0);  // halfwords of a stage
+    constexpr int SUM = WK > 1 ? 72 * 64 * 2 * WR * WC * (WK / 2) : 0;   // halfwords of the groups' sums
+    constexpr int NL = 2 * WK * (XB + GB) > SUM ? 2 * WK * (XB + GB) : SUM;
+    static_assert(NR % 3 == 0, "the G rows rotate through 3 operands");
+    __shared__ __align__(16) uint16_t S[NL];
+    // (readfirstlane: the group's pointers are uniform in a wavefront and belong in scalar registers)
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int kg = wave / (WR * WC), wr = wave % WR, wc = (wave / WR) % WC, u = t % TG;
+    // blocks of one XCD take neighbouring parts; the tiles of a part are adjacent
+    const int ndz = a.dims == 3 ? 3 : 1, tr = rows / RB, tc = a.cin / CB, tiles = tr * tc * ndz;
+    const int nb = (int)gridDim.x, q8 = nb >> 3, r8 = nb & 7, xcd = (int)blockIdx.x & 7;
+    const int bt = xcd * q8 + (xcd < r8 ? xcd : r8) + ((int)blockIdx.x >> 3);
+    const int zp = bt / tiles, tile = bt - zp * tiles;
+    const int r0 = tile % tr * RB, ci0 = tile / tr % tc * CB, dz = a.dims == 3 ? tile / (tr * tc) - 1 : 0;
+    const int npx = (a.w + PW - 1) / PW, strips = a.n * a.d * npx;       // (PW = 16: one per plane)
+    const int nseg = (strips + SP - 1) / SP * wk.pieces;
+    uint16_t *X = S + kg * (XB + GB), *Gs = X + XB;                      // buffer 0; buffer 1 is 2nd half of S
+    constexpr int BUF = WK * (XB + GB);
+    constexpr int GSL = NR * 32 * 32 + (WR > 1 ? 32 : 0);                // a slab of G; two slabs start 16 banks apart
+
+    // the thread's chunks of a stage: byte offsets from the stage's first input / G pixel (OOB: not in the plane)
+    unsigned xo[XN], go[GN];
+    const uint16_t *xb = a.in, *gb = g;
+    int y = 0, yend = 0;                                                 // next stage's first G row, segment's end
+    auto segment = [&](int sg) {
+        const int st = sg / wk.pieces * SP, y0 = (sg - sg / wk.pieces * wk.pieces) * wk.len;
+        const int img = st / npx, px0 = (st - img * npx) * PW;           // img = sample * d + plane
+        y = y0;
+        yend = sg < nseg ? min(y0 + wk.len, a.h) : y0;
+        const long long pix = ((long long)img * a.h + y0) * a.w + px0;
+        gb = g + g_co + r0 + pix * g_cs;
+        xb = a.in + a.in_co + ci0 + (pix + ((long long)dz * a.h - 1) * a.w - 1) * a.in_cs;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int q = 8 * G + 4 * h + e;                 // pixel q of the patch (row q / PW, column q % PW)
-        xr[h] = Xs + ((q / PW + 1) * HW + q % PW + 1) * XS + 16 * wc + 4 * c;
-        gr[h] = Gs + q * GS + 32 * wr + 4 * c;
-    }
-    f32x4 acc[NTAP][2];
-#pragma unroll
-    for (int j = 0; j < NTAP; ++j) acc[j][0] = acc[j][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const uint16_t *xin = a.in + a.in_co + ci0;
-    const uint16_t *gin = g + g_co + r0;
-    uint4 xv[XN], gv[GN];
-    auto load = [&](int P) {
-        const int px0 = (P % npx) * PW, rest = P / npx;
-        const int py0 = (rest % npy) * PH, img = rest / npy;   // img = sample * d + plane
-        const int base = (img * a.h + py0) * a.w + px0;  // the patch's first pixel
-        // input plane z + dz (3D), zero outside the volume
-        const bool zok = (unsigned)(img % a.d + dz) < (unsigned)a.d;
-        const int xbase = base + dz * a.h * a.w;
-#pragma unroll
-        for (int i = 0; i < XN; ++i) {
-            const int idx = t + 256 * i, hp = idx / XCH, cc = idx % XCH;
-            const int y = py0 - 1 + hp / HW, x = px0 - 1 + hp % HW;
-            const bool ok = zok && idx < HP * XCH && (unsigned)y < (unsigned)a.h && (unsigned)x < (unsigned)a.w &&
-                            ci0 + 8 * cc < a.cin;
-            const long long pix = xbase + (hp / HW - 1) * a.w + hp % HW - 1;
-            xv[i] = ok ? *(const uint4 *)(xin + pix * a.in_cs + 8 * cc) : make_uint4(0, 0, 0, 0);
+        for (int k = 0; k < XN; ++k) {
+            const int e = u + TG * k, cc = e % XCH, p = e / XCH % HT, row = e / (XCH * HT);
+            const int half = p / HW, c = p - half * HW;
+            const bool ok = e < XE && st + half < strips && (unsigned)((img + half) % a.d + dz) < (unsigned)a.d &&
+                            (unsigned)(px0 + c - 1) < (unsigned)a.w;
+            xo[k] = ok ? 2u * (unsigned)(((half * a.h + row) * a.w + c) * a.in_cs + 8 * cc) : OOB;
         }
 #pragma unroll
-        for (int i = 0; i < GN; ++i) {
-            const int idx = t + 256 * i, p = idx / GCH, cc = idx % GCH;
-            const bool ok = py0 + p / PW < a.h && px0 + p % PW < a.w;
-            const long long pix = base + (p / PW) * a.w + p % PW;
-            gv[i] = ok ? *(const uint4 *)(gin + pix * g_cs + 8 * cc) : make_uint4(0, 0, 0, 0);
+        for (int k = 0; k < GN; ++k) {
+            const int e = u + TG * k, cc = e % GCH, p = e / GCH % 32, row = e / (GCH * 32);
+            const int half = p / PW, c = p - half * PW;
+            const bool ok = e < GE && st + half < strips && px0 + c < a.w;
+            go[k] = ok ? 2u * (unsigned)(((half * a.h + row) * a.w + c) * g_cs + 8 * cc) : OOB;
         }
     };
-    if (pb < pe) load(pb);
-    for (int P = pb; P < pe; ++P) {
-        __syncthreads();                                 // the previous stage's operand reads are done
+    uint4 xv[XN], gv[GN];
+    auto load = [&] {
+        const __amdgpu_buffer_rsrc_t rx = rsrc_of(xb, 0x80000000u), rg = rsrc_of(gb, 0x80000000u);
 #pragma unroll
-        for (int i = 0; i < XN; ++i) {
-            const int idx = t + 256 * i;
-            if (idx < HP * XCH) *(uint4 *)&Xs[(idx / XCH) * XS + 8 * (idx % XCH)] = xv[i];
+        for (int k = 0; k < XN; ++k) {
+            const int row = (u + TG * k) / (XCH * HT);
+            xv[k] = bload16(rx, (unsigned)(y - 1 + row) < (unsigned)a.h && y - 1 + row <= yend ? xo[k] : OOB);
         }
 #pragma unroll
-        for (int i = 0; i < GN; ++i) {
-            const int idx = t + 256 * i;
-            *(uint4 *)&Gs[(idx / GCH) * GS + 8 * (idx % GCH)] = gv[i];
+        for (int k = 0; k < GN; ++k) gv[k] = bload16(rg, y + (u + TG * k) / (GCH * 32) < yend ? go[k] : OOB);
+        y += NR;
+        xb += (long long)NR * a.w * a.in_cs;
+        gb += (long long)NR * a.w * g_cs;
+    };
+    // LDS: slab of 32 channels, row, column, channel
+    auto stash = [&](int buf) {
+#pragma unroll
+        for (int k = 0; k < XN; ++k) {
+            const int e = u + TG * k, cc = e % XCH, p = e / XCH;
+            const int sw = C8 ? 0 : (p % HT % HW >> 2) & 2;
+            if (e < XE) *(uint4 *)&X[buf * BUF + ((cc >> 2) * NR * HT + p) * XS + ((cc & 3) ^ sw) * 8] = xv[k];
         }
+#pragma unroll
+        for (int k = 0; k < GN; ++k) {
+            const int e = u + TG * k, cc = e % GCH, p = e / GCH;
+            if (e < GE) *(uint4 *)&Gs[buf * BUF + (cc >> 2) * GSL + p * 32 + ((cc & 3) ^ ((p >> 2) & 2)) * 8] = gv[k];
+        }
+    };
+    // the lane's transposing-read addresses (h = 0, 1) in row 0
+    const int G = lane >> 4, e4 = (lane >> 2) & 3, c4 = lane & 3;
+    const uint16_t *xr[3][2], *gr[2][2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int q = 8 * G + 4 * h + e4;
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) {
+            const int px = q % PW + dx;
+            xr[dx][h] = X + ((wc >> 1) * NR * HT + q / PW * HW + px) * XS +
+                        (C8 ? 4 * (c4 & 1) : 16 * ((wc ^ (px >> 3)) & 1) + 4 * c4);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) gr[i][h] = Gs + wr * GSL + q * 32 + 16 * (i ^ (G & 1)) + 4 * c4;
+    }
+    f32x4 acc[9][2];
+#pragma unroll
+    for (int j = 0; j < 9; ++j) acc[j][0] = acc[j][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 fg[3][2], fx[2][3];                         // operands of G's last three rows, of this and the next input row
+#pragma unroll
+    for (int k = 0; k < 3; ++k) fg[k][0] = fg[k][1] = as_bf16x8(make_uint4(0, 0, 0, 0));
+    int sg = (zp * WK + kg) * wk.per, left = wk.sps;   // (segments past the last one hold no rows)
+    const int total = wk.per * wk.sps;
+    segment(sg);
+    load();
+    stash(0);
+    for (int st = 0; st < total; ++st) {
+        const int o = (st & 1) * BUF;
         __syncthreads();
-        if (P + 1 < pe) load(P + 1);
-        // wavefront group wt takes taps 9 wt / WT .. 9 (wt + 1) / WT - 1
-        if (WT == 1) {
-            wgrad_halo_stage<PW, XS, GS, 0, 9, NTAP>(xr[0], xr[1], gr[0], gr[1], acc);
-        } else if (WT == 2) {
-            if (wt == 0) wgrad_halo_stage<PW, XS, GS, 0, 4, NTAP>(xr[0], xr[1], gr[0], gr[1], acc);
-            else wgrad_halo_stage<PW, XS, GS, 4, 9, NTAP>(xr[0], xr[1], gr[0], gr[1], acc);
-        } else {
-            if (wt == 0) wgrad_halo_stage<PW, XS, GS, 0, 2, NTAP>(xr[0], xr[1], gr[0], gr[1], acc);
-            else if (wt == 1) wgrad_halo_stage<PW, XS, GS, 2, 4, NTAP>(xr[0], xr[1], gr[0], gr[1], acc);
-            else if (wt == 2) wgrad_halo_stage<PW, XS, GS, 4, 6, NTAP>(xr[0], xr[1], gr[0], gr[1], acc);
-            else wgrad_halo_stage<PW, XS, GS, 6, 9, NTAP>(xr[0], xr[1], gr[0], gr[1], acc);
-        }
-    }
-    // acc[j][i][q]: row r0 + 32 wr + 16 i + 4 (lane >> 4) + q, channel ci0 + 16 wc + (lane & 15), tap T0 + j
-    float *dst = part + (long long)blockIdx.z * rows * a.K;
-    // 3D: the launch of plane offset dz holds taps 9 (dz + 1) .. 9 (dz + 1) + 8
-    const int t0 = 9 * wt / WT + (a.dims == 3 ? 9 * (dz + 1) : 0), nt = 9 * (wt + 1) / WT - 9 * wt / WT;
-    const int ci = ci0 + 16 * wc + (lane & 15);
-    if (ci >= a.cin) return;                              // the zero channels of a 16-channel tile over 8
-#pragma unroll
-    for (int j = 0; j < NTAP; ++j) {
-        if (j >= nt) break;
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int rr = r0 + 32 * wr + 16 * i + 4 * (lane >> 4) + q;
-                if (rr < rows) dst[(long long)rr * a.K + (t0 + j) * a.cin + ci] = acc[j][i][q];
+        if (st + 1 < total) {
+            if (--left == 0) {
+                left = wk.sps;
+                segment(++sg);
             }
+            load();
+        }
+        auto read_row = [&](int k) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) fg[k % 3][i] = tr_operand(gr[i][0] + o + k * 32 * 32, gr[i][1] + o + k * 32 * 32);
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx) fx[k & 1][dx] = tr_operand(xr[dx][0] + o + k * HT * XS, xr[dx][1] + o + k * HT * XS);
+        };
+        read_row(0);
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            // dy = 2 uses the oldest G row, whose operand the next row's read replaces
+#pragma unroll
+            for (int dy = 2; dy >= 0; --dy) {
+                if (dy == 1) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (k + 1 < NR) read_row(k + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        acc[dy * 3 + dx][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            fg[(k + 3 - dy) % 3][i], fx[k & 1][dx], acc[dy * 3 + dx][i], 0, 0, 0);
+            }
+        }
+        if (st + 1 < total) stash((st + 1) & 1);
     }
+    // the groups' sums: the upper half of the groups adds to the lower half until one is left
+    if (WK > 1) {
+        float *sum = (float *)S + lane;
+#pragma unroll
+        for (int half = WK / 2; half > 0; half >>= 1) {
+            __syncthreads();
+            float *w = sum + (((kg - half) * WR * WC + wave % (WR * WC)) * 72) * 64;
+            if (kg >= half && kg < 2 * half)
+#pragma unroll
+                for (int j = 0; j < 72; ++j) w[64 * j] = acc[j >> 3][(j >> 2) & 1][j & 3];
+            __syncthreads();
+            w = sum + ((kg * WR * WC + wave % (WR * WC)) * 72) * 64;
+            if (kg < half)
+#pragma unroll
+                for (int j = 0; j < 72; ++j) acc[j >> 3][(j >> 2) & 1][j & 3] += w[64 * j];
+        }
+        if (kg) return;
+    }
+    // acc[j][i][q]: row r0 + 32 wr + 16 i + 4 (lane >> 4) + q, channel ci0 + 16 wc + (lane & 15), tap j
+    float *dst = part + (long long)zp * rows * a.K + (a.dims == 3 ? 9 * (dz + 1) * a.cin : 0) + ci0 + 16 * wc + (lane & 15);
+    if (C8 && (lane & 15) >= 8) return;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float *d = dst + (long long)(r0 + 32 * wr + 16 * i + 4 * (lane >> 4) + q) * a.K;
+#pragma unroll
+            for (int j = 0; j < 9; ++j) d[j * a.cin] = acc[j][i][q];
+        }
 }
 
-// Sum of split partials: a block takes 64 outputs, its four wavefronts the
-// splits z = w, w + 4, ... (coalesced 64-float rows), combined in a fixed
-// order (deterministic).
-__global__ void __launch_bounds__(256) k_sum_splits(const float *__restrict__ part, int splits, long long n,
-                                                    long long row, float *__restrict__ out, int accumulate) {
-    __shared__ float sh[4][64];
+// Sum of split partials: a block takes 64 V outputs (V per lane, one load), its
+// NW wavefronts the splits z = w, w + NW, ..., combined in wavefront order
+// (deterministic).  Bound by memory: 16 wavefronts keep enough rows in flight
+// where outputs are few and splits many.
+template <int NW, int V>
+__global__ void __launch_bounds__(64 * NW) k_sum_splits(const float *__restrict__ part, int splits, long long n,
+                                                        float *__restrict__ out, int accumulate) {
+    typedef float vec __attribute__((ext_vector_type(V)));
+    __shared__ vec sh[NW][64];
     const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const long long i = (long long)blockIdx.x * 64 + l;
-    float s = 0.f;
+    const long long i = ((long long)blockIdx.x * 64 + l) * V;
+    vec s = 0.f;
     if (i < n)
-        for (int z = w; z < splits; z += 4) s += part[(long long)z * row + i];
+#pragma unroll 8
+        for (int z = w; z < splits; z += NW) s += *(const vec *)(part + (long long)z * n + i);
     sh[w][l] = s;
     __syncthreads();
     if (w == 0 && i < n) {
-        const float v = (sh[0][l] + sh[1][l]) + (sh[2][l] + sh[3][l]);
-        out[i] = accumulate ? out[i] + v : v;
+        vec v = 0.f;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) v += sh[k][l];
+#pragma unroll
+        for (int k = 0; k < V; ++k) out[i + k] = accumulate ? out[i + k] + v[k] : v[k];
     }
-}
-
-// First pass of a long split sum: thread (i, c) adds the partials of splits
-// c S .. c S + S - 1 of output i in order and stores the sum over split
-// c S's own partial, which no other thread reads; k_sum_splits then adds
-// the chunk sums (row stride S n), in order.
-__global__ void __launch_bounds__(256) k_sum_split_chunks(float *__restrict__ part, int splits, long long n, int S) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const int z0 = (int)blockIdx.y * S, z1 = min(z0 + S, splits);
-    float s = 0.f;
-#pragma unroll 8
-    for (int z = z0; z < z1; ++z) s += part[(long long)z * n + i];
-    part[(long long)z0 * n + i] = s;
 }
 
 // Sum of split partials when there are few outputs: one block per output,
@@ -1477,33 +1556,26 @@ long long wgrad_chunk(long long M, int splits) {
 }
 
 // Sum of z split partials into n outputs: a block per output when there are
-// few; else a thread per output and four wavefronts over the splits, after a
-// first pass that adds chunks of 8 splits in place when there are more than
-// 32 (each partial is added once, in split order within a chunk and in chunk
-// order after; deterministic).
-static hipError_t sum_splits(float *part, int z, long long n, float *out, int accumulate, hipStream_t s) {
-    if (n <= 8192 && z > 16) {
+// few (bias gradients), else 64 outputs per block.
+static hipError_t sum_splits(const float *part, int z, long long n, float *out, int accumulate, hipStream_t s) {
+    if (n <= 1024 && z > 16)
         hipLaunchKernelGGL(k_sum_splits_narrow, dim3((unsigned)n), dim3(256), 0, s, part, z, n, out, accumulate);
-        return hipGetLastError();
-    }
-    long long row = n;
-    if (z > 32) {
-        constexpr int S = 8;
-        const int chunks = (z + S - 1) / S;
-        hipLaunchKernelGGL(k_sum_split_chunks, dim3(blocks(n, 256), (unsigned)chunks), dim3(256), 0, s, part, z, n, S);
-        z = chunks;
-        row = S * n;
-    }
-    hipLaunchKernelGGL(k_sum_splits, dim3(blocks(n, 64)), dim3(256), 0, s, part, z, n, row, out, accumulate);
+    else if (n % 4 == 0 && ((uintptr_t)part & 15) == 0 && n >= 65536)
+        hipLaunchKernelGGL((k_sum_splits<4, 4>), dim3(blocks(n, 256)), dim3(256), 0, s, part, z, n, out, accumulate);
+    else if (z > 32)
+        hipLaunchKernelGGL((k_sum_splits<16, 1>), dim3(blocks(n, 64)), dim3(1024), 0, s, part, z, n, out, accumulate);
+    else
+        hipLaunchKernelGGL((k_sum_splits<4, 1>), dim3(blocks(n, 64)), dim3(256), 0, s, part, z, n, out, accumulate);
     return hipGetLastError();
 }
 
-// The halo kernel's block shape for a layer, or 0: (WR, WC) = (2, 2) for
-// 64-row multiples, (1, 4) for 32 rows of 64-channel multiples, (1, 2) (taps
-// split over two wavefront pairs) for 32 rows of 32-channel multiples, (1, 1)
-// (taps split over the four wavefronts) for 32 rows of 8 channels.
-static int halo_shape(const ConvArgs &a, int rows) {
+// The row kernel's block shape (10 WR + WC) for a layer, or 0: 64 rows x 32
+// channels, 32 rows x 64 or 32 channels (two groups), or 32 rows x 8 channels
+// (four groups).  Its loads take 32-bit byte offsets from a stage's first pixel.
+static int rows_shape(const ConvArgs &a, int rows, int g_cs) {
     if (a.ks != 3 || (a.flags & (FLAG_S2D | FLAG_D2S | FLAG_S2D_G)) || a.w < 16) return 0;
+    const long long reach = ((a.w <= 16 ? a.h : 0) + WG_NR + 1LL) * a.w + 34;
+    if (2 * reach * (a.in_cs > g_cs ? a.in_cs : g_cs) >= (1LL << 31)) return 0;
     if (rows % 64 == 0 && a.cin % 32 == 0) return 22;
     if (rows % 32 == 0 && a.cin % 64 == 0) return 14;
     if (rows % 32 == 0 && a.cin % 32 == 0) return 12;
@@ -1512,42 +1584,45 @@ static int halo_shape(const ConvArgs &a, int rows) {
 }
 
 template <int PW>
-static void launch_wgrad_halo(int shape, const ConvArgs &a, const uint16_t *g, int g_cs, int g_co, int rows,
-                              float *part, int z, int per, int dz, hipStream_t s) {
-    const int RB = shape == 22 ? 64 : 32, CB = shape == 22 ? 32 : shape == 14 ? 64 : shape == 12 ? 32 : 16;
-    const dim3 grid((unsigned)(rows / RB), (unsigned)((a.cin + CB - 1) / CB), (unsigned)z);
+static hipError_t launch_wgrad_rows(int shape, const ConvArgs &a, const uint16_t *g, int g_cs, int g_co, int rows,
+                                    float *part, int &z, hipStream_t s) {
+    const int RB = shape == 22 ? 64 : 32, CB = shape == 11 ? 8 : shape == 14 ? 64 : 32;
+    const int WK = shape == 11 ? 8 : shape == 12 ? 4 : 2;
+    const long long tiles = (long long)(rows / RB) * (a.cin / CB) * (a.dims == 3 ? 3 : 1);
+    const long long npx = (a.w + PW - 1) / PW, strips = ((long long)a.n * a.d * npx + 32 / PW - 1) / (32 / PW);
+    // one block per CU, within the partials that the workspace holds; the cut of the strips into segments
+    // that gives the longest walk the fewest stages (a segment costs two steps more than it has rows)
+    const long long zt = tiles >= 256 ? 1 : 256 / tiles, walkers = (zt < z ? zt : z) * WK;
+    WgradWalk k{};
+    long long best = 0;
+    for (int pieces = 1; pieces <= 64 && (pieces == 1 || a.h >= 4 * pieces); ++pieces) {
+        const int len = (a.h + pieces - 1) / pieces, sps = (len + 2 + WG_NR - 1) / WG_NR;
+        const long long per = (strips * pieces + walkers - 1) / walkers;
+        if (pieces > 1 && per * sps >= best) continue;
+        best = per * sps;
+        k = WgradWalk{len, pieces, (int)per, sps, (int)((strips * pieces + per * WK - 1) / (per * WK))};
+    }
+    z = k.z;
+    const dim3 grid((unsigned)(tiles * z));
     if (shape == 22)
-        hipLaunchKernelGGL((k_wgrad_halo<PW, 2, 2>), grid, dim3(256), 0, s, a, g, g_cs, g_co, rows, part, per, dz);
+        hipLaunchKernelGGL((k_wgrad_rows<PW, 2, 2, false>), grid, dim3(512), 0, s, a, g, g_cs, g_co, rows, part, k);
     else if (shape == 14)
-        hipLaunchKernelGGL((k_wgrad_halo<PW, 1, 4>), grid, dim3(256), 0, s, a, g, g_cs, g_co, rows, part, per, dz);
+        hipLaunchKernelGGL((k_wgrad_rows<PW, 1, 4, false>), grid, dim3(512), 0, s, a, g, g_cs, g_co, rows, part, k);
     else if (shape == 12)
-        hipLaunchKernelGGL((k_wgrad_halo<PW, 1, 2>), grid, dim3(256), 0, s, a, g, g_cs, g_co, rows, part, per, dz);
+        hipLaunchKernelGGL((k_wgrad_rows<PW, 1, 2, false>), grid, dim3(512), 0, s, a, g, g_cs, g_co, rows, part, k);
     else
-        hipLaunchKernelGGL((k_wgrad_halo<PW, 1, 1>), grid, dim3(256), 0, s, a, g, g_cs, g_co, rows, part, per, dz);
+        hipLaunchKernelGGL((k_wgrad_rows<PW, 1, 1, true>), grid, dim3(512), 0, s, a, g, g_cs, g_co, rows, part, k);
+    return hipGetLastError();
 }
 
 hipError_t wgrad(const ConvArgs &a, const uint16_t *g, int g_cs, int g_co, int rows, float *part, int splits,
                  float *dw, int accumulate, hipStream_t s) {
     const long long chunk = wgrad_chunk(a.M, splits);
     int z = (int)((a.M + chunk - 1) / chunk);
-    if (const int shape = halo_shape(a, rows)) {
-        // patches of 4 x 32 (or 8 x 16 when w <= 16) pixels, split into at
-        // most as many ranges as the workspace holds partials for
-        // 3D: one launch per plane offset dz = -1, 0, 1, each the 9 taps of its
-        // plane pair, written to disjoint columns of the same partials
-        const int pw = a.w > 16 ? 32 : 16, ph = 128 / pw;
-        const long long npt = (long long)a.n * a.d * ((a.h + ph - 1) / ph) * ((a.w + pw - 1) / pw);
-        const int per = (int)((npt + z - 1) / z);
-        z = (int)((npt + per - 1) / per);
-        for (int dz = a.dims == 3 ? -1 : 0; dz <= (a.dims == 3 ? 1 : 0); ++dz) {
-            if (pw == 32)
-                launch_wgrad_halo<32>(shape, a, g, g_cs, g_co, rows, part, z, per, dz, s);
-            else
-                launch_wgrad_halo<16>(shape, a, g, g_cs, g_co, rows, part, z, per, dz, s);
-            const hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-        return sum_splits(part, z, (long long)rows * a.K, dw, accumulate, s);
+    if (const int shape = rows_shape(a, rows, g_cs)) {
+        const hipError_t e = a.w > 16 ? launch_wgrad_rows<32>(shape, a, g, g_cs, g_co, rows, part, z, s)
+                                      : launch_wgrad_rows<16>(shape, a, g, g_cs, g_co, rows, part, z, s);
+        return e != hipSuccess ? e : sum_splits(part, z, (long long)rows * a.K, dw, accumulate, s);
     }
     if (rows <= 32) {
         const dim3 grid(1u, (unsigned)((a.K + 127) / 128), (unsigned)z);

@@ -202,6 +202,23 @@ def test_halo_weight_gradient(dims, grid, cin, cout, splits):
     assert rel(dw.cpu().numpy(), ref.reshape(cout, -1)) <= 1e-5
 
 
+# long walks of the row kernel: several segments of a strip and several strips per group of wavefronts,
+# groups with fewer segments than others and with none, pairs of 16-column planes with one left over
+WALKS = [(2, (9, 1, 64, 40), 64, 64, 2), (2, (5, 1, 33, 16), 32, 64, 1), (2, (3, 1, 50, 100), 8, 32, 1),
+         (2, (7, 1, 21, 35), 64, 32, 3), (3, (2, 5, 24, 16), 32, 32, 2), (3, (3, 3, 7, 64), 8, 64, 4)]
+
+
+@pytest.mark.parametrize("dims,grid,cin,cout,splits", WALKS)
+def test_weight_gradient_walks(dims, grid, cin, cout, splits):
+    rng = np.random.default_rng(15)
+    x = bf(rng.standard_normal(grid + (cin + 8,)))
+    g = bf(rng.standard_normal(grid + (cout,)))
+    dw = wgrad_call(dev_bf(x), dev_bf(g), 3, dims, cout, splits=splits, cin=cin, in_co=8)
+    ref, _ = N.conv_wgrad(x[..., 8:], g, 3, dims)
+    # FP32 accumulation of up to 25,000 products per entry: 6e-8 sqrt(25,000) relative to the norm
+    assert rel(dw.cpu().numpy(), ref.reshape(cout, -1)) <= 1e-5
+
+
 # Deep, low-resolution layers (few output tiles, long K) split their K loop
 # through the workspace entry point: FP32 output with accumulate, BF16 output
 # with bias and ReLU, a D2S transposed convolution and an S2D input gradient
