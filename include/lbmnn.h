@@ -78,6 +78,14 @@ size_t lbmnn_conv_workspace_bytes(const lbmnn_conv_desc *c);
 int lbmnn_conv_ws(const lbmnn_conv_desc *c, const void *w, const float *bias, float *ws, size_t ws_bytes,
                   void *stream);
 
+/* lbmnn_conv_ws (no bias) followed by the ReLU backward: output element (m, c)
+ * is 0 where channel y_coff + c of y at pixel m is not > 0.  The input gradient
+ * of a layer whose input was a ReLU's output y: bit for bit the convolution
+ * and lbmnn_relu_bwd one after the other.  Output: c->out (BF16), overwritten;
+ * LBM_EINVAL with LBMNN_RELU, LBMNN_ACCUMULATE, LBMNN_D2S or an FP32 output. */
+int lbmnn_conv_relu_bwd(const lbmnn_conv_desc *c, const void *w, const void *y, int y_cstride, int y_coff, float *ws,
+                        size_t ws_bytes, void *stream);
+
 /* Weight gradient dW[r][k] = sum_m G[m][r] A[m][k] for the A operand that c
  * describes (c->cout is ignored), G = gradient of the GEMM output with
  * channel stride/offset g_cstride / g_coff and `rows` columns (LBMNN_S2D_G in
@@ -88,6 +96,13 @@ int lbmnn_conv_ws(const lbmnn_conv_desc *c, const void *w, const float *bias, fl
 size_t lbmnn_wgrad_workspace_bytes(long long pixels, int rows, int K, int splits);
 int lbmnn_conv_wgrad(const lbmnn_conv_desc *c, const void *g, int g_cstride, int g_coff, int rows, float *dw,
                      int accumulate, float *ws, size_t ws_bytes, int splits, void *stream);
+
+/* lbmnn_conv_wgrad and the bias gradient of the same G (as lbmnn_bias_grad, up
+ * to the order of the FP32 sums): db[r] = sum_m G[m][r], with LBMNN_S2D_G the
+ * Cr sums over the finer grid.  ws: at least lbmnn_wgrad_workspace_bytes(pixels,
+ * rows, K + 1, splits) bytes. */
+int lbmnn_conv_wgrad_bias(const lbmnn_conv_desc *c, const void *g, int g_cstride, int g_coff, int rows, float *dw,
+                          float *db, int accumulate, float *ws, size_t ws_bytes, int splits, void *stream);
 
 /* lbmnn_conv_wgrad without a workspace argument, for callers that cannot
  * allocate device memory (code under graph capture, tight training loops,
@@ -134,6 +149,11 @@ int lbmnn_pool_fwd(const void *in, int in_cstride, int in_coff, void *out, int o
 int lbmnn_pool_bwd(const void *in, int in_cstride, int in_coff, const void *gout, int g_cstride, int g_coff,
                    void *gin, int gi_cstride, int gi_coff, int n, int d, int h, int w, int C, int dims,
                    int accumulate, void *stream);
+/* lbmnn_pool_bwd followed by the ReLU backward: in holds ReLU outputs, and gin
+ * is 0 where they are not > 0 (bit for bit the two calls). */
+int lbmnn_pool_bwd_relu(const void *in, int in_cstride, int in_coff, const void *gout, int g_cstride, int g_coff,
+                        void *gin, int gi_cstride, int gi_coff, int n, int d, int h, int w, int C, int dims,
+                        int accumulate, void *stream);
 
 /* Masked MSE: loss = scale * sum_m wpix[m] sum_{c < creal} (pred[m][c] - tgt[m][c])^2
  * with pred FP32 at channel stride pcs and tgt FP32 [m][creal]; writes the

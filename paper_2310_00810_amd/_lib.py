@@ -110,10 +110,11 @@ def check(rc, where):
 
 # ------------------------------------------------------------ lbmnn.h ABI --
 NN_EXPORTS = [
-    "lbmnn_conv", "lbmnn_conv_workspace_bytes", "lbmnn_conv_ws", "lbmnn_wgrad_workspace_bytes", "lbmnn_conv_wgrad",
-    "lbmnn_conv_wgrad_noalloc",
+    "lbmnn_conv", "lbmnn_conv_workspace_bytes", "lbmnn_conv_ws", "lbmnn_conv_relu_bwd",
+    "lbmnn_wgrad_workspace_bytes", "lbmnn_conv_wgrad", "lbmnn_conv_wgrad_bias", "lbmnn_conv_wgrad_noalloc",
     "lbmnn_weight_transpose",
     "lbmnn_bias_grad", "lbmnn_relu_bwd", "lbmnn_relu_bwd_bias_grad", "lbmnn_pool_fwd", "lbmnn_pool_bwd",
+    "lbmnn_pool_bwd_relu",
     "lbmnn_mse", "lbmnn_adam", "lbmnn_to_bf16", "lbmnn_features", "lbmnn_normalize", "lbmnn_denormalize",
     "lbmnn_flux_balance_workspace_bytes", "lbmnn_flux_balance",
 ]
@@ -143,9 +144,11 @@ def nnlib():
         L.lbmnn_conv_workspace_bytes.argtypes = [dp]
         L.lbmnn_conv_workspace_bytes.restype = ctypes.c_size_t
         L.lbmnn_conv_ws.argtypes = [dp, vp, vp, vp, ctypes.c_size_t, vp]
+        L.lbmnn_conv_relu_bwd.argtypes = [dp, vp, vp, ip, ip, vp, ctypes.c_size_t, vp]
         L.lbmnn_wgrad_workspace_bytes.argtypes = [ll, ip, ip, ip]
         L.lbmnn_wgrad_workspace_bytes.restype = ctypes.c_size_t
         L.lbmnn_conv_wgrad.argtypes = [dp, vp, ip, ip, ip, vp, ip, vp, ctypes.c_size_t, ip, vp]
+        L.lbmnn_conv_wgrad_bias.argtypes = [dp, vp, ip, ip, ip, vp, vp, ip, vp, ctypes.c_size_t, ip, vp]
         L.lbmnn_conv_wgrad_noalloc.argtypes = [dp, vp, ip, ip, ip, vp, ip, ip, vp]
         L.lbmnn_weight_transpose.argtypes = [vp, vp, ip, ip, ip, ip, vp]
         L.lbmnn_bias_grad.argtypes = [vp, ip, ip, ll, ip, vp, ip, vp, ip, vp]
@@ -153,6 +156,7 @@ def nnlib():
         L.lbmnn_relu_bwd_bias_grad.argtypes = [vp, vp, ip, ip, ll, ip, vp, ip, vp, ip, vp]
         L.lbmnn_pool_fwd.argtypes = [vp, ip, ip, vp, ip, ip, ip, ip, ip, ip, ip, ip, vp]
         L.lbmnn_pool_bwd.argtypes = [vp, ip, ip, vp, ip, ip, vp, ip, ip, ip, ip, ip, ip, ip, ip, ip, vp]
+        L.lbmnn_pool_bwd_relu.argtypes = L.lbmnn_pool_bwd.argtypes
         L.lbmnn_mse.argtypes = [vp, ip, vp, vp, ip, ll, fl, vp, vp, vp, vp]
         L.lbmnn_adam.argtypes = [vp, vp, vp, vp, vp, ll, fl, fl, fl, fl, ip, vp]
         L.lbmnn_to_bf16.argtypes = [vp, vp, ll, vp]

@@ -142,12 +142,7 @@ size_t lbmnn_conv_workspace_bytes(const lbmnn_conv_desc *c) {
     return S > 1 ? sizeof(float) * (size_t)S * (size_t)a.M * (size_t)a.ncols : 0;
 }
 
-int lbmnn_conv_ws(const lbmnn_conv_desc *c, const void *w, const float *bias, float *ws, size_t ws_bytes,
-                  void *stream) {
-    int rc = check_desc(c, true);
-    if (rc) return rc;
-    if (!w || !aligned16(w)) return lbm_fail(LBM_EINVAL, "weights must be a 16-byte aligned device pointer");
-    const nn::ConvArgs a = to_args(c, w, bias);
+static int conv_ws(const nn::ConvArgs &a, float *ws, size_t ws_bytes, void *stream) {
     const int S = nn::conv_splits(a);
     if (S > 1) {
         const size_t need = sizeof(float) * (size_t)S * (size_t)a.M * (size_t)a.ncols;
@@ -158,6 +153,32 @@ int lbmnn_conv_ws(const lbmnn_conv_desc *c, const void *w, const float *bias, fl
         NN_TRY(nn::conv(a, (hipStream_t)stream));
     }
     return LBM_OK;
+}
+
+int lbmnn_conv_ws(const lbmnn_conv_desc *c, const void *w, const float *bias, float *ws, size_t ws_bytes,
+                  void *stream) {
+    int rc = check_desc(c, true);
+    if (rc) return rc;
+    if (!w || !aligned16(w)) return lbm_fail(LBM_EINVAL, "weights must be a 16-byte aligned device pointer");
+    return conv_ws(to_args(c, w, bias), ws, ws_bytes, stream);
+}
+
+int lbmnn_conv_relu_bwd(const lbmnn_conv_desc *c, const void *w, const void *y, int y_cstride, int y_coff, float *ws,
+                        size_t ws_bytes, void *stream) {
+    int rc = check_desc(c, true);
+    if (rc) return rc;
+    if (!w || !aligned16(w)) return lbm_fail(LBM_EINVAL, "weights must be a 16-byte aligned device pointer");
+    if (!y || !aligned16(y) || !mult8(y_cstride) || !mult8(y_coff) || y_coff < 0 || y_coff + c->cout > y_cstride)
+        return lbm_fail(LBM_EINVAL, "y must be a 16-byte aligned device pointer of cout channels at a stride and offset "
+                                    "that are multiples of 8");
+    if (!c->out || c->out_f32 || (c->flags & (LBMNN_RELU | LBMNN_ACCUMULATE | LBMNN_D2S)))
+        return lbm_fail(LBM_EINVAL, "the masked convolution overwrites a BF16 output on the grid of y");
+    nn::ConvArgs a = to_args(c, w, nullptr);
+    a.mask = (const uint16_t *)y;
+    a.mask_cs = y_cstride;
+    a.mask_co = y_coff;
+    // the split rule looks at the layer alone, so lbmnn_conv_workspace_bytes(c) holds here too
+    return conv_ws(a, ws, ws_bytes, stream);
 }
 
 size_t lbmnn_wgrad_workspace_bytes(long long pixels, int rows, int K, int splits) {
@@ -175,7 +196,22 @@ int lbmnn_conv_wgrad(const lbmnn_conv_desc *c, const void *g, int g_cstride, int
     if (rc) return rc;
     if (!ws) return lbm_fail(LBM_EINVAL, "workspace is NULL");
     if (ws_bytes < need) return lbm_fail(LBM_ENOMEM, "wgrad workspace of %zu bytes, %zu needed", ws_bytes, need);
-    NN_TRY(nn::wgrad(a, (const uint16_t *)g, g_cstride, g_coff, rows, ws, splits, dw, accumulate,
+    NN_TRY(nn::wgrad(a, (const uint16_t *)g, g_cstride, g_coff, rows, ws, splits, dw, nullptr, accumulate,
+                     (hipStream_t)stream));
+    return LBM_OK;
+}
+
+int lbmnn_conv_wgrad_bias(const lbmnn_conv_desc *c, const void *g, int g_cstride, int g_coff, int rows, float *dw,
+                          float *db, int accumulate, float *ws, size_t ws_bytes, int splits, void *stream) {
+    nn::ConvArgs a;
+    size_t need = 0;
+    int rc = wgrad_prepare(c, g, g_cstride, g_coff, rows, dw, splits, a, need);
+    if (rc) return rc;
+    if (!db) return lbm_fail(LBM_EINVAL, "db is NULL");
+    need = lbmnn_wgrad_workspace_bytes(a.M, rows, a.K + 1, splits);
+    if (!ws) return lbm_fail(LBM_EINVAL, "workspace is NULL");
+    if (ws_bytes < need) return lbm_fail(LBM_ENOMEM, "wgrad workspace of %zu bytes, %zu needed", ws_bytes, need);
+    NN_TRY(nn::wgrad(a, (const uint16_t *)g, g_cstride, g_coff, rows, ws, splits, dw, db, accumulate,
                      (hipStream_t)stream));
     return LBM_OK;
 }
@@ -191,7 +227,7 @@ int lbmnn_conv_wgrad_noalloc(const lbmnn_conv_desc *c, const void *g, int g_cstr
                                     "lbmnn_conv_wgrad_noalloc: use fewer splits", need, LBMNN_NOALLOC_SCRATCH_BYTES);
     float *part = nullptr;
     if ((rc = scratch_ptr(&part))) return rc;
-    NN_TRY(nn::wgrad(a, (const uint16_t *)g, g_cstride, g_coff, rows, part, splits, dw, accumulate,
+    NN_TRY(nn::wgrad(a, (const uint16_t *)g, g_cstride, g_coff, rows, part, splits, dw, nullptr, accumulate,
                      (hipStream_t)stream));
     return LBM_OK;
 }
@@ -236,14 +272,29 @@ int lbmnn_pool_fwd(const void *in, int in_cstride, int in_coff, void *out, int o
     return LBM_OK;
 }
 
-int lbmnn_pool_bwd(const void *in, int in_cstride, int in_coff, const void *gout, int g_cstride, int g_coff,
-                   void *gin, int gi_cstride, int gi_coff, int n, int d, int h, int w, int C, int dims,
-                   int accumulate, void *stream) {
+static int pool_bwd(const void *in, int in_cstride, int in_coff, const void *gout, int g_cstride, int g_coff,
+                    void *gin, int gi_cstride, int gi_coff, int n, int d, int h, int w, int C, int dims,
+                    int accumulate, int relu, void *stream) {
     if (!in || !gout || !gin || C < 1 || (dims != 2 && dims != 3) || (dims == 2 && d != 1))
         return lbm_fail(LBM_EINVAL, "bad pooling arguments");
     NN_TRY(nn::pool_bwd((const uint16_t *)in, in_cstride, in_coff, (const uint16_t *)gout, g_cstride, g_coff,
-                        (uint16_t *)gin, gi_cstride, gi_coff, n, d, h, w, C, dims, accumulate, (hipStream_t)stream));
+                        (uint16_t *)gin, gi_cstride, gi_coff, n, d, h, w, C, dims, accumulate, relu,
+                        (hipStream_t)stream));
     return LBM_OK;
+}
+
+int lbmnn_pool_bwd(const void *in, int in_cstride, int in_coff, const void *gout, int g_cstride, int g_coff,
+                   void *gin, int gi_cstride, int gi_coff, int n, int d, int h, int w, int C, int dims,
+                   int accumulate, void *stream) {
+    return pool_bwd(in, in_cstride, in_coff, gout, g_cstride, g_coff, gin, gi_cstride, gi_coff, n, d, h, w, C, dims,
+                    accumulate, 0, stream);
+}
+
+int lbmnn_pool_bwd_relu(const void *in, int in_cstride, int in_coff, const void *gout, int g_cstride, int g_coff,
+                        void *gin, int gi_cstride, int gi_coff, int n, int d, int h, int w, int C, int dims,
+                        int accumulate, void *stream) {
+    return pool_bwd(in, in_cstride, in_coff, gout, g_cstride, g_coff, gin, gi_cstride, gi_coff, n, d, h, w, C, dims,
+                    accumulate, 1, stream);
 }
 
 int lbmnn_mse(const float *pred, int pcs, const float *tgt, const float *wpix, int creal, long long pixels,

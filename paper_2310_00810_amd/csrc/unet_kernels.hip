@@ -164,6 +164,14 @@ __device__ inline void cursor_inc(Cursor &c, const ConvArgs &a) { cursor_add(c, 
 
 __device__ inline bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 
+// ReLU backward: v[k] = 0 where the 8 activations y (NaN included) are not > 0.
+__device__ inline void relu_mask(float (&v)[8], uint4 y) {
+    float f[8];
+    unpack8(y, f);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = f[k] > 0.f ? v[k] : 0.f;
+}
+
 // Output element of GEMM cell (m, c): returns the flat index and the bias
 // channel; D2S maps column c = sub * Cr + co to the fine pixel.
 __device__ inline long long out_index(const ConvArgs &a, long long m, int c, int &bias_c) {
@@ -279,7 +287,7 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a, float *__restrict__ pa
     const bool d2s = (a.flags & FLAG_D2S) != 0;
     const int cr = d2s ? a.ncols >> a.dims : a.ncols;      // D2S: columns sub * cr + co
     const uintptr_t base = a.out32 ? (uintptr_t)a.out32 : (uintptr_t)a.out;
-    if (((a.out_cs | a.out_co) & 7) == 0 && (!d2s || (cr & 7) == 0) && (base & 15) == 0) {
+    if (((a.out_cs | a.out_co | a.mask_cs | a.mask_co) & 7) == 0 && ((uintptr_t)a.mask & 15) == 0 && (!d2s || (cr & 7) == 0) && (base & 15) == 0) {
         // the tile goes through LDS (the buffers are free after the last barrier) so that each
         // thread stores 8 consecutive channels of a pixel (of the fine pixel for D2S, whose
         // 8-column groups stay inside one sub-pixel) with 16-byte writes
@@ -338,6 +346,7 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a, float *__restrict__ pa
 #pragma unroll
                     for (int k = 0; k < 8; ++k) v[k] += bf2f((uint16_t)(ow[k >> 1] >> (16 * (k & 1))));
                 }
+                if (a.mask) relu_mask(v, *(const uint4 *)(a.mask + m * a.mask_cs + a.mask_co + c));
                 uint32_t pw[4];
 #pragma unroll
                 for (int k = 0; k < 4; ++k) pw[k] = f2bf2(v[2 * k], v[2 * k + 1]);
@@ -346,6 +355,7 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a, float *__restrict__ pa
                 for (int k = 0; k < a.ncols - c; ++k) {
                     float v = src[k];
                     if (a.flags & FLAG_ACC) v += bf2f(dst[k]);
+                    if (a.mask && !(bf2f(a.mask[m * a.mask_cs + a.mask_co + c + k]) > 0.f)) v = 0.f;
                     dst[k] = f2bf(v);
                 }
             }
@@ -370,6 +380,7 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a, float *__restrict__ pa
                     a.out32[o] = (a.flags & FLAG_ACC) ? a.out32[o] + v : v;
                 } else {
                     if (a.flags & FLAG_ACC) v += bf2f(a.out[o]);
+                    if (a.mask && !(bf2f(a.mask[m * a.mask_cs + a.mask_co + c]) > 0.f)) v = 0.f;
                     a.out[o] = f2bf(v);
                 }
             }
@@ -435,8 +446,10 @@ __device__ inline void lds_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memor
 // in registers throughout; else every stage's weights pass through LDS, where
 // the next stage's are loaded (straight from memory) as soon as all wavefronts
 // have read the current ones.
-// PLAIN: BF16 output, overwritten.
-template <int TN, int DIMS, bool RES, bool PLAIN>
+// MODE: OUT_PLAIN BF16 output, overwritten; OUT_MASK the same behind a ReLU
+// backward; OUT_ANY accumulated or FP32 (no mask).
+enum { OUT_PLAIN, OUT_MASK, OUT_ANY };
+template <int TN, int DIMS, bool RES, int MODE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 k_conv3x3_rows(ConvArgs a, int per) {
     constexpr int WY = TN == 32 ? 4 : 8;
@@ -582,8 +595,14 @@ k_conv3x3_rows(ConvArgs a, int per) {
             if (a.bias)
 #pragma unroll
                 for (int k = 0; k < 8; ++k) bias[k] = a.bias[c + k];
+            constexpr int MB = 4;                     // mask loads in flight (registers)
+            uint4 mk[MB];
 #pragma unroll
             for (int r = 0; r < WY; ++r) {
+                if (MODE == OUT_MASK && r % MB == 0)
+#pragma unroll
+                    for (int k = 0; k < MB; ++k)
+                        mk[k] = *(const uint4 *)(a.mask + (m0 + (long long)(r + k) * a.w) * a.mask_cs + a.mask_co + c);
                 const long long o = (m0 + (long long)r * a.w) * a.out_cs + a.out_co + c;
                 float v[8];
 #pragma unroll
@@ -591,19 +610,20 @@ k_conv3x3_rows(ConvArgs a, int per) {
                     v[k] = acc[r][k >> 2][k & 3] + bias[k];
                     v[k] = relu && !(v[k] > 0.f) ? 0.f : v[k];
                 }
-                if (!PLAIN && a.out32) {
+                if (MODE == OUT_ANY && a.out32) {
                     float *dst = a.out32 + o;
 #pragma unroll
                     for (int k = 0; k < 8; ++k) dst[k] = (a.flags & FLAG_ACC) ? dst[k] + v[k] : v[k];
                     continue;
                 }
                 uint16_t *dst = a.out + o;
-                if (!PLAIN && (a.flags & FLAG_ACC)) {
+                if (MODE == OUT_ANY && (a.flags & FLAG_ACC)) {
                     float old[8];
                     unpack8(*(const uint4 *)dst, old);
 #pragma unroll
                     for (int k = 0; k < 8; ++k) v[k] += old[k];
                 }
+                if (MODE == OUT_MASK) relu_mask(v, mk[r % MB]);
                 *(uint4 *)dst = pack8(v);
             }
         }
@@ -825,6 +845,9 @@ __device__ inline bf16x8 tr_operand(const uint16_t *p0, const uint16_t *p1) {
 // two runs, 32 bytes a pixel) cover all 64 banks.  A layer of 8 input channels
 // keeps 16-byte rows and computes its 8 channels twice.
 //
+// SUMS: the bias gradient's partials too (bpart), the row sums of G, as products of
+// G's operands with ones in the blocks of the first channel tile.
+//
 // 16 x 256^2, 32 -> 32: 29 us (4.6 TB/s; sum of the partials 4 us), bound by
 // memory; 16 x 64^2, 128 -> 128: 27 us, of which 12 us are the launch, the first
 // loads and the partials and the rest the stages (twice their MFMA time); with
@@ -835,19 +858,20 @@ constexpr int WG_NR = 3;
 struct WgradWalk { int len, pieces, per, sps, z; };   // segment rows, segments per strip, segments per walker,
                                                       // stages per segment, block parts
 
-template <int PW, int WR, int WC, bool C8>
+template <int PW, int WR, int WC, bool C8, bool SUMS>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
 k_wgrad_rows(ConvArgs a, const uint16_t *__restrict__ g, int g_cs, int g_co, int rows, float *__restrict__ part,
-             WgradWalk wk) {
+             float *__restrict__ bpart, WgradWalk wk) {
     constexpr int NR = WG_NR, SP = 32 / PW, HW = PW + 2, HT = SP * HW;   // strips side by side, LDS row of the input
     constexpr int RB = 32 * WR, CB = C8 ? 8 : 16 * WC, WK = 8 / (WR * WC), TG = 512 / WK;
     constexpr int XS = C8 ? 8 : 32, XCH = CB / 8, GCH = RB / 8;          // LDS pixel (halfwords), 16-byte chunks
     constexpr int XE = NR * HT * XCH, GE = NR * 32 * GCH;                // chunks of a stage
     constexpr int XN = (XE + TG - 1) / TG, GN = (GE + TG - 1) / TG;
     constexpr int XB = NR * HT * CB, GB = NR * 32 * RB + (WR > 1 ? 64 : 0);  // halfwords of a stage
-    constexpr int SUM = WK > 1 ? 72 * 64 * 2 * WR * WC * (WK / 2) : 0;   // halfwords of the groups' sums
+    constexpr int NA = SUMS ? 80 : 72;                                   // a lane's sums
+    constexpr int SUM = NA * 64 * 2 * WR * WC * (WK / 2);                // halfwords of the groups' sums
     constexpr int NL = 2 * WK * (XB + GB) > SUM ? 2 * WK * (XB + GB) : SUM;
-    static_assert(NR % 3 == 0, "the G rows rotate through 3 operands");
+    static_assert(NR == 3, "the G rows rotate through 3 operands");
     __shared__ __align__(16) uint16_t S[NL];
     // (readfirstlane: the group's pointers are uniform in a wavefront and belong in scalar registers)
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -938,6 +962,10 @@ k_wgrad_rows(ConvArgs a, const uint16_t *__restrict__ g, int g_cs, int g_co, int
     f32x4 acc[9][2];
 #pragma unroll
     for (int j = 0; j < 9; ++j) acc[j][0] = acc[j][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // (wave-uniform)
+    const bool sums = SUMS && ci0 == 0 && dz == 0 && wc == 0;
+    const bf16x8 ones = as_bf16x8(make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u));
+    f32x4 accb[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
     bf16x8 fg[3][2], fx[2][3];                         // operands of G's last three rows, of this and the next input row
 #pragma unroll
     for (int k = 0; k < 3; ++k) fg[k][0] = fg[k][1] = as_bf16x8(make_uint4(0, 0, 0, 0));
@@ -981,26 +1009,41 @@ k_wgrad_rows(ConvArgs a, const uint16_t *__restrict__ g, int g_cs, int g_co, int
                             fg[(k + 3 - dy) % 3][i], fx[k & 1][dx], acc[dy * 3 + dx][i], 0, 0, 0);
             }
         }
+        if (sums)                                      // fg[k]: G's row k of the stage
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) accb[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fg[k][i], ones, accb[i], 0, 0, 0);
         if (st + 1 < total) stash((st + 1) & 1);
     }
     // the groups' sums: the upper half of the groups adds to the lower half until one is left
-    if (WK > 1) {
-        float *sum = (float *)S + lane;
+    float *sum = (float *)S + lane;
 #pragma unroll
-        for (int half = WK / 2; half > 0; half >>= 1) {
-            __syncthreads();
-            float *w = sum + (((kg - half) * WR * WC + wave % (WR * WC)) * 72) * 64;
-            if (kg >= half && kg < 2 * half)
+    for (int half = WK / 2; half > 0; half >>= 1) {
+        __syncthreads();
+        float *w = sum + (((kg - half) * WR * WC + wave % (WR * WC)) * NA) * 64;
+        if (kg >= half && kg < 2 * half) {
 #pragma unroll
-                for (int j = 0; j < 72; ++j) w[64 * j] = acc[j >> 3][(j >> 2) & 1][j & 3];
-            __syncthreads();
-            w = sum + ((kg * WR * WC + wave % (WR * WC)) * 72) * 64;
-            if (kg < half)
+            for (int j = 0; j < 72; ++j) w[64 * j] = acc[j >> 3][(j >> 2) & 1][j & 3];
+            if (SUMS)
 #pragma unroll
-                for (int j = 0; j < 72; ++j) acc[j >> 3][(j >> 2) & 1][j & 3] += w[64 * j];
+                for (int j = 0; j < 8; ++j) w[64 * (72 + j)] = accb[j >> 2][j & 3];
         }
-        if (kg) return;
+        __syncthreads();
+        w = sum + ((kg * WR * WC + wave % (WR * WC)) * NA) * 64;
+        if (kg < half) {
+#pragma unroll
+            for (int j = 0; j < 72; ++j) acc[j >> 3][(j >> 2) & 1][j & 3] += w[64 * j];
+            if (SUMS)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) accb[j >> 2][j & 3] += w[64 * (72 + j)];
+        }
     }
+    if (kg) return;
+    if (sums && (lane & 15) == 0)                          // accb[i][q]: row r0 + 32 wr + 16 i + 4 (lane >> 4) + q
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            bpart[(long long)zp * rows + r0 + 32 * wr + 16 * (j >> 2) + 4 * (lane >> 4) + (j & 3)] = accb[j >> 2][j & 3];
     // acc[j][i][q]: row r0 + 32 wr + 16 i + 4 (lane >> 4) + q, channel ci0 + 16 wc + (lane & 15), tap j
     float *dst = part + (long long)zp * rows * a.K + (a.dims == 3 ? 9 * (dz + 1) * a.cin : 0) + ci0 + 16 * wc + (lane & 15);
     if (C8 && (lane & 15) >= 8) return;
@@ -1017,14 +1060,24 @@ k_wgrad_rows(ConvArgs a, const uint16_t *__restrict__ g, int g_cs, int g_co, int
 // Sum of split partials: a block takes 64 V outputs (V per lane, one load), its
 // NW wavefronts the splits z = w, w + NW, ..., combined in wavefront order
 // (deterministic).  Bound by memory: 16 wavefronts keep enough rows in flight
-// where outputs are few and splits many.
+// where outputs are few and splits many.  The blocks from the nb'th on sum the
+// n2 outputs of part2 (the bias gradient's partials).
 template <int NW, int V>
 __global__ void __launch_bounds__(64 * NW) k_sum_splits(const float *__restrict__ part, int splits, long long n,
-                                                        float *__restrict__ out, int accumulate) {
+                                                        float *__restrict__ out, int accumulate, unsigned nb,
+                                                        const float *__restrict__ part2, long long n2,
+                                                        float *__restrict__ out2) {
     typedef float vec __attribute__((ext_vector_type(V)));
     __shared__ vec sh[NW][64];
     const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const long long i = ((long long)blockIdx.x * 64 + l) * V;
+    unsigned b = blockIdx.x;
+    if (b >= nb) {
+        b -= nb;
+        part = part2;
+        n = n2;
+        out = out2;
+    }
+    const long long i = ((long long)b * 64 + l) * V;
     vec s = 0.f;
     if (i < n)
 #pragma unroll 8
@@ -1157,7 +1210,8 @@ __global__ void k_pool_fwd(const uint16_t *__restrict__ in, int in_cs, int in_co
 // Routes dout to the first maximal element of each window (sub order).
 __global__ void k_pool_bwd(const uint16_t *__restrict__ in, int in_cs, int in_co,
                            const uint16_t *__restrict__ gout, int g_cs, int g_co, uint16_t *__restrict__ gin,
-                           int gi_cs, int gi_co, int n, int d, int h, int w, int C, int dims, int accumulate) {
+                           int gi_cs, int gi_co, int n, int d, int h, int w, int C, int dims, int accumulate,
+                           int relu) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     const long long total = (long long)n * d * h * w * C;
     if (i >= total) return;
@@ -1179,7 +1233,8 @@ __global__ void k_pool_bwd(const uint16_t *__restrict__ in, int in_cs, int in_co
     for (int sub = 0; sub < (1 << dims); ++sub) {
         const long long o = fidx[sub] * gi_cs + gi_co + c;
         const float add = sub == arg ? gv : 0.f;
-        if (accumulate) { if (sub == arg) gin[o] = f2bf(bf2f(gin[o]) + add); }
+        if (relu && !(bf2f(in[fidx[sub] * in_cs + in_co + c]) > 0.f)) gin[o] = 0;
+        else if (accumulate) { if (sub == arg) gin[o] = f2bf(bf2f(gin[o]) + add); }
         else gin[o] = f2bf(add);
     }
 }
@@ -1211,37 +1266,47 @@ __global__ void __launch_bounds__(256) k_pool_fwd8(const uint16_t *__restrict__ 
     *(uint4 *)(out + m * out_cs + out_co + c) = pack8(best);
 }
 
+// RELU: `in` holds ReLU outputs, and the sum is 0 where they are not > 0.
+template <int DIMS, bool RELU>
 __global__ void __launch_bounds__(256) k_pool_bwd8(const uint16_t *__restrict__ in, int in_cs, int in_co,
                                                    const uint16_t *__restrict__ gout, int g_cs, int g_co,
                                                    uint16_t *__restrict__ gin, int gi_cs, int gi_co, int n, int d,
-                                                   int h, int w, int C, int dims, int accumulate) {
+                                                   int h, int w, int C, int accumulate) {
+    constexpr int NS = 1 << DIMS;
     const int CG = C >> 3;
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (long long)n * d * h * w * CG) return;
     const long long m = i / CG;
     const int c = (int)(i - m * CG) * 8;
     const Pix p = pix_of(m, d, h, w);
-    const int fd = dims == 3 ? 2 * d : 1;
+    const int fd = DIMS == 3 ? 2 * d : 1;
     float best[8], v[8], gv[8];
     int arg[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) { best[k] = -INFINITY; arg[k] = 0; }
-    long long fidx[8];
-    for (int sub = 0; sub < (1 << dims); ++sub) {
+    long long fidx[NS];
+    uint4 win[NS], old[NS];
+#pragma unroll
+    for (int sub = 0; sub < NS; ++sub) {
         const int sx = sub & 1, sy = (sub >> 1) & 1, sz = (sub >> 2) & 1;
-        const int zf = dims == 3 ? 2 * p.z + sz : 0;
+        const int zf = DIMS == 3 ? 2 * p.z + sz : 0;
         fidx[sub] = (((long long)p.b * fd + zf) * (2 * h) + 2 * p.y + sy) * (2 * w) + 2 * p.x + sx;
-        unpack8(*(const uint4 *)(in + fidx[sub] * in_cs + in_co + c), v);
+        win[sub] = *(const uint4 *)(in + fidx[sub] * in_cs + in_co + c);
+        if (accumulate) old[sub] = *(const uint4 *)(gin + fidx[sub] * gi_cs + gi_co + c);
+    }
+#pragma unroll
+    for (int sub = 0; sub < NS; ++sub) {
+        unpack8(win[sub], v);
 #pragma unroll
         for (int k = 0; k < 8; ++k)
             if (v[k] > best[k]) { best[k] = v[k]; arg[k] = sub; }
     }
     unpack8(*(const uint4 *)(gout + m * g_cs + g_co + c), gv);
-    for (int sub = 0; sub < (1 << dims); ++sub) {
-        uint16_t *o = gin + fidx[sub] * gi_cs + gi_co + c;
+#pragma unroll
+    for (int sub = 0; sub < NS; ++sub) {
         float r[8];
         if (accumulate) {
-            unpack8(*(const uint4 *)o, r);
+            unpack8(old[sub], r);
 #pragma unroll
             for (int k = 0; k < 8; ++k)
                 if (sub == arg[k]) r[k] = r[k] + gv[k];
@@ -1249,7 +1314,8 @@ __global__ void __launch_bounds__(256) k_pool_bwd8(const uint16_t *__restrict__ 
 #pragma unroll
             for (int k = 0; k < 8; ++k) r[k] = sub == arg[k] ? gv[k] : 0.f;
         }
-        *(uint4 *)o = pack8(r);
+        if (RELU) relu_mask(r, win[sub]);
+        *(uint4 *)(gin + fidx[sub] * gi_cs + gi_co + c) = pack8(r);
     }
 }
 
@@ -1449,7 +1515,7 @@ static bool halo_ok(const ConvArgs &a) {
     return (a.dims == 2 || a.dims == 3) && a.ks == 3 && !(a.flags & (FLAG_S2D | FLAG_D2S)) && a.cin % 8 == 0 &&
            a.h % HY == 0 &&
            a.w % HX == 0 && ((a.in_cs | a.in_co | a.out_cs | a.out_co) & 7) == 0 && ((uintptr_t)a.in & 15) == 0 &&
-           (ob & 15) == 0 && 18LL * a.w * a.in_cs < (1LL << 31) && (long long)a.ncols * a.K < (1LL << 31) &&
+           (ob & 15) == 0 && ((a.mask_cs | a.mask_co) & 7) == 0 && ((uintptr_t)a.mask & 15) == 0 && 18LL * a.w * a.in_cs < (1LL << 31) && (long long)a.ncols * a.K < (1LL << 31) &&
            a.M < (1LL << 31);
 }
 
@@ -1471,6 +1537,7 @@ __global__ void __launch_bounds__(256) k_conv_reduce(ConvArgs a, const float *__
         a.out32[o] = (a.flags & FLAG_ACC) ? a.out32[o] + v : v;
     } else {
         if (a.flags & FLAG_ACC) v += bf2f(a.out[o]);
+        if (a.mask && !(bf2f(a.mask[m * a.mask_cs + a.mask_co + c]) > 0.f)) v = 0.f;
         a.out[o] = f2bf(v);
     }
 }
@@ -1518,14 +1585,17 @@ hipError_t conv(const ConvArgs &a, hipStream_t s) {
         const int tn = a.ncols <= 32 ? 32 : 64, tiles_n = (a.ncols + tn - 1) / tn;
         const long long tiles = (long long)a.n * a.d * (a.h / HY) * (a.w / HX);
         const bool res = a.dims == 2 && a.cin <= HC;
-        const bool plain = !a.out32 && !(a.flags & FLAG_ACC);
+        const int mode = a.out32 || (a.flags & FLAG_ACC) ? OUT_ANY : a.mask ? OUT_MASK : OUT_PLAIN;
         // two blocks per CU, each walking over as many tiles as that leaves it
         const int runs = (512 + tiles_n - 1) / tiles_n, per = (int)((tiles + runs - 1) / runs);
         const dim3 grid((unsigned)((tiles + per - 1) / per * tiles_n));
-#define CALL(TN, DIMS, RES)                                                                                     \
-    do {                                                                                                        \
-        if (plain) hipLaunchKernelGGL((k_conv3x3_rows<TN, DIMS, RES, true>), grid, dim3(256), 0, s, a, per);    \
-        else hipLaunchKernelGGL((k_conv3x3_rows<TN, DIMS, RES, false>), grid, dim3(256), 0, s, a, per);         \
+#define LAUNCH(TN, DIMS, RES, MODE) \
+    hipLaunchKernelGGL((k_conv3x3_rows<TN, DIMS, RES, MODE>), grid, dim3(256), 0, s, a, per)
+#define CALL(TN, DIMS, RES)                                        \
+    do {                                                           \
+        if (mode == OUT_PLAIN) LAUNCH(TN, DIMS, RES, OUT_PLAIN);   \
+        else if (mode == OUT_MASK) LAUNCH(TN, DIMS, RES, OUT_MASK); \
+        else LAUNCH(TN, DIMS, RES, OUT_ANY);                       \
     } while (0)
         if (a.dims == 3) {
             if (tn == 32) CALL(32, 3, false);
@@ -1538,6 +1608,7 @@ hipError_t conv(const ConvArgs &a, hipStream_t s) {
             else CALL(64, 2, false);
         }
 #undef CALL
+#undef LAUNCH
         return hipGetLastError();
     }
     if (a.ncols <= 32) {
@@ -1555,17 +1626,21 @@ long long wgrad_chunk(long long M, int splits) {
     return (c + WPB - 1) / WPB * WPB;
 }
 
-// Sum of z split partials into n outputs: a block per output when there are
-// few (bias gradients), else 64 outputs per block.
-static hipError_t sum_splits(const float *part, int z, long long n, float *out, int accumulate, hipStream_t s) {
-    if (n <= 1024 && z > 16)
+// Sum of z split partials into n outputs (and of part2 into n2): a block per
+// output when there are few (bias gradients), else 64 or 256 outputs per block.
+static hipError_t sum_splits(const float *part, int z, long long n, float *out, int accumulate, hipStream_t s,
+                             const float *part2 = nullptr, long long n2 = 0, float *out2 = nullptr) {
+    if (n <= 1024 && z > 16 && !part2) {
         hipLaunchKernelGGL(k_sum_splits_narrow, dim3((unsigned)n), dim3(256), 0, s, part, z, n, out, accumulate);
-    else if (n % 4 == 0 && ((uintptr_t)part & 15) == 0 && n >= 65536)
-        hipLaunchKernelGGL((k_sum_splits<4, 4>), dim3(blocks(n, 256)), dim3(256), 0, s, part, z, n, out, accumulate);
-    else if (z > 32)
-        hipLaunchKernelGGL((k_sum_splits<16, 1>), dim3(blocks(n, 64)), dim3(1024), 0, s, part, z, n, out, accumulate);
-    else
-        hipLaunchKernelGGL((k_sum_splits<4, 1>), dim3(blocks(n, 64)), dim3(256), 0, s, part, z, n, out, accumulate);
+        return hipGetLastError();
+    }
+#define CALL(NW, V)                                                                                              \
+    hipLaunchKernelGGL((k_sum_splits<NW, V>), dim3(blocks(n, 64 * V) + blocks(n2, 64 * V)), dim3(64 * NW), 0, s, \
+                       part, z, n, out, accumulate, blocks(n, 64 * V), part2, n2, out2)
+    if (n >= 65536 && ((n | n2) & 3) == 0 && (((uintptr_t)part | (uintptr_t)part2) & 15) == 0) CALL(4, 4);
+    else if (z > 32) CALL(16, 1);
+    else CALL(4, 1);
+#undef CALL
     return hipGetLastError();
 }
 
@@ -1583,7 +1658,7 @@ static int rows_shape(const ConvArgs &a, int rows, int g_cs) {
     return 0;
 }
 
-template <int PW>
+template <int PW, bool SUMS>
 static hipError_t launch_wgrad_rows(int shape, const ConvArgs &a, const uint16_t *g, int g_cs, int g_co, int rows,
                                     float *part, int &z, hipStream_t s) {
     const int RB = shape == 22 ? 64 : 32, CB = shape == 11 ? 8 : shape == 14 ? 64 : 32;
@@ -1603,26 +1678,31 @@ static hipError_t launch_wgrad_rows(int shape, const ConvArgs &a, const uint16_t
         k = WgradWalk{len, pieces, (int)per, sps, (int)((strips * pieces + per * WK - 1) / (per * WK))};
     }
     z = k.z;
+    float *bpart = part + (long long)z * rows * a.K;
     const dim3 grid((unsigned)(tiles * z));
     if (shape == 22)
-        hipLaunchKernelGGL((k_wgrad_rows<PW, 2, 2, false>), grid, dim3(512), 0, s, a, g, g_cs, g_co, rows, part, k);
+        hipLaunchKernelGGL((k_wgrad_rows<PW, 2, 2, false, SUMS>), grid, dim3(512), 0, s, a, g, g_cs, g_co, rows, part, bpart, k);
     else if (shape == 14)
-        hipLaunchKernelGGL((k_wgrad_rows<PW, 1, 4, false>), grid, dim3(512), 0, s, a, g, g_cs, g_co, rows, part, k);
+        hipLaunchKernelGGL((k_wgrad_rows<PW, 1, 4, false, SUMS>), grid, dim3(512), 0, s, a, g, g_cs, g_co, rows, part, bpart, k);
     else if (shape == 12)
-        hipLaunchKernelGGL((k_wgrad_rows<PW, 1, 2, false>), grid, dim3(512), 0, s, a, g, g_cs, g_co, rows, part, k);
+        hipLaunchKernelGGL((k_wgrad_rows<PW, 1, 2, false, SUMS>), grid, dim3(512), 0, s, a, g, g_cs, g_co, rows, part, bpart, k);
     else
-        hipLaunchKernelGGL((k_wgrad_rows<PW, 1, 1, true>), grid, dim3(512), 0, s, a, g, g_cs, g_co, rows, part, k);
+        hipLaunchKernelGGL((k_wgrad_rows<PW, 1, 1, true, SUMS>), grid, dim3(512), 0, s, a, g, g_cs, g_co, rows, part, bpart, k);
     return hipGetLastError();
 }
 
+// Weight gradient and (db) the bias gradient of the same G: from the row
+// kernel, else by a pass of its own.
 hipError_t wgrad(const ConvArgs &a, const uint16_t *g, int g_cs, int g_co, int rows, float *part, int splits,
-                 float *dw, int accumulate, hipStream_t s) {
-    const long long chunk = wgrad_chunk(a.M, splits);
+                 float *dw, float *db, int accumulate, hipStream_t s) {
+    const long long chunk = wgrad_chunk(a.M, splits), n = (long long)rows * a.K;
     int z = (int)((a.M + chunk - 1) / chunk);
     if (const int shape = rows_shape(a, rows, g_cs)) {
-        const hipError_t e = a.w > 16 ? launch_wgrad_rows<32>(shape, a, g, g_cs, g_co, rows, part, z, s)
-                                      : launch_wgrad_rows<16>(shape, a, g, g_cs, g_co, rows, part, z, s);
-        return e != hipSuccess ? e : sum_splits(part, z, (long long)rows * a.K, dw, accumulate, s);
+        const auto f = db ? (a.w > 16 ? launch_wgrad_rows<32, true> : launch_wgrad_rows<16, true>)
+                          : (a.w > 16 ? launch_wgrad_rows<32, false> : launch_wgrad_rows<16, false>);
+        const hipError_t e = f(shape, a, g, g_cs, g_co, rows, part, z, s);
+        if (e != hipSuccess) return e;
+        return db ? sum_splits(part, z, n, dw, accumulate, s, part + z * n, rows, db) : sum_splits(part, z, n, dw, accumulate, s);
     }
     if (rows <= 32) {
         const dim3 grid(1u, (unsigned)((a.K + 127) / 128), (unsigned)z);
@@ -1631,8 +1711,15 @@ hipError_t wgrad(const ConvArgs &a, const uint16_t *g, int g_cs, int g_co, int r
         const dim3 grid((unsigned)((rows + BM - 1) / BM), (unsigned)((a.K + BN - 1) / BN), (unsigned)z);
         hipLaunchKernelGGL(k_wgrad<false>, grid, dim3(256), 0, s, a, g, g_cs, g_co, rows, part, chunk);
     }
-    const long long n = (long long)rows * a.K;
-    return sum_splits(part, z, n, dw, accumulate, s);
+    const hipError_t e = sum_splits(part, z, n, dw, accumulate, s);
+    if (!db || e != hipSuccess) return e;
+    const int fine = (a.flags & FLAG_S2D_G) ? a.dims : 0;         // rows = sub * C + co over the finer grid's pixels
+    const long long pixels = a.M << fine;
+    const int C = rows >> fine;
+    // about 16K elements (32 KB) of G per split, within the z rows floats that the workspace holds
+    long long sp = (pixels * C + 16383) / 16384;
+    if (sp > ((long long)z << fine)) sp = (long long)z << fine;
+    return bias_grad(g, g_cs, g_co, pixels, C, part + z * n, (int)(sp < 1 ? 1 : sp), db, accumulate, s);
 }
 
 bool bias_grad8_ok(const void *g, int cs, int co, int C) {
@@ -1689,15 +1776,21 @@ hipError_t pool_fwd(const uint16_t *in, int in_cs, int in_co, uint16_t *out, int
 
 hipError_t pool_bwd(const uint16_t *in, int in_cs, int in_co, const uint16_t *gout, int g_cs, int g_co,
                     uint16_t *gin, int gi_cs, int gi_co, int n, int d, int h, int w, int C, int dims, int acc,
-                    hipStream_t s) {
+                    int relu, hipStream_t s) {
     const long long tot = (long long)n * d * h * w * C;
     if (vec8(C, in_cs, in_co, g_cs, g_co, in, gout) && vec8(gi_cs, gi_co, 0, 0, 0, gin, nullptr)) {
-        hipLaunchKernelGGL(k_pool_bwd8, dim3(blocks(tot / 8, 256)), dim3(256), 0, s, in, in_cs, in_co, gout, g_cs,
-                           g_co, gin, gi_cs, gi_co, n, d, h, w, C, dims, acc);
+#define CALL(DIMS, RELU)                                                                                          \
+    hipLaunchKernelGGL((k_pool_bwd8<DIMS, RELU>), dim3(blocks(tot / 8, 256)), dim3(256), 0, s, in, in_cs, in_co, \
+                       gout, g_cs, g_co, gin, gi_cs, gi_co, n, d, h, w, C, acc)
+        if (dims == 2 && relu) CALL(2, true);
+        else if (dims == 2) CALL(2, false);
+        else if (relu) CALL(3, true);
+        else CALL(3, false);
+#undef CALL
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_pool_bwd, dim3(blocks(tot, 256)), dim3(256), 0, s, in, in_cs, in_co, gout, g_cs, g_co, gin,
-                       gi_cs, gi_co, n, d, h, w, C, dims, acc);
+                       gi_cs, gi_co, n, d, h, w, C, dims, acc, relu);
     return hipGetLastError();
 }
 

@@ -29,6 +29,8 @@ struct ConvArgs {
     int cin, ncols, ks, dims, flags;
     int K;
     long long M;
+    const uint16_t *mask;   // ReLU backward in the epilogue (BF16 output): 0 where mask[m][mask_co + c] is not > 0
+    int mask_cs, mask_co;
 };
 
 hipError_t conv(const ConvArgs &a, hipStream_t s);
@@ -36,7 +38,7 @@ int conv_splits(const ConvArgs &a);
 hipError_t conv_split(const ConvArgs &a, float *part, int S, hipStream_t s);
 long long wgrad_chunk(long long M, int splits);
 hipError_t wgrad(const ConvArgs &a, const uint16_t *g, int g_cs, int g_co, int rows, float *part, int splits,
-                 float *dw, int accumulate, hipStream_t s);
+                 float *dw, float *db, int accumulate, hipStream_t s);
 hipError_t bias_grad(const uint16_t *g, int cs, int co, long long npix, int C, float *part, int splits, float *db,
                      int accumulate, hipStream_t s);
 hipError_t relu_bwd(uint16_t *g, const uint16_t *y, int cs, int co, long long npix, int C, hipStream_t s);
@@ -46,7 +48,7 @@ hipError_t pool_fwd(const uint16_t *in, int in_cs, int in_co, uint16_t *out, int
                     int h, int w, int C, int dims, hipStream_t s);
 hipError_t pool_bwd(const uint16_t *in, int in_cs, int in_co, const uint16_t *gout, int g_cs, int g_co,
                     uint16_t *gin, int gi_cs, int gi_co, int n, int d, int h, int w, int C, int dims, int acc,
-                    hipStream_t s);
+                    int relu, hipStream_t s);
 hipError_t mse(const float *pred, int pcs, const float *tgt, const float *wpix, int creal, long long npix,
                float scale, uint16_t *dpred, double *part, double *loss, hipStream_t s);
 hipError_t adam(float *w, const float *g, float *m1, float *m2, uint16_t *wb, long long n, float lr, float b1,

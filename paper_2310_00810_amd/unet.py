@@ -74,7 +74,6 @@ class UNet:
         self.t = 0
         self._bufs = {}
         self._ws = torch.empty(0, dtype=torch.float32, device=dev)
-        self._bws = torch.empty(1 << 18, dtype=torch.float32, device=dev)
         self._mse_part = torch.empty(0, dtype=torch.float64, device=dev)
         self.loss_dev = torch.zeros(1, dtype=torch.float64, device=dev)
         self.init_weights(seed)
@@ -203,7 +202,8 @@ class UNet:
 
     # ---------------------------------------------------------- primitives --
     def _conv(self, grid, ks, cin, cout, flags, inp, in_cs, in_co, name, out=None, out_cs=0, out_co=0,
-              out32=None, transposed=False, use_bias=True):
+              out32=None, transposed=False, use_bias=True, relu_of=None):
+        # relu_of = (y, channel stride, offset): the output is masked by the ReLU that produced y
         n, d, h, w = grid
         wsrc = self.wT if transposed else self.wbf
         desc = C.lbmnn_conv_desc(n, d, h, w, self.dims, ks, cin, cout, flags, inp.data_ptr(), in_cs, in_co,
@@ -213,24 +213,32 @@ class UNet:
         taps = (1 << self.dims) if flags & C.NN_S2D else ks ** self.dims
         M = n * d * h * w
         m_in = M << self.dims if flags & C.NN_S2D else M
-        nbytes = 2 * m_in * cin + (4 if out32 is not None else 2) * M * cout + 2 * cout * taps * cin
+        nbytes = (2 * m_in * cin + (4 if out32 is not None else 2) * M * cout + 2 * cout * taps * cin +
+                  (2 * M * cout if relu_of else 0))
         # the deep levels split their K loop: FP32 partials in the shared workspace
         need = self.L.lbmnn_conv_workspace_bytes(ctypes.byref(desc))
         if self._ws.numel() * 4 < need:
             self._ws = torch.empty(need // 4 + 1024, dtype=torch.float32, device=self.device)
-        self._timed("dgrad" if transposed else "fwd", name, 2 * M * cout * taps * cin, nbytes,
-                    lambda: C.check(self.L.lbmnn_conv_ws(ctypes.byref(desc), _ptr(wsrc, self.woff[name]), b,
-                                                         _ptr(self._ws), self._ws.numel() * 4, self._stream()),
-                                    "lbmnn_conv_ws"))
+        if relu_of:
+            y, y_cs, y_co = relu_of
+            run = lambda: C.check(self.L.lbmnn_conv_relu_bwd(ctypes.byref(desc), _ptr(wsrc, self.woff[name]), _ptr(y),
+                                                             y_cs, y_co, _ptr(self._ws), self._ws.numel() * 4,
+                                                             self._stream()), "lbmnn_conv_relu_bwd")
+        else:
+            run = lambda: C.check(self.L.lbmnn_conv_ws(ctypes.byref(desc), _ptr(wsrc, self.woff[name]), b,
+                                                       _ptr(self._ws), self._ws.numel() * 4, self._stream()),
+                                  "lbmnn_conv_ws")
+        self._timed("dgrad" if transposed else "fwd", name, 2 * M * cout * taps * cin, nbytes, run)
 
     def _wgrad(self, grid, ks, cin, flags, inp, in_cs, in_co, g, g_cs, g_co, rows, name):
+        # weight and bias gradient of the layer
         n, d, h, w = grid
         M = n * d * h * w
         K = cin * (ks ** self.dims) if not (flags & C.NN_S2D) else cin * (1 << self.dims)
         # blocks per pixel split: 32 x 128 tiles for at most 32 rows, else 64 x 64
         base_blocks = -(-K // 128) if rows <= 32 else -(-rows // 64) * -(-K // 64)
         splits = max(1, min(M // 512, max(1, 2048 // base_blocks)))
-        need = self.L.lbmnn_wgrad_workspace_bytes(M, rows, K, splits)
+        need = self.L.lbmnn_wgrad_workspace_bytes(M, rows, K + 1, splits)
         if self._ws.numel() * 4 < need:
             self._ws = torch.empty(need // 4 + 1024, dtype=torch.float32, device=self.device)
         desc = C.lbmnn_conv_desc(n, d, h, w, self.dims, ks, cin, 0, flags, inp.data_ptr(), in_cs, in_co,
@@ -240,29 +248,11 @@ class UNet:
         g_ch = rows >> self.dims if flags & C.NN_S2D_G else rows
         nbytes = 2 * m_in * cin + 2 * m_g * g_ch + 4 * rows * K
         self._timed("wgrad", name, 2 * M * rows * K, nbytes,
-                    lambda: C.check(self.L.lbmnn_conv_wgrad(ctypes.byref(desc), ctypes.c_void_p(g.data_ptr()), g_cs,
-                                                            g_co, rows, _ptr(self.grad, self.woff[name]), 0,
-                                                            _ptr(self._ws), self._ws.numel() * 4, splits,
-                                                            self._stream()), "lbmnn_conv_wgrad"))
-
-    def _bgrad(self, g, cs, co, pixels, Cn, name):
-        # about 16K elements (32 KB) per split, enough blocks to keep HBM busy at every level,
-        # bounded by the partials buffer
-        splits = max(1, min(-(-pixels * Cn // 16384), self._bws.numel() // Cn))
-        self._timed("bgrad", name, pixels * Cn, 2 * pixels * Cn + 4 * Cn,
-                    lambda: C.check(self.L.lbmnn_bias_grad(ctypes.c_void_p(g.data_ptr()), cs, co, pixels, Cn,
-                                                           _ptr(self.grad, self.boff[name]), 0, _ptr(self._bws),
-                                                           splits, self._stream()), "lbmnn_bias_grad"))
-
-    def _relu_bgrad(self, g, y, cs, co, pixels, Cn, name):
-        # ReLU backward and the bias gradient of the masked g in one pass (splits as in _bgrad)
-        splits = max(1, min(-(-pixels * Cn // 16384), self._bws.numel() // Cn))
-        self._timed("relu_bgrad", name, 2 * pixels * Cn, 6 * pixels * Cn + 4 * Cn,
-                    lambda: C.check(self.L.lbmnn_relu_bwd_bias_grad(ctypes.c_void_p(g.data_ptr()),
-                                                                    ctypes.c_void_p(y.data_ptr()), cs, co, pixels, Cn,
-                                                                    _ptr(self.grad, self.boff[name]), 0,
-                                                                    _ptr(self._bws), splits, self._stream()),
-                                    "lbmnn_relu_bwd_bias_grad"))
+                    lambda: C.check(self.L.lbmnn_conv_wgrad_bias(ctypes.byref(desc), ctypes.c_void_p(g.data_ptr()),
+                                                                 g_cs, g_co, rows, _ptr(self.grad, self.woff[name]),
+                                                                 _ptr(self.grad, self.boff[name]), 0, _ptr(self._ws),
+                                                                 self._ws.numel() * 4, splits, self._stream()),
+                                    "lbmnn_conv_wgrad_bias"))
 
     # -------------------------------------------------------------- forward --
     def forward(self, x):
@@ -317,54 +307,46 @@ class UNet:
         self._transpose_weights()
         dims = self.dims
         S = 1 << dims
-        npix = lambda lv: math.prod(self._grid(shape, lv))
         g0 = self._grid(shape, 0)
+        # Every gradient is masked by its layer's ReLU where it is produced, by an input
+        # gradient or a pooling backward, and its bias gradient comes with the weight gradient.
         # head (1x1)
-        self._wgrad(g0, 1, self.base, 0, B["d0c1"] if self.levels > 1 else B["bott"], self.base, 0,
-                    g_head, self.cout, 0, self.cout, "head")
-        self._bgrad(g_head, self.cout, 0, npix(0), self.cout, "head")
-        self._conv(g0, 1, self.cout, self.base, 0, g_head, self.cout, 0, "head", out=B["g_d0c1"],
-                   out_cs=self.base, transposed=True, use_bias=False)
+        top = ("d0c1" if self.levels > 1 else "bott")
+        self._wgrad(g0, 1, self.base, 0, B[top], self.base, 0, g_head, self.cout, 0, self.cout, "head")
+        self._conv(g0, 1, self.cout, self.base, 0, g_head, self.cout, 0, "head", out=B["g_" + top],
+                   out_cs=self.base, transposed=True, relu_of=(B[top], self.base, 0))
         for lv in range(0, self.levels - 1):
             Cl = self.base << lv
             g = self._grid(shape, lv)
-            P = npix(lv)
             # second decoder conv
-            self._relu_bgrad(B[f"g_d{lv}c1"], B[f"d{lv}c1"], Cl, 0, P, Cl, f"d{lv}c1")
             self._wgrad(g, 3, Cl, 0, B[f"d{lv}c0"], Cl, 0, B[f"g_d{lv}c1"], Cl, 0, Cl, f"d{lv}c1")
             self._conv(g, 3, Cl, Cl, 0, B[f"g_d{lv}c1"], Cl, 0, f"d{lv}c1", out=B[f"g_d{lv}c0"], out_cs=Cl,
-                       transposed=True, use_bias=False)
+                       transposed=True, relu_of=(B[f"d{lv}c0"], Cl, 0))
             # first decoder conv (input: concatenation)
-            self._relu_bgrad(B[f"g_d{lv}c0"], B[f"d{lv}c0"], Cl, 0, P, Cl, f"d{lv}c0")
             self._wgrad(g, 3, 2 * Cl, 0, B[f"cat{lv}"], 2 * Cl, 0, B[f"g_d{lv}c0"], Cl, 0, Cl, f"d{lv}c0")
             self._conv(g, 3, Cl, 2 * Cl, 0, B[f"g_d{lv}c0"], Cl, 0, f"d{lv}c0", out=B[f"g_cat{lv}"],
                        out_cs=2 * Cl, transposed=True, use_bias=False)
             # transposed conv: input on the coarser grid
             gc = self._grid(shape, lv + 1)
-            hin = B[f"d{lv + 1}c1"] if lv + 1 < self.levels - 1 else B["bott"]
-            g_hin = B[f"g_d{lv + 1}c1"] if lv + 1 < self.levels - 1 else B["g_bott"]
-            self._wgrad(gc, 1, 2 * Cl, C.NN_S2D_G, hin, 2 * Cl, 0, B[f"g_cat{lv}"], 2 * Cl, 0, S * Cl, f"d{lv}t")
-            self._bgrad(B[f"g_cat{lv}"], 2 * Cl, 0, P, Cl, f"d{lv}t")
-            self._conv(gc, 1, Cl, 2 * Cl, C.NN_S2D, B[f"g_cat{lv}"], 2 * Cl, 0, f"d{lv}t", out=g_hin,
-                       out_cs=2 * Cl, transposed=True, use_bias=False)
+            below = f"d{lv + 1}c1" if lv + 1 < self.levels - 1 else "bott"
+            self._wgrad(gc, 1, 2 * Cl, C.NN_S2D_G, B[below], 2 * Cl, 0, B[f"g_cat{lv}"], 2 * Cl, 0, S * Cl, f"d{lv}t")
+            self._conv(gc, 1, Cl, 2 * Cl, C.NN_S2D, B[f"g_cat{lv}"], 2 * Cl, 0, f"d{lv}t", out=B["g_" + below],
+                       out_cs=2 * Cl, transposed=True, relu_of=(B[below], 2 * Cl, 0))
         for lv in range(self.levels - 1, -1, -1):
             Cl = self.base << lv
             g = self._grid(shape, lv)
-            P = npix(lv)
             if lv < self.levels - 1:
                 # skip gradient (already in the upper half of g_cat) + pooling path
                 gc = self._grid(shape, lv + 1)
-                C.check(self.L.lbmnn_pool_bwd(_ptr(B[f"cat{lv}"]), 2 * Cl, Cl, _ptr(B[f"g_p{lv}"]), Cl, 0,
-                                              _ptr(B[f"g_cat{lv}"]), 2 * Cl, Cl, *gc, Cl, dims, 1,
-                                              self._stream()), "lbmnn_pool_bwd")
-                y1, gy1, cs1, co1 = B[f"cat{lv}"], B[f"g_cat{lv}"], 2 * Cl, Cl
+                C.check(self.L.lbmnn_pool_bwd_relu(_ptr(B[f"cat{lv}"]), 2 * Cl, Cl, _ptr(B[f"g_p{lv}"]), Cl, 0,
+                                                   _ptr(B[f"g_cat{lv}"]), 2 * Cl, Cl, *gc, Cl, dims, 1,
+                                                   self._stream()), "lbmnn_pool_bwd_relu")
+                gy1, cs1, co1 = B[f"g_cat{lv}"], 2 * Cl, Cl
             else:
-                y1, gy1, cs1, co1 = B["bott"], B["g_bott"], Cl, 0
-            self._relu_bgrad(gy1, y1, cs1, co1, P, Cl, f"e{lv}c1")
+                gy1, cs1, co1 = B["g_bott"], Cl, 0
             self._wgrad(g, 3, Cl, 0, B[f"e{lv}c0"], Cl, 0, gy1, cs1, co1, Cl, f"e{lv}c1")
             self._conv(g, 3, Cl, Cl, 0, gy1, cs1, co1, f"e{lv}c1", out=B[f"g_e{lv}c0"], out_cs=Cl,
-                       transposed=True, use_bias=False)
-            self._relu_bgrad(B[f"g_e{lv}c0"], B[f"e{lv}c0"], Cl, 0, P, Cl, f"e{lv}c0")
+                       transposed=True, relu_of=(B[f"e{lv}c0"], Cl, 0))
             if lv == 0:
                 xin, xcs, Cin = x, self.cin, self.cin
             else:
@@ -469,7 +451,7 @@ MFMA_PEAK_TFLOPS, HBM_PEAK_GBS = 2500.0, 8000.0
 
 def layer_roofline(net, x, tgt, wpix, steps=3):
     """Per operation of a training step (layer forward, input gradient,
-    weight gradient, bias / ReLU backward): HIP-event time on the current
+    weight and bias gradient): HIP-event time on the current
     stream, averaged over `steps` steps, against its own roofline: the larger
     of flops / dense BF16 MFMA peak and minimal bytes / HBM peak.  Returns a
     list of dicts sorted by time, longest first."""

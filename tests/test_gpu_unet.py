@@ -557,3 +557,82 @@ def test_fused_relu_backward_and_bias_gradient(npix, cs, co, Cn):
     gm[y.float().cpu().numpy()[:, co:co + Cn] <= 0] = 0
     assert np.array_equal(gb.float().cpu().numpy()[:, co:co + Cn], gm)
     assert np.allclose(db.cpu().numpy(), gm.sum(0), rtol=1e-5, atol=1e-4)
+
+
+# the fused backward passes against the separate ones, on the row kernel (2D, 3D, channel slices), the
+# im2col kernel, its K-split form and an S2D input gradient
+FUSED = [(2, 3, (7, 1, 160, 128), 40, 72, 0), (3, 3, (3, 5, 120, 96), 32, 24, 0), (2, 3, (2, 1, 20, 24), 16, 24, 0),
+         (2, 1, (1, 1, 40, 72), 8, 32, 0), (2, 3, (1, 1, 16, 16), 128, 64, 0), (2, 1, (1, 1, 12, 20), 32, 64, 4)]
+
+
+@pytest.mark.parametrize("dims,ks,grid,cin,cout,flags", FUSED)
+def test_masked_convolution_equals_the_two_passes(dims, ks, grid, cin, cout, flags):
+    g = torch.Generator(device="cuda").manual_seed(6)
+    C = C_()
+    L = C.nnlib()
+    n, d, h, w = grid
+    f = 2 if flags else 1
+    x = torch.randn((n, d, f * h, f * w, cin), generator=g, device="cuda").to(torch.bfloat16)
+    K = cin * (4 if flags else ks ** dims)
+    W = (torch.randn((cout, K), generator=g, device="cuda") / K ** 0.5).to(torch.bfloat16)
+    y = torch.randn(grid + (cout + 16,), generator=g, device="cuda").clamp(min=0).to(torch.bfloat16)
+    out = [torch.zeros(grid + (cout + 8,), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    desc = [C.lbmnn_conv_desc(n, d, h, w, dims, ks, cin, cout, flags, x.data_ptr(), cin, 0, o.data_ptr(), None,
+                              cout + 8, 8) for o in out]
+    need = L.lbmnn_conv_workspace_bytes(ctypes.byref(desc[0]))
+    ws = torch.empty(need // 4 + 1, dtype=torch.float32, device="cuda")
+    C.check(L.lbmnn_conv_relu_bwd(ctypes.byref(desc[0]), W.data_ptr(), y.data_ptr(), cout + 16, 8, ws.data_ptr(),
+                                  need, stream()), "conv_relu_bwd")
+    C.check(L.lbmnn_conv_ws(ctypes.byref(desc[1]), W.data_ptr(), None, ws.data_ptr(), need, stream()), "conv_ws")
+    out[1][..., 8:][y[..., 8:8 + cout] == 0] = 0
+    assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("dims,ks,grid,cin,rows,flags,splits", [
+    (2, 3, (3, 1, 18, 45), 64, 64, 0, 7), (2, 3, (2, 1, 37, 70), 32, 32, 0, 64), (2, 3, (1, 1, 33, 16), 8, 32, 0, 3),
+    (3, 3, (2, 5, 12, 40), 64, 32, 0, 4), (2, 3, (2, 1, 9, 12), 16, 24, 0, 5), (2, 1, (2, 1, 30, 40), 32, 8, 0, 6),
+    (2, 1, (1, 1, 20, 24), 64, 128, 16, 9), (3, 1, (1, 3, 8, 8), 16, 64, 16, 2)])
+@pytest.mark.parametrize("accumulate", [0, 1])
+def test_weight_gradient_with_bias_gradient(dims, ks, grid, cin, rows, flags, splits, accumulate):
+    rng = np.random.default_rng(16)
+    C = C_()
+    L = C.nnlib()
+    n, d, h, w = grid
+    f = 2 if flags else 1
+    gch = rows >> dims if flags else rows
+    x = dev_bf(bf(rng.standard_normal(grid + (cin,))))
+    g = bf(rng.standard_normal((n, d * (f if dims == 3 else 1), h * f, w * f, gch + 8)))
+    gd = dev_bf(g)
+    K = cin * ks ** dims
+    need = L.lbmnn_wgrad_workspace_bytes(n * d * h * w, rows, K + 1, splits)
+    ws = torch.empty(need // 4 + 1, dtype=torch.float32, device="cuda")
+    dw, ref = (torch.full((rows, K), 0.5, device="cuda") for _ in range(2))
+    db = torch.full((gch,), 0.25, device="cuda")
+    desc = C.lbmnn_conv_desc(n, d, h, w, dims, ks, cin, 0, flags, x.data_ptr(), cin, 0, None, None, 0, 0)
+    C.check(L.lbmnn_conv_wgrad_bias(ctypes.byref(desc), gd.data_ptr(), gch + 8, 8, rows, dw.data_ptr(), db.data_ptr(),
+                                    accumulate, ws.data_ptr(), need, splits, stream()), "wgrad_bias")
+    C.check(L.lbmnn_conv_wgrad(ctypes.byref(desc), gd.data_ptr(), gch + 8, 8, rows, ref.data_ptr(), accumulate,
+                               ws.data_ptr(), need, splits, stream()), "wgrad")
+    exp = g[..., 8:].reshape(-1, gch).sum(0) + (0.25 if accumulate else 0.0)
+    assert torch.equal(dw, ref)
+    # FP32 sums of up to 5,000 unit-variance values: 6e-8 x 70 x a few roundings
+    assert np.all(np.abs(db.double().cpu().numpy() - exp) <= 1e-4)
+
+
+@pytest.mark.parametrize("dims,Cn,cs,co,acc", [(2, 16, 32, 8, 1), (3, 8, 8, 0, 0), (2, 12, 20, 3, 1), (3, 16, 24, 8, 1)])
+def test_masked_pooling_backward_equals_the_two_passes(dims, Cn, cs, co, acc):
+    g = torch.Generator(device="cuda").manual_seed(8)
+    C = C_()
+    L = C.nnlib()
+    d = 3 if dims == 3 else 1
+    fine = (2, 2 * d if dims == 3 else 1, 10, 14)
+    x = torch.randn(fine + (cs,), generator=g, device="cuda").clamp(min=0).to(torch.bfloat16)
+    go = torch.randn((2, d, 5, 7, cs), generator=g, device="cuda").to(torch.bfloat16)
+    a = torch.randn(fine + (cs,), generator=g, device="cuda").to(torch.bfloat16)
+    b = a.clone()
+    args = (x.data_ptr(), cs, co, go.data_ptr(), cs, co)
+    dim = (cs, co, 2, d, 5, 7, Cn, dims, acc, stream())
+    C.check(L.lbmnn_pool_bwd_relu(*args, a.data_ptr(), *dim), "pool_bwd_relu")
+    C.check(L.lbmnn_pool_bwd(*args, b.data_ptr(), *dim), "pool_bwd")
+    C.check(L.lbmnn_relu_bwd(b.data_ptr(), x.data_ptr(), cs, co, b.numel() // cs, Cn, stream()), "relu_bwd")
+    assert torch.equal(a, b)
