@@ -112,7 +112,7 @@ def check(rc, where):
 NN_EXPORTS = [
     "lbmnn_conv", "lbmnn_conv_workspace_bytes", "lbmnn_conv_ws", "lbmnn_conv_relu_bwd",
     "lbmnn_wgrad_workspace_bytes", "lbmnn_conv_wgrad", "lbmnn_conv_wgrad_bias", "lbmnn_conv_wgrad_noalloc",
-    "lbmnn_weight_transpose",
+    "lbmnn_weight_transpose", "lbmnn_weight_transpose_layers",
     "lbmnn_bias_grad", "lbmnn_relu_bwd", "lbmnn_relu_bwd_bias_grad", "lbmnn_pool_fwd", "lbmnn_pool_bwd",
     "lbmnn_pool_bwd_relu",
     "lbmnn_mse", "lbmnn_adam", "lbmnn_to_bf16", "lbmnn_features", "lbmnn_normalize", "lbmnn_denormalize",
@@ -151,6 +151,7 @@ def nnlib():
         L.lbmnn_conv_wgrad_bias.argtypes = [dp, vp, ip, ip, ip, vp, vp, ip, vp, ctypes.c_size_t, ip, vp]
         L.lbmnn_conv_wgrad_noalloc.argtypes = [dp, vp, ip, ip, ip, vp, ip, ip, vp]
         L.lbmnn_weight_transpose.argtypes = [vp, vp, ip, ip, ip, ip, vp]
+        L.lbmnn_weight_transpose_layers.argtypes = [vp, vp, ip, vp, vp, vp, vp, vp, vp]
         L.lbmnn_bias_grad.argtypes = [vp, ip, ip, ll, ip, vp, ip, vp, ip, vp]
         L.lbmnn_relu_bwd.argtypes = [vp, vp, ip, ip, ll, ip, vp]
         L.lbmnn_relu_bwd_bias_grad.argtypes = [vp, vp, ip, ip, ll, ip, vp, ip, vp, ip, vp]

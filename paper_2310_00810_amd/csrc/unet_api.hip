@@ -238,6 +238,29 @@ int lbmnn_weight_transpose(const void *w, void *wt, int rows, int taps, int cols
     return LBM_OK;
 }
 
+int lbmnn_weight_transpose_layers(const void *w, void *wt, int n, const int *off, const int *rows, const int *taps,
+                                  const int *cols, const int *flip, void *stream) {
+    if (!w || !wt || n < 0 || !off || !rows || !taps || !cols || !flip)
+        return lbm_fail(LBM_EINVAL, "bad transpose arguments");
+    for (int i = 0; i < n; ++i)
+        if (off[i] < 0 || rows[i] < 1 || taps[i] < 1 || cols[i] < 1 ||
+            (long long)rows[i] * taps[i] >= (1LL << 31) || (long long)rows[i] * taps[i] * cols[i] >= (1LL << 25))
+            return lbm_fail(LBM_EINVAL, "bad shape of layer %d", i);
+    for (int i = 0; i < n; i += nn::WtransLayers::MAX) {
+        nn::WtransLayers L{};
+        L.n = n - i < nn::WtransLayers::MAX ? n - i : nn::WtransLayers::MAX;
+        for (int k = 0; k < L.n; ++k) {
+            L.off[k] = off[i + k];
+            L.rows[k] = rows[i + k];
+            L.taps[k] = taps[i + k];
+            L.cols[k] = cols[i + k];
+            L.flip[k] = flip[i + k];
+        }
+        NN_TRY(nn::wtrans_layers((const uint16_t *)w, (uint16_t *)wt, L, (hipStream_t)stream));
+    }
+    return LBM_OK;
+}
+
 int lbmnn_bias_grad(const void *g, int cstride, int coff, long long pixels, int C, float *db, int accumulate,
                     float *ws, int splits, void *stream) {
     if (!g || !db || !ws || C < 1 || pixels < 1 || splits < 1 || coff + C > cstride)

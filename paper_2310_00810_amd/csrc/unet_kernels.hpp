@@ -66,5 +66,14 @@ hipError_t denormalize(const float *pred, int pcs, const uint8_t *solid, const f
 }  // namespace nn
 
 namespace nn {
+// Up to MAX layers of a weight buffer to transpose in one launch: element
+// offset (the same in both buffers) and shape of each; first (a layer's first
+// block) is filled in.
+struct WtransLayers {
+    static constexpr int MAX = 64;                  // lanes of a wavefront
+    int n;
+    int first[MAX], off[MAX], rows[MAX], taps[MAX], cols[MAX], flip[MAX];
+};
+hipError_t wtrans_layers(const uint16_t *w, uint16_t *wt, WtransLayers L, hipStream_t s);
 hipError_t wtrans(const uint16_t *w, uint16_t *wt, int rows, int taps, int cols, int flip, hipStream_t s);
 }

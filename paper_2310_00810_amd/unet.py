@@ -63,6 +63,11 @@ class UNet:
             self.boff[name] = off
             off += co
         self.n_params = off
+        # (offset, rows, taps, cols, flip) of the layers' transposes, as five int arrays:
+        # conv flips the taps and swaps cin / cout, tconv [sub*co + c][ci] -> [ci][sub*co + c]
+        shapes = [(self.woff[k], self.wshape[k][0], 1 if kind == "tconv" else ks ** dims, ci, int(kind != "tconv"))
+                  for k, (kind, ci, co, ks) in self.layers.items()]
+        self._wt_shapes = [(ctypes.c_int * len(shapes))(*v) for v in zip(*shapes)]
         n8 = (off + 7) // 8 * 8
         dev = self.device
         self.master = torch.zeros(n8, dtype=torch.float32, device=dev)
@@ -290,14 +295,8 @@ class UNet:
 
     # ------------------------------------------------------------- backward --
     def _transpose_weights(self):
-        for name, (kind, ci, co, ks) in self.layers.items():
-            rows, K = self.wshape[name]
-            if kind == "tconv":
-                args = (rows, 1, ci, 0)              # [sub*co + c][ci] -> [ci][sub*co + c]
-            else:
-                args = (co, ks ** self.dims, ci, 1)  # flip taps, swap cin / cout
-            C.check(self.L.lbmnn_weight_transpose(_ptr(self.wbf, self.woff[name]), _ptr(self.wT, self.woff[name]),
-                                                  *args, self._stream()), "lbmnn_weight_transpose")
+        C.check(self.L.lbmnn_weight_transpose_layers(_ptr(self.wbf), _ptr(self.wT), len(self.layers), *self._wt_shapes,
+                                                     self._stream()), "lbmnn_weight_transpose_layers")
 
     def backward(self, g_head):
         """Gradients of <head, g_head> into self.grad (overwritten)."""

@@ -636,3 +636,20 @@ def test_masked_pooling_backward_equals_the_two_passes(dims, Cn, cs, co, acc):
     C.check(L.lbmnn_pool_bwd(*args, b.data_ptr(), *dim), "pool_bwd")
     C.check(L.lbmnn_relu_bwd(b.data_ptr(), x.data_ptr(), cs, co, b.numel() // cs, Cn, stream()), "relu_bwd")
     assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n", [1, 5, 70])
+def test_layer_transposes_in_one_launch(n):
+    C = C_()
+    shapes = [(8 + 8 * (i % 7), (1, 9, 27)[i % 3], 8 + 16 * (i % 5), i % 2) for i in range(n)]
+    off = np.cumsum([0] + [r * t * c + 8 * (i % 2) for i, (r, t, c, _) in enumerate(shapes)])
+    g = torch.Generator(device="cuda").manual_seed(9)
+    w = torch.randn(int(off[-1]), generator=g, device="cuda").to(torch.bfloat16)
+    a = torch.zeros_like(w)
+    b = torch.zeros_like(w)
+    cols = [(ctypes.c_int * n)(*[int(v) for v in col]) for col in (off[:-1], *zip(*shapes))]
+    C.check(C.nnlib().lbmnn_weight_transpose_layers(w.data_ptr(), a.data_ptr(), n, *cols, stream()), "layers")
+    for o, (r, t, c, flip) in zip(off, shapes):
+        v = w[o:o + r * t * c].view(r, t, c)
+        b[o:o + r * t * c] = (v.flip(1) if flip else v).permute(2, 1, 0).reshape(-1)
+    assert torch.equal(a, b)
