@@ -633,6 +633,114 @@ k_conv3x3_rows(ConvArgs a, int per) {
     }
 }
 
+// 1 x 1 convolution (normal and D2S: the head, its input gradient and the
+// transposed convolutions) of few input channels.  Bound by memory; nothing is
+// shared between pixels, so nothing goes through LDS: a wavefront keeps the
+// weights of 32 output channels in registers (KS K steps of 32) and walks over
+// groups of PT x 16 pixels, whose rows of A are MFMA operands as they lie in
+// memory (lane l: pixel l & 15, K entries 8 (l >> 4) ..); the next group's are
+// loaded before this one's MFMAs.  Operands, channel order and stores as in
+// k_conv3x3_rows; products are added in the order of k_conv.  The gw wavefronts
+// of a block that take neighbouring channels read the same pixels.
+//
+// 16 x 256^2 (before, in k_conv's 64 x 32 and 64 x 64 tiles): 32 -> 8 in FP32
+// 18 us, 5.6 TB/s (43 us); 8 -> 32 with its ReLU mask 24 us (47 us); 16 x 128^2
+// 64 -> 4 x 32 D2S 28 us (49 us), 16 x 64^2 128 -> 4 x 64 26 us (29 us).
+template <int KS, int PT>
+__global__ void __launch_bounds__(256) k_conv1x1(ConvArgs a, int gw) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int n0 = ((int)blockIdx.y * gw + wave % gw) * 32;
+    if (n0 >= a.ncols) return;
+    const int walkers = (int)gridDim.x * (4 / gw);
+    const int tiles = (int)((a.M + 16 * PT - 1) / (16 * PT));
+    const int kl = 8 * (lane >> 4), pl = lane & 15;
+    bf16x8 wf[KS][2];
+    bool kv[KS];
+    int ko[KS];                                        // (entries past K: the pixel's first, replaced by zeros)
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        const int k = 32 * s + kl;
+        kv[s] = k < a.K;
+        ko[s] = kv[s] ? k : 0;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int n = n0 + 8 * (pl >> 2) + 4 * j + (pl & 3);
+            wf[s][j] = as_bf16x8(kv[s] && n < a.ncols ? *(const uint4 *)(a.wt + (long long)n * a.K + k) : make_uint4(0, 0, 0, 0));
+        }
+    }
+    const int c = n0 + kl;                             // the lane's output channels
+    const bool d2s = (a.flags & FLAG_D2S) != 0, cv = c < a.ncols;
+    const int cr = d2s ? a.ncols >> a.dims : a.ncols, bc = d2s ? c - c / cr * cr : c;
+    float bias[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (a.bias && cv)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) bias[k] = a.bias[bc + k];
+    auto load = [&](int t, uint4 (&v)[PT][KS]) {
+#pragma unroll
+        for (int p = 0; p < PT; ++p) {
+            const long long m = (long long)(t * PT + p) * 16 + pl;
+            const uint16_t *src = a.in + (m < a.M ? m : 0) * a.in_cs + a.in_co;
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                const uint4 x = *(const uint4 *)(src + ko[s]);
+                v[p][s] = kv[s] ? x : make_uint4(0, 0, 0, 0);
+            }
+        }
+    };
+    int t = (int)blockIdx.x * (4 / gw) + wave / gw;
+    uint4 cur[PT][KS], nxt[PT][KS];
+    if (t < tiles) load(t, cur);
+    for (; t < tiles; t += walkers) {
+        if (t + walkers < tiles) load(t + walkers, nxt);
+#pragma unroll
+        for (int p = 0; p < PT; ++p) {
+            f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[s][j], as_bf16x8(cur[p][s]), acc[j], 0, 0, 0);
+            const long long m = (long long)(t * PT + p) * 16 + pl;
+            if (m < a.M && cv) {
+                int b;
+                const long long o = out_index(a, m, c, b);
+                float v[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    v[k] = acc[k >> 2][k & 3] + bias[k];
+                    if (a.flags & FLAG_RELU) v[k] = v[k] > 0.f ? v[k] : 0.f;
+                }
+                if (a.out32) {
+                    float4 *dst = (float4 *)(a.out32 + o);
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        float4 x = make_float4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
+                        if (a.flags & FLAG_ACC) {
+                            const float4 old = dst[k];
+                            x = make_float4(old.x + x.x, old.y + x.y, old.z + x.z, old.w + x.w);
+                        }
+                        dst[k] = x;
+                    }
+                } else {
+                    uint16_t *dst = a.out + o;
+                    if (a.flags & FLAG_ACC) {
+                        float old[8];
+                        unpack8(*(const uint4 *)dst, old);
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) v[k] += old[k];
+                    }
+                    if (a.mask) relu_mask(v, *(const uint4 *)(a.mask + m * a.mask_cs + a.mask_co + c));
+                    *(uint4 *)dst = pack8(v);
+                }
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < PT; ++p)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) cur[p][s] = nxt[p][s];
+    }
+}
+
 // Weight gradient: dW[r][k] = sum_m G[m][r] * im2col(in)[m][k], G = dout
 // (S2D: r = sub * Cr + co read at the fine pixel).  blockIdx.z splits the
 // pixel range; partials are summed by k_sum_splits.  The contraction runs
@@ -1609,6 +1717,25 @@ hipError_t conv(const ConvArgs &a, hipStream_t s) {
         }
 #undef CALL
 #undef LAUNCH
+        return hipGetLastError();
+    }
+    const uintptr_t ob = a.out32 ? (uintptr_t)a.out32 : (uintptr_t)a.out;
+    // From 256 input channels on (K steps of a wavefront's weights: 64 registers) too few pixel groups are in
+    // flight: 16 x 32^2, 256 -> 4 x 128 33 us against 20 us in k_conv; S2D at K = 128 gains nothing (33 us both).
+    if (a.ks == 1 && a.K <= 128 && !(a.flags & FLAG_S2D) && ((a.out_cs | a.out_co) & 7) == 0 && (ob & 15) == 0) {
+        const int steps = (a.K + 31) / 32, groups = (a.ncols + 31) / 32, gw = groups >= 3 ? 4 : groups;
+        const int gy = (groups + gw - 1) / gw, pt = steps <= 1 ? 4 : 2;
+        const long long want = (a.M + 16 * pt * (4 / gw) - 1) / (16 * pt * (4 / gw));
+        // as many blocks as are resident together (5, 4 or 3 per CU), in multiples of 8 along x, so that the blocks
+        // of a pixel group fall on one XCD (twice as many: 30 instead of 28 us at 64 -> 4 x 32)
+        long long gx = (256 * (steps <= 1 ? 5 : steps <= 2 ? 4 : 3) / gy + 7) / 8 * 8;
+        if (gx > want) gx = want;
+        const dim3 grid((unsigned)gx, (unsigned)gy);
+#define CALL(KS, PT) hipLaunchKernelGGL((k_conv1x1<KS, PT>), grid, dim3(256), 0, s, a, gw)
+        if (steps <= 1) CALL(1, 4);
+        else if (steps <= 2) CALL(2, 2);
+        else CALL(4, 2);
+#undef CALL
         return hipGetLastError();
     }
     if (a.ncols <= 32) {

@@ -653,3 +653,34 @@ def test_layer_transposes_in_one_launch(n):
         v = w[o:o + r * t * c].view(r, t, c)
         b[o:o + r * t * c] = (v.flip(1) if flip else v).permute(2, 1, 0).reshape(-1)
     assert torch.equal(a, b)
+
+
+# edges of the 1 x 1 kernel: one, two, three and four K steps with a part step, 8 channels past a group of 32,
+# five groups (two per block row), pixels that fill no group, both output types, D2S, channel slices
+ONE = [(2, (1, 1, 5, 7), 8, 8, 0), (2, (3, 1, 37, 41), 32, 40, 0), (2, (2, 1, 70, 90), 72, 152, 0),
+       (3, (1, 3, 9, 11), 120, 64, 8), (2, (1, 1, 33, 20), 64, 96, 8)]
+
+
+@pytest.mark.parametrize("dims,grid,cin,cout,flags", ONE)
+@pytest.mark.parametrize("out32,extra", [(True, 0), (False, 1), (False, 2), (True, 2)])
+def test_one_by_one_kernel_edges(dims, grid, cin, cout, flags, out32, extra):
+    rng = np.random.default_rng(17)
+    x = bf(rng.standard_normal(grid + (cin + 8,)))
+    W = bf(rng.standard_normal((cout, cin)) / np.sqrt(cin))
+    n, d, h, w = grid
+    cr = cout >> dims if flags else cout
+    b = rng.standard_normal(cr).astype(np.float32)
+    z = x[..., 8:] @ W.T
+    if flags:                            # column sub * cr + co to the fine pixel
+        f = 2 if dims == 3 else 1
+        z = z.reshape(n, d, h, w, f, 2, 2, cr).transpose(0, 1, 4, 2, 5, 3, 6, 7).reshape(n, d * f, 2 * h, 2 * w, cr)
+    z = z + b
+    old = bf(rng.standard_normal(z.shape[:-1] + (cr + 8,)))
+    exp = np.maximum(z, 0) if extra == 1 else old[..., 8:] + z if extra == 2 else z
+    out = torch.from_numpy(old).float().cuda() if out32 else dev_bf(old)
+    conv_call(dev_bf(x), dev_bf(W), torch.from_numpy(b).cuda(), 1, dims, cout, flags=flags | extra, out32=out32,
+              cin=cin, in_co=8, out=out, out_co=8)
+    got = out.double().cpu().numpy()
+    assert np.array_equal(got[..., :8], old[..., :8])
+    # FP32 accumulation of at most 120 products; BF16 outputs add one rounding
+    assert np.all(np.abs(got[..., 8:] - exp) <= (0 if out32 else 2 ** -7) * np.abs(exp) + 1e-5)
