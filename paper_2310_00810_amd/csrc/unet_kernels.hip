@@ -387,6 +387,148 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a, float *__restrict__ pa
         }
 }
 
+// Loads through a buffer resource: an offset past its range reads 0, which
+// stands for the zero padding.
+constexpr unsigned OOB = 0xFFFFFF00u;
+__device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const uint16_t *p, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)p, (short)0, (int)bytes, 0x00020000);
+}
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+__device__ inline uint4 bload16(__amdgpu_buffer_rsrc_t r, unsigned off) {
+    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+// The same GEMM for small layers (one image, the deep levels), which are bound
+// by latency: a wavefront takes 32 pixels x 32 output channels over the K range
+// of one split and loads its MFMA operands straight from memory (lane l: pixel
+// or channel l & 15, K entries 8 (l >> 4) ..; rows of weights permuted as in
+// k_conv3x3_rows), DS K steps of 32 ahead; the S wavefronts of a tile add their
+// sums in LDS in split order.  Products and splits are added in the order of
+// k_conv<SPLIT> and k_conv_reduce, in one launch and without partials in
+// memory.  S = 1: the block's four wavefronts take four tiles.
+// cin % 32 == 0: a step lies in one tap, whose place is scalar arithmetic; the
+// input and the weights are addressed by 31-bit offsets (host-checked).
+__global__ void __launch_bounds__(1024) k_conv_direct(ConvArgs a, int S, int sper, unsigned in_bytes) {
+    constexpr int DS = 4;                              // (6 spill)
+    extern __shared__ float sums[];                    // [split][pixel tile][2][lane][4]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int tiles_n = (a.ncols + 31) / 32;
+    const int nb = (int)gridDim.x, q8 = nb >> 3, r8 = nb & 7, xcd = (int)blockIdx.x & 7;
+    const int bt = xcd * q8 + (xcd < r8 ? xcd : r8) + ((int)blockIdx.x >> 3);
+    const int tile = S == 1 ? bt * 4 + wave : bt, z = S == 1 ? 0 : wave;
+    const int n0 = tile % tiles_n * 32, kl = 8 * (lane >> 4), pl = lane & 15;
+    const long long m0 = (long long)(tile / tiles_n) * 32;
+    const __amdgpu_buffer_rsrc_t ri = rsrc_of(a.in, in_bytes), rw = rsrc_of(a.wt, (unsigned)a.ncols * a.K * 2u);
+    constexpr unsigned OUT = 0x80000000u;              // past both ranges, also with a channel offset added
+    int k = z * sper * 64, tap = k / a.cin, ci = k - tap * a.cin;        // the step to load
+    const int steps = (min(a.K, (z + 1) * sper * 64) - k) / 32;
+    Row row[2];
+    unsigned io[2], wo[2];                             // byte offsets: the tap's pixel or OUT; the weight row or OUT
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        row[i] = row_of(a, m0 + 16 * i + pl);
+        const int n = n0 + 8 * (pl >> 2) + 4 * i + (pl & 3);
+        wo[i] = n < a.ncols ? 2u * (unsigned)(n * a.K + kl) : OUT;
+    }
+    auto place = [&] {
+        int dx = 0, dy = 0, dz = 0;
+        if (a.ks == 3) {
+            dz = a.dims == 3 ? tap / 9 - 1 : 0;
+            const int t9 = a.dims == 3 ? tap % 9 : tap;
+            dy = t9 / 3 - 1;
+            dx = t9 % 3 - 1;
+        }
+        const int delta = ((dz * a.h + dy) * a.w + dx) * a.in_cs + kl;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const bool ok = row[i].valid && (unsigned)(row[i].x + dx) < (unsigned)a.w &&
+                            (unsigned)(row[i].y + dy) < (unsigned)a.h && (unsigned)(row[i].z + dz) < (unsigned)a.d;
+            io[i] = ok ? 2u * (unsigned)((int)row[i].base + delta) : OUT;
+        }
+    };
+    uint4 vi[DS][2], vw[DS][2];
+    auto fetch = [&](int d) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            vi[d][i] = bload16(ri, io[i] + 2u * (unsigned)ci);
+            vw[d][i] = bload16(rw, wo[i] + 2u * (unsigned)k);
+        }
+        k += 32;
+        ci += 32;
+        if (ci == a.cin) {
+            ci = 0;
+            ++tap;
+            place();
+        }
+    };
+    place();
+#pragma unroll
+    for (int d = 0; d < DS; ++d)
+        if (d < steps) fetch(d);
+    f32x4 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < steps; s += DS)
+#pragma unroll
+        for (int d = 0; d < DS; ++d) {
+            if (s + d >= steps) break;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vw[d][j]), as_bf16x8(vi[d][i]), acc[i][j], 0, 0, 0);
+            if (s + d + DS < steps) fetch(d);
+        }
+    int i0 = 0, i1 = 2;
+    if (S > 1) {
+        f32x4 *dst = (f32x4 *)sums;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) dst[((z * 2 + i) * 2 + j) * 64 + lane] = acc[i][j];
+        __syncthreads();
+        if (wave >= 2) return;
+        f32x4 v[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+        for (int p = 0; p < S; ++p)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) v[j] += dst[((p * 2 + wave) * 2 + j) * 64 + lane];
+        i0 = wave;
+        i1 = wave + 1;
+        acc[0][0] = acc[1][0] = v[0];
+        acc[0][1] = acc[1][1] = v[1];
+    }
+    const int c = n0 + kl;                             // the lane's 8 output channels
+    if (c >= a.ncols) return;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const long long m = m0 + 16 * i + pl;
+        if (i < i0 || i >= i1 || m >= a.M) continue;
+        int bc;
+        const long long o = out_index(a, m, c, bc);
+        float v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            v[q] = acc[i][q >> 2][q & 3] + (a.bias ? a.bias[bc + q] : 0.f);
+            if (a.flags & FLAG_RELU) v[q] = v[q] > 0.f ? v[q] : 0.f;
+        }
+        if (a.out32) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) a.out32[o + q] = (a.flags & FLAG_ACC) ? a.out32[o + q] + v[q] : v[q];
+            continue;
+        }
+        uint16_t *dst = a.out + o;
+        if (a.flags & FLAG_ACC) {
+            float old[8];
+            unpack8(*(const uint4 *)dst, old);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] += old[q];
+        }
+        if (a.mask) relu_mask(v, *(const uint4 *)(a.mask + m * a.mask_cs + a.mask_co + c));
+        *(uint4 *)dst = pack8(v);
+    }
+}
+
 // 3 x 3 (3 x 3 x 3) convolution on image rows (the plane sizes must be
 // multiples of 8 x 32 pixels; input channels in chunks of 32, a last, shorter
 // chunk zero-filled).  Per chunk a block's input patch of 8 x 32 pixels with
@@ -418,18 +560,7 @@ constexpr int HC = 32;                               // chunk channels
 // every bank twice: 8.8 instead of 4.4 cycles a read).
 __device__ inline int granule(int r, int g) { return g ^ ((r >> 1) & 2); }
 
-// Loads through a buffer resource: an offset past its range reads 0, which
-// stands for the zero padding.
-constexpr unsigned OOB = 0xFFFFFF00u;
-__device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const uint16_t *p, unsigned bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc((void *)p, (short)0, (int)bytes, 0x00020000);
-}
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-__device__ inline uint4 bload16(__amdgpu_buffer_rsrc_t r, unsigned off) {
-    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
-// The same load straight to LDS: lane l of the wavefront fills the 16 bytes at
+// bload16 straight to LDS: lane l of the wavefront fills the 16 bytes at
 // dst + 16 l (dst uniform).  Complete after lds_wait() and a barrier.
 __device__ inline void bload16_lds(__amdgpu_buffer_rsrc_t r, uint16_t *dst, unsigned off) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)dst, 16, off, 0, 0, 0);
@@ -1672,8 +1803,32 @@ int conv_splits(const ConvArgs &a) {
     return (steps + sper - 1) / sper;
 }
 
+// The direct kernel's conditions; its splits are the wavefronts of a block.
+// It reads every operand from the caches for each 32 x 32 tile, so it pays while
+// launches and latency dominate, up to about 1.3e9 multiply-adds with splits
+// (us, direct against partials and k_conv_reduce: 128^2, 64 -> 64 and 32^2, 256
+// -> 256 11 : 16, 128^2, 128 -> 64 19 : 22, 64^2, 256 -> 128 19 : 21, 16^3, 128
+// -> 128 26 : 23, four images of 32^2, 256 -> 256 35 : 24) and half as many
+// without (256^2, 32 -> 32 8.5 : 9.7, 64 -> 32 20 : 14; 1 x 1 32^2, 256 -> 512
+// 7.3 : 6.9).
+static bool direct_ok(const ConvArgs &a, int S, unsigned *in_bytes) {
+    const uintptr_t ob = a.out32 ? (uintptr_t)a.out32 : (uintptr_t)a.out;
+    const long long bytes = 2 * a.M * a.in_cs;
+    *in_bytes = (unsigned)bytes;
+    return S <= 16 && a.M * a.ncols <= (S > 1 ? 5LL << 28 : 5LL << 27) / a.K && a.cin % 32 == 0 && !(a.flags & FLAG_S2D) && bytes < (1LL << 31) && 2LL * a.ncols * a.K < (1LL << 31) && ((a.out_cs | a.out_co) & 7) == 0 &&
+           (ob & 15) == 0;
+}
+static hipError_t conv_direct(const ConvArgs &a, int S, int sper, unsigned in_bytes, hipStream_t s) {
+    const long long tiles = (long long)blocks(a.M, 32) * ((a.ncols + 31) / 32);
+    hipLaunchKernelGGL(k_conv_direct, dim3((unsigned)(S == 1 ? (tiles + 3) / 4 : tiles)), dim3(64 * (S == 1 ? 4 : S)),
+                       S == 1 ? 0 : 4096 * S, s, a, S, sper, in_bytes);
+    return hipGetLastError();
+}
+
 hipError_t conv_split(const ConvArgs &a, float *part, int S, hipStream_t s) {
     const int steps = (a.K + 63) / 64, sper = (steps + S - 1) / S;
+    unsigned in_bytes;
+    if (direct_ok(a, S, &in_bytes)) return conv_direct(a, S, sper, in_bytes, s);
     if (a.ncols <= 32) {
         dim3 grid(blocks(a.M, 64), (unsigned)((a.ncols + 31) / 32), (unsigned)S);
         hipLaunchKernelGGL((k_conv<64, 32, true>), grid, dim3(256), 0, s, a, part, sper);
@@ -1738,6 +1893,9 @@ hipError_t conv(const ConvArgs &a, hipStream_t s) {
 #undef CALL
         return hipGetLastError();
     }
+    unsigned in_bytes;
+    if (a.ks == 3 && direct_ok(a, 1, &in_bytes))
+        return conv_direct(a, 1, (a.K + 63) / 64, in_bytes, s);
     if (a.ncols <= 32) {
         dim3 grid(blocks(a.M, 64), (unsigned)((a.ncols + 31) / 32));
         hipLaunchKernelGGL((k_conv<64, 32>), grid, dim3(256), 0, s, a);

@@ -684,3 +684,35 @@ def test_one_by_one_kernel_edges(dims, grid, cin, cout, flags, out32, extra):
     assert np.array_equal(got[..., :8], old[..., :8])
     # FP32 accumulation of at most 120 products; BF16 outputs add one rounding
     assert np.all(np.abs(got[..., 8:] - exp) <= (0 if out32 else 2 ** -7) * np.abs(exp) + 1e-5)
+
+
+# edges of the direct kernel: splits that end inside a tap, 3, 13 and (beyond it) 18 splits, 8 channels past
+# a tile of 32, ragged pixel tiles, part loads of the last steps, no split with a last block of fewer tiles
+DIRECT = [(2, 3, (1, 1, 9, 11), 96, 40), (2, 3, (1, 1, 5, 5), 448, 64), (2, 3, (1, 1, 5, 5), 512, 64),
+          (3, 3, (1, 3, 5, 7), 32, 72), (2, 3, (1, 1, 190, 190), 32, 8), (2, 1, (2, 1, 6, 7), 544, 40)]
+
+
+@pytest.mark.parametrize("dims,ks,grid,cin,cout", DIRECT)
+def test_direct_kernel_edges(dims, ks, grid, cin, cout):
+    rng = np.random.default_rng(18)
+    C = C_()
+    L = C.nnlib()
+    x = bf(rng.standard_normal(grid + (cin + 8,)))
+    W = bf(rng.standard_normal((cout, ks ** dims, cin)) / np.sqrt(cin * ks ** dims))
+    b = rng.standard_normal(cout).astype(np.float32)
+    old = bf(rng.standard_normal(grid + (cout + 16,)))
+    ref = N.conv_fwd(x[..., 8:], W, b.astype(np.float64), ks, dims)
+    xd, wd, bd = dev_bf(x), dev_bf(W.reshape(cout, -1)), torch.from_numpy(b).cuda()
+    for flags in (C.NN_RELU, C.NN_ACCUMULATE):
+        exp = np.maximum(ref, 0) if flags == C.NN_RELU else old[..., 8:8 + cout] + ref
+        for out32 in (True, False):
+            out = torch.from_numpy(old).float().cuda() if out32 else dev_bf(old)
+            desc = C.lbmnn_conv_desc(*grid, dims, ks, cin, cout, flags, xd.data_ptr(), cin + 8, 8,
+                                     None if out32 else out.data_ptr(), out.data_ptr() if out32 else None, cout + 16, 8)
+            need = L.lbmnn_conv_workspace_bytes(ctypes.byref(desc))
+            ws = torch.empty(need // 4 + 1, dtype=torch.float32, device="cuda")
+            C.check(L.lbmnn_conv_ws(ctypes.byref(desc), wd.data_ptr(), bd.data_ptr(), ws.data_ptr(), need, stream()), "conv")
+            got = out.double().cpu().numpy()
+            assert np.array_equal(got[..., :8], old[..., :8]) and np.array_equal(got[..., 8 + cout:], old[..., 8 + cout:])
+            # FP32 accumulation of up to 4,608 products of unit-variance sums; BF16 outputs add one rounding
+            assert np.all(np.abs(got[..., 8:8 + cout] - exp) <= (0 if out32 else 2 ** -7) * np.abs(exp) + 2e-5)
