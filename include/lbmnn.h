@@ -161,6 +161,24 @@ int lbmnn_pool_bwd_relu(const void *in, int in_cstride, int in_coff, const void 
                         void *gin, int gi_cstride, int gi_coff, int n, int d, int h, int w, int C, int dims,
                         int accumulate, void *stream);
 
+/* A sequence of convolutions (lbmnn_conv_ws) and max poolings (pool = 1:
+ * lbmnn_pool_fwd of c.cin channels to the grid of c) in one call: a network's
+ * forward pass without a host call per layer.  Layer i reads bufs[in] and
+ * writes bufs[out] (FP32 with f32 = 1) with the shape, strides, offsets and
+ * flags of c, whose pointers are ignored; its weights start at element w_off
+ * of w (BF16), its bias at bias[b_off] (b_off < 0 or bias NULL: none).  ws:
+ * lbmnn_forward_workspace_bytes() bytes.  Errors as the calls it stands for,
+ * LBM_EINVAL for an index out of range; layers before the failing one have run. */
+typedef struct {
+    lbmnn_conv_desc c;
+    long long w_off, b_off;
+    int in, out;
+    int pool, f32;
+} lbmnn_layer;
+size_t lbmnn_forward_workspace_bytes(const lbmnn_layer *layers, int n);
+int lbmnn_forward(const lbmnn_layer *layers, int n, void *const *bufs, int n_bufs, const void *w, const float *bias,
+                  float *ws, size_t ws_bytes, void *stream);
+
 /* Masked MSE: loss = scale * sum_m wpix[m] sum_{c < creal} (pred[m][c] - tgt[m][c])^2
  * with pred FP32 at channel stride pcs and tgt FP32 [m][creal]; writes the
  * BF16 gradient dpred [m][pcs] (zero beyond creal) and the loss (FP64) to

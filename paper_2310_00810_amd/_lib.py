@@ -114,7 +114,7 @@ NN_EXPORTS = [
     "lbmnn_wgrad_workspace_bytes", "lbmnn_conv_wgrad", "lbmnn_conv_wgrad_bias", "lbmnn_conv_wgrad_noalloc",
     "lbmnn_weight_transpose", "lbmnn_weight_transpose_layers",
     "lbmnn_bias_grad", "lbmnn_relu_bwd", "lbmnn_relu_bwd_bias_grad", "lbmnn_pool_fwd", "lbmnn_pool_bwd",
-    "lbmnn_pool_bwd_relu",
+    "lbmnn_pool_bwd_relu", "lbmnn_forward", "lbmnn_forward_workspace_bytes",
     "lbmnn_mse", "lbmnn_adam", "lbmnn_to_bf16", "lbmnn_features", "lbmnn_normalize", "lbmnn_denormalize",
     "lbmnn_flux_balance_workspace_bytes", "lbmnn_flux_balance",
 ]
@@ -130,7 +130,13 @@ class lbmnn_conv_desc(ctypes.Structure):
                 ("out_cstride", ctypes.c_int), ("out_coff", ctypes.c_int)]
 
 
+class lbmnn_layer(ctypes.Structure):
+    _fields_ = [("c", lbmnn_conv_desc), ("w_off", ctypes.c_longlong), ("b_off", ctypes.c_longlong),
+                ("in_", ctypes.c_int), ("out", ctypes.c_int), ("pool", ctypes.c_int), ("f32", ctypes.c_int)]
+
+
 _nn_ready = False
+
 
 
 def nnlib():
@@ -158,6 +164,9 @@ def nnlib():
         L.lbmnn_pool_fwd.argtypes = [vp, ip, ip, vp, ip, ip, ip, ip, ip, ip, ip, ip, vp]
         L.lbmnn_pool_bwd.argtypes = [vp, ip, ip, vp, ip, ip, vp, ip, ip, ip, ip, ip, ip, ip, ip, ip, vp]
         L.lbmnn_pool_bwd_relu.argtypes = L.lbmnn_pool_bwd.argtypes
+        L.lbmnn_forward_workspace_bytes.argtypes = [ctypes.POINTER(lbmnn_layer), ip]
+        L.lbmnn_forward_workspace_bytes.restype = ctypes.c_size_t
+        L.lbmnn_forward.argtypes = [ctypes.POINTER(lbmnn_layer), ip, vp, ip, vp, vp, vp, ctypes.c_size_t, vp]
         L.lbmnn_mse.argtypes = [vp, ip, vp, vp, ip, ll, fl, vp, vp, vp, vp]
         L.lbmnn_adam.argtypes = [vp, vp, vp, vp, vp, ll, fl, fl, fl, fl, ip, vp]
         L.lbmnn_to_bf16.argtypes = [vp, vp, ll, vp]
@@ -168,7 +177,7 @@ def nnlib():
         L.lbmnn_flux_balance_workspace_bytes.restype = ll
         L.lbmnn_flux_balance.argtypes = [vp, ip, ip, ip, ip, ip, vp, vp, ll, vp]
         for n in NN_EXPORTS:
-            if n not in ("lbmnn_wgrad_workspace_bytes", "lbmnn_conv_workspace_bytes"):
+            if not n.endswith("_workspace_bytes"):
                 getattr(L, n).restype = ctypes.c_int
         _nn_ready = True
     return L

@@ -320,6 +320,41 @@ int lbmnn_pool_bwd_relu(const void *in, int in_cstride, int in_coff, const void 
                     accumulate, 1, stream);
 }
 
+size_t lbmnn_forward_workspace_bytes(const lbmnn_layer *layers, int n) {
+    size_t need = 0;
+    for (int i = 0; layers && i < n; ++i) {
+        if (layers[i].pool) continue;
+        lbmnn_conv_desc c = layers[i].c;
+        alignas(16) static char stand_in[16];           // the desc is validated with its pointers
+        c.in = stand_in;
+        c.out = layers[i].f32 ? nullptr : stand_in;
+        c.out_f32 = layers[i].f32 ? (float *)stand_in : nullptr;
+        const size_t b = lbmnn_conv_workspace_bytes(&c);
+        need = b > need ? b : need;
+    }
+    return need;
+}
+
+int lbmnn_forward(const lbmnn_layer *layers, int n, void *const *bufs, int n_bufs, const void *w, const float *bias,
+                  float *ws, size_t ws_bytes, void *stream) {
+    if (n < 0 || n_bufs < 0 || (n && (!layers || !bufs || !w))) return lbm_fail(LBM_EINVAL, "bad forward arguments");
+    for (int i = 0; i < n; ++i) {
+        const lbmnn_layer &l = layers[i];
+        if (l.in < 0 || l.in >= n_bufs || l.out < 0 || l.out >= n_bufs || l.w_off < 0)
+            return lbm_fail(LBM_EINVAL, "layer %d: buffer index or weight offset out of range", i);
+        lbmnn_conv_desc c = l.c;
+        c.in = bufs[l.in];
+        c.out = l.f32 ? nullptr : bufs[l.out];
+        c.out_f32 = l.f32 ? (float *)bufs[l.out] : nullptr;
+        const int rc = l.pool ? lbmnn_pool_fwd(c.in, c.in_cstride, c.in_coff, c.out, c.out_cstride, c.out_coff, c.n, c.d,
+                                               c.h, c.w, c.cin, c.dims, stream)
+                              : lbmnn_conv_ws(&c, (const uint16_t *)w + l.w_off, bias && l.b_off >= 0 ? bias + l.b_off : nullptr,
+                                              ws, ws_bytes, stream);
+        if (rc) return rc;
+    }
+    return LBM_OK;
+}
+
 int lbmnn_mse(const float *pred, int pcs, const float *tgt, const float *wpix, int creal, long long pixels,
               float scale, void *dpred, double *part, double *loss, void *stream) {
     if (!pred || !tgt || !dpred || !part || !loss || creal < 1 || creal > pcs || pixels < 1)

@@ -77,7 +77,7 @@ class UNet:
         self.wbf = torch.zeros(n8, dtype=BF16, device=dev)
         self.wT = torch.zeros(n8, dtype=BF16, device=dev)
         self.t = 0
-        self._bufs = {}
+        self._bufs, self._plans = {}, {}
         self._ws = torch.empty(0, dtype=torch.float32, device=dev)
         self._mse_part = torch.empty(0, dtype=torch.float64, device=dev)
         self.loss_dev = torch.zeros(1, dtype=torch.float64, device=dev)
@@ -206,34 +206,28 @@ class UNet:
         return B
 
     # ---------------------------------------------------------- primitives --
-    def _conv(self, grid, ks, cin, cout, flags, inp, in_cs, in_co, name, out=None, out_cs=0, out_co=0,
-              out32=None, transposed=False, use_bias=True, relu_of=None):
-        # relu_of = (y, channel stride, offset): the output is masked by the ReLU that produced y
+    def _dgrad(self, grid, ks, cin, cout, flags, inp, in_cs, in_co, name, out, out_cs, relu_of=None):
+        # input gradient of layer `name`: the convolution with its transposed weights;
+        # relu_of = (y, channel stride, offset): masked by the ReLU that produced y
         n, d, h, w = grid
-        wsrc = self.wT if transposed else self.wbf
         desc = C.lbmnn_conv_desc(n, d, h, w, self.dims, ks, cin, cout, flags, inp.data_ptr(), in_cs, in_co,
-                                 out.data_ptr() if out is not None else None,
-                                 out32.data_ptr() if out32 is not None else None, out_cs, out_co)
-        b = _ptr(self.master, self.boff[name]) if use_bias else None
+                                 out.data_ptr(), None, out_cs, 0)
         taps = (1 << self.dims) if flags & C.NN_S2D else ks ** self.dims
         M = n * d * h * w
         m_in = M << self.dims if flags & C.NN_S2D else M
-        nbytes = (2 * m_in * cin + (4 if out32 is not None else 2) * M * cout + 2 * cout * taps * cin +
-                  (2 * M * cout if relu_of else 0))
+        nbytes = 2 * m_in * cin + 2 * M * cout + 2 * cout * taps * cin + (2 * M * cout if relu_of else 0)
         # the deep levels split their K loop: FP32 partials in the shared workspace
         need = self.L.lbmnn_conv_workspace_bytes(ctypes.byref(desc))
         if self._ws.numel() * 4 < need:
             self._ws = torch.empty(need // 4 + 1024, dtype=torch.float32, device=self.device)
+        wsrc, ws = _ptr(self.wT, self.woff[name]), (_ptr(self._ws), self._ws.numel() * 4, self._stream())
         if relu_of:
             y, y_cs, y_co = relu_of
-            run = lambda: C.check(self.L.lbmnn_conv_relu_bwd(ctypes.byref(desc), _ptr(wsrc, self.woff[name]), _ptr(y),
-                                                             y_cs, y_co, _ptr(self._ws), self._ws.numel() * 4,
-                                                             self._stream()), "lbmnn_conv_relu_bwd")
+            run = lambda: C.check(self.L.lbmnn_conv_relu_bwd(ctypes.byref(desc), wsrc, _ptr(y), y_cs, y_co, *ws),
+                                  "lbmnn_conv_relu_bwd")
         else:
-            run = lambda: C.check(self.L.lbmnn_conv_ws(ctypes.byref(desc), _ptr(wsrc, self.woff[name]), b,
-                                                       _ptr(self._ws), self._ws.numel() * 4, self._stream()),
-                                  "lbmnn_conv_ws")
-        self._timed("dgrad" if transposed else "fwd", name, 2 * M * cout * taps * cin, nbytes, run)
+            run = lambda: C.check(self.L.lbmnn_conv_ws(ctypes.byref(desc), wsrc, None, *ws), "lbmnn_conv_ws")
+        self._timed("dgrad", name, 2 * M * cout * taps * cin, nbytes, run)
 
     def _wgrad(self, grid, ks, cin, flags, inp, in_cs, in_co, g, g_cs, g_co, rows, name):
         # weight and bias gradient of the layer
@@ -260,37 +254,79 @@ class UNet:
                                     "lbmnn_conv_wgrad_bias"))
 
     # -------------------------------------------------------------- forward --
+    def _forward_plan(self, shape):
+        """The forward pass on inputs of this shape as one native call's layer
+        list (built once per shape): shapes, offsets and buffer indices only;
+        the pointers are handed over with each call.  -> (layer array, layer
+        names, buffer names after the input, workspace bytes)."""
+        plan = self._plans.get(shape)
+        if plan is not None:
+            return plan
+        layers, names, bufs = [], [], []
+        R = C.NN_RELU
+
+        def index(buf):
+            if buf is None:
+                return 0
+            if buf not in bufs:
+                bufs.append(buf)
+            return 1 + bufs.index(buf)
+
+        def add(name, grid, ks, cin, cout, flags, inp, in_cs, in_co, out, out_cs, out_co=0, pool=0):
+            desc = C.lbmnn_conv_desc(*grid, self.dims, ks, cin, cout, flags, None, in_cs, in_co, None, None, out_cs,
+                                     out_co)
+            layers.append(C.lbmnn_layer(desc, 0 if pool else self.woff[name], -1 if pool else self.boff[name],
+                                        index(inp), index(out), pool, int(out == "head")))
+            names.append(name)
+
+        h, h_cs, Ch = None, self.cin, self.cin
+        for lv in range(self.levels):
+            Cl = self.base << lv
+            g = self._grid(shape, lv)
+            add(f"e{lv}c0", g, 3, Ch, Cl, R, h, h_cs, 0, f"e{lv}c0", Cl)
+            if lv < self.levels - 1:
+                add(f"e{lv}c1", g, 3, Cl, Cl, R, f"e{lv}c0", Cl, 0, f"cat{lv}", 2 * Cl, Cl)
+                add(f"p{lv}", self._grid(shape, lv + 1), 1, Cl, Cl, 0, f"cat{lv}", 2 * Cl, Cl, f"p{lv}", Cl, pool=1)
+                h, h_cs, Ch = f"p{lv}", Cl, Cl
+            else:
+                add(f"e{lv}c1", g, 3, Cl, Cl, R, f"e{lv}c0", Cl, 0, "bott", Cl)
+                h, h_cs, Ch = "bott", Cl, Cl
+        for lv in range(self.levels - 2, -1, -1):
+            Cl = self.base << lv
+            gc, g = self._grid(shape, lv + 1), self._grid(shape, lv)
+            add(f"d{lv}t", gc, 1, 2 * Cl, Cl << self.dims, C.NN_D2S, h, h_cs, 0, f"cat{lv}", 2 * Cl)
+            add(f"d{lv}c0", g, 3, 2 * Cl, Cl, R, f"cat{lv}", 2 * Cl, 0, f"d{lv}c0", Cl)
+            add(f"d{lv}c1", g, 3, Cl, Cl, R, f"d{lv}c0", Cl, 0, f"d{lv}c1", Cl)
+            h, h_cs, Ch = f"d{lv}c1", Cl, Cl
+        add("head", self._grid(shape, 0), 1, self.base, self.cout, 0, h, h_cs, 0, "head", self.cout)
+        arr = (C.lbmnn_layer * len(layers))(*layers)
+        plan = (arr, names, bufs, self.L.lbmnn_forward_workspace_bytes(arr, len(layers)))
+        self._plans[shape] = plan
+        return plan
+
     def forward(self, x):
         """x: BF16 (n, d, h, w, cin) -> FP32 head output (n, d, h, w, cout)."""
         shape = tuple(x.shape[:4])
         B = self.buffers(shape)
         self._x = x
-        R = C.NN_RELU
-        h, h_cs, h_co, Ch = x, self.cin, 0, self.cin
-        for lv in range(self.levels):
-            Cl = self.base << lv
-            g = self._grid(shape, lv)
-            self._conv(g, 3, Ch, Cl, R, h, h_cs, h_co, f"e{lv}c0", out=B[f"e{lv}c0"], out_cs=Cl)
-            if lv < self.levels - 1:
-                self._conv(g, 3, Cl, Cl, R, B[f"e{lv}c0"], Cl, 0, f"e{lv}c1", out=B[f"cat{lv}"],
-                           out_cs=2 * Cl, out_co=Cl)
-                gc = self._grid(shape, lv + 1)
-                C.check(self.L.lbmnn_pool_fwd(_ptr(B[f"cat{lv}"]), 2 * Cl, Cl, _ptr(B[f"p{lv}"]), Cl, 0, *gc, Cl,
-                                              self.dims, self._stream()), "lbmnn_pool_fwd")
-                h, h_cs, h_co, Ch = B[f"p{lv}"], Cl, 0, Cl
-            else:
-                self._conv(g, 3, Cl, Cl, R, B[f"e{lv}c0"], Cl, 0, f"e{lv}c1", out=B["bott"], out_cs=Cl)
-                h, h_cs, h_co, Ch = B["bott"], Cl, 0, Cl
-        for lv in range(self.levels - 2, -1, -1):
-            Cl = self.base << lv
-            gc, g = self._grid(shape, lv + 1), self._grid(shape, lv)
-            self._conv(gc, 1, 2 * Cl, Cl << self.dims, C.NN_D2S, h, h_cs, h_co, f"d{lv}t", out=B[f"cat{lv}"],
-                       out_cs=2 * Cl, out_co=0)
-            self._conv(g, 3, 2 * Cl, Cl, R, B[f"cat{lv}"], 2 * Cl, 0, f"d{lv}c0", out=B[f"d{lv}c0"], out_cs=Cl)
-            self._conv(g, 3, Cl, Cl, R, B[f"d{lv}c0"], Cl, 0, f"d{lv}c1", out=B[f"d{lv}c1"], out_cs=Cl)
-            h, h_cs, h_co, Ch = B[f"d{lv}c1"], Cl, 0, Cl
-        g0 = self._grid(shape, 0)
-        self._conv(g0, 1, self.base, self.cout, 0, h, h_cs, h_co, "head", out32=B["head"], out_cs=self.cout)
+        arr, names, bufs, need = self._forward_plan(shape)
+        if self._ws.numel() * 4 < need:
+            self._ws = torch.empty(need // 4 + 1024, dtype=torch.float32, device=self.device)
+        ptrs = (ctypes.c_void_p * (1 + len(bufs)))(x.data_ptr(), *[B[b].data_ptr() for b in bufs])
+        args = (ptrs, len(ptrs), _ptr(self.wbf), _ptr(self.master), _ptr(self._ws), self._ws.numel() * 4,
+                self._stream())
+        if self._prof is None:
+            C.check(self.L.lbmnn_forward(arr, len(arr), *args), "lbmnn_forward")
+            return B["head"]
+        for name, l in zip(names, arr):
+            run = lambda: C.check(self.L.lbmnn_forward(ctypes.byref(l), 1, *args), "lbmnn_forward")
+            if l.pool:
+                run()
+                continue
+            c = l.c
+            M, K = c.n * c.d * c.h * c.w, c.cin * c.ks ** self.dims
+            self._timed("fwd", name, 2 * M * c.cout * K,
+                        2 * M * c.cin + (4 if l.f32 else 2) * M * c.cout + 2 * c.cout * K, run)
         return B["head"]
 
     # ------------------------------------------------------------- backward --
@@ -312,25 +348,25 @@ class UNet:
         # head (1x1)
         top = ("d0c1" if self.levels > 1 else "bott")
         self._wgrad(g0, 1, self.base, 0, B[top], self.base, 0, g_head, self.cout, 0, self.cout, "head")
-        self._conv(g0, 1, self.cout, self.base, 0, g_head, self.cout, 0, "head", out=B["g_" + top],
-                   out_cs=self.base, transposed=True, relu_of=(B[top], self.base, 0))
+        self._dgrad(g0, 1, self.cout, self.base, 0, g_head, self.cout, 0, "head", out=B["g_" + top],
+                    out_cs=self.base, relu_of=(B[top], self.base, 0))
         for lv in range(0, self.levels - 1):
             Cl = self.base << lv
             g = self._grid(shape, lv)
             # second decoder conv
             self._wgrad(g, 3, Cl, 0, B[f"d{lv}c0"], Cl, 0, B[f"g_d{lv}c1"], Cl, 0, Cl, f"d{lv}c1")
-            self._conv(g, 3, Cl, Cl, 0, B[f"g_d{lv}c1"], Cl, 0, f"d{lv}c1", out=B[f"g_d{lv}c0"], out_cs=Cl,
-                       transposed=True, relu_of=(B[f"d{lv}c0"], Cl, 0))
+            self._dgrad(g, 3, Cl, Cl, 0, B[f"g_d{lv}c1"], Cl, 0, f"d{lv}c1", out=B[f"g_d{lv}c0"], out_cs=Cl,
+                        relu_of=(B[f"d{lv}c0"], Cl, 0))
             # first decoder conv (input: concatenation)
             self._wgrad(g, 3, 2 * Cl, 0, B[f"cat{lv}"], 2 * Cl, 0, B[f"g_d{lv}c0"], Cl, 0, Cl, f"d{lv}c0")
-            self._conv(g, 3, Cl, 2 * Cl, 0, B[f"g_d{lv}c0"], Cl, 0, f"d{lv}c0", out=B[f"g_cat{lv}"],
-                       out_cs=2 * Cl, transposed=True, use_bias=False)
+            self._dgrad(g, 3, Cl, 2 * Cl, 0, B[f"g_d{lv}c0"], Cl, 0, f"d{lv}c0", out=B[f"g_cat{lv}"],
+                        out_cs=2 * Cl)
             # transposed conv: input on the coarser grid
             gc = self._grid(shape, lv + 1)
             below = f"d{lv + 1}c1" if lv + 1 < self.levels - 1 else "bott"
             self._wgrad(gc, 1, 2 * Cl, C.NN_S2D_G, B[below], 2 * Cl, 0, B[f"g_cat{lv}"], 2 * Cl, 0, S * Cl, f"d{lv}t")
-            self._conv(gc, 1, Cl, 2 * Cl, C.NN_S2D, B[f"g_cat{lv}"], 2 * Cl, 0, f"d{lv}t", out=B["g_" + below],
-                       out_cs=2 * Cl, transposed=True, relu_of=(B[below], 2 * Cl, 0))
+            self._dgrad(gc, 1, Cl, 2 * Cl, C.NN_S2D, B[f"g_cat{lv}"], 2 * Cl, 0, f"d{lv}t", out=B["g_" + below],
+                        out_cs=2 * Cl, relu_of=(B[below], 2 * Cl, 0))
         for lv in range(self.levels - 1, -1, -1):
             Cl = self.base << lv
             g = self._grid(shape, lv)
@@ -344,16 +380,16 @@ class UNet:
             else:
                 gy1, cs1, co1 = B["g_bott"], Cl, 0
             self._wgrad(g, 3, Cl, 0, B[f"e{lv}c0"], Cl, 0, gy1, cs1, co1, Cl, f"e{lv}c1")
-            self._conv(g, 3, Cl, Cl, 0, gy1, cs1, co1, f"e{lv}c1", out=B[f"g_e{lv}c0"], out_cs=Cl,
-                       transposed=True, relu_of=(B[f"e{lv}c0"], Cl, 0))
+            self._dgrad(g, 3, Cl, Cl, 0, gy1, cs1, co1, f"e{lv}c1", out=B[f"g_e{lv}c0"], out_cs=Cl,
+                        relu_of=(B[f"e{lv}c0"], Cl, 0))
             if lv == 0:
                 xin, xcs, Cin = x, self.cin, self.cin
             else:
                 xin, xcs, Cin = B[f"p{lv - 1}"], Cl >> 1, Cl >> 1
             self._wgrad(g, 3, Cin, 0, xin, xcs, 0, B[f"g_e{lv}c0"], Cl, 0, Cl, f"e{lv}c0")
             if lv > 0:
-                self._conv(g, 3, Cl, Cin, 0, B[f"g_e{lv}c0"], Cl, 0, f"e{lv}c0", out=B[f"g_p{lv - 1}"],
-                           out_cs=Cin, transposed=True, use_bias=False)
+                self._dgrad(g, 3, Cl, Cin, 0, B[f"g_e{lv}c0"], Cl, 0, f"e{lv}c0", out=B[f"g_p{lv - 1}"],
+                            out_cs=Cin)
 
     # ------------------------------------------------------------ training --
     def loss_and_grad(self, out, target, wpix, scale):
