@@ -281,12 +281,10 @@ struct FTile {
 };
 
 template <int D>
-__device__ inline FTile fluid_tile(const Geo &G, int tile) {
+__device__ inline FTile fluid_tile(const InstDev &I, const FTileDesc &e, int tile) {
     FTile t;
     t.tile = tile;
-    const FTileDesc e = G.fblk[tile];
     t.b = e.b;
-    const InstDev &I = G.inst[e.b];
     t.id0 = (tile - I.ftile_begin) * FT;
     t.w0 = e.w0;
     t.w1 = e.w1;
