@@ -907,9 +907,9 @@ __device__ inline void transpose_4x8(const uint4 (&v)[4], uint2 (&o)[8]) {
 // no MFMA works on the empty rows a 64-row tile would carry; each thread then
 // loads two column groups of the im2col rows, and half the threads the rows
 // of G.
-template <bool NARROW>
+template <bool NARROW, bool SUMS>
 __global__ void __launch_bounds__(256) k_wgrad(ConvArgs a, const uint16_t *__restrict__ g, int g_cs,
-                                               int g_co, int rows, float *__restrict__ part,
+                                               int g_co, int rows, float *__restrict__ part, float *__restrict__ bpart,
                                                long long chunk) {
     constexpr int RM = NARROW ? 32 : BM;            // rows per block
     constexpr int CN = NARROW ? 128 : BN;           // columns per block
@@ -986,6 +986,10 @@ __global__ void __launch_bounds__(256) k_wgrad(ConvArgs a, const uint16_t *__res
         }
         cursor_add(cur, step, a);
     };
+    // SUMS: the row sums of G too (the bias gradient's partials), as products with ones in the first column tile
+    const bool sums = SUMS && blockIdx.y == 0 && wn == 0;
+    const bf16x8 ones = as_bf16x8(make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u));
+    f32x4 accb[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
     load(mb);
     for (long long mm = mb; mm < me; mm += WPB) {
         __syncthreads();                              // the previous stage's MFMA reads are done
@@ -1020,9 +1024,18 @@ __global__ void __launch_bounds__(256) k_wgrad(ConvArgs a, const uint16_t *__res
                 const bf16x8 fa = as_bf16x8(*(const uint4 *)&Gs[gr][wcol(gr, kr)]);
 #pragma unroll
                 for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fb[j], acc[i][j], 0, 0, 0);
+                if (sums) accb[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, ones, accb[i], 0, 0, 0);
             }
         }
     }
+    if (sums && (lane & 15) == 0)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int rr = r0 + wm * 32 + i * 16 + (lane >> 4) * 4 + q;
+                if (rr < rows) bpart[(long long)blockIdx.z * rows + rr] = accb[i][q];
+            }
     float *dst = part + (long long)blockIdx.z * rows * a.K;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -1300,12 +1313,12 @@ k_wgrad_rows(ConvArgs a, const uint16_t *__restrict__ g, int g_cs, int g_co, int
 // NW wavefronts the splits z = w, w + NW, ..., combined in wavefront order
 // (deterministic).  Bound by memory: 16 wavefronts keep enough rows in flight
 // where outputs are few and splits many.  The blocks from the nb'th on sum the
-// n2 outputs of part2 (the bias gradient's partials).
+// splits2 partials of the n2 outputs of part2 (the bias gradient's).
 template <int NW, int V>
 __global__ void __launch_bounds__(64 * NW) k_sum_splits(const float *__restrict__ part, int splits, long long n,
                                                         float *__restrict__ out, int accumulate, unsigned nb,
-                                                        const float *__restrict__ part2, long long n2,
-                                                        float *__restrict__ out2) {
+                                                        const float *__restrict__ part2, int splits2,
+                                                        long long n2, float *__restrict__ out2) {
     typedef float vec __attribute__((ext_vector_type(V)));
     __shared__ vec sh[NW][64];
     const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -1313,6 +1326,7 @@ __global__ void __launch_bounds__(64 * NW) k_sum_splits(const float *__restrict_
     if (b >= nb) {
         b -= nb;
         part = part2;
+        splits = splits2;
         n = n2;
         out = out2;
     }
@@ -1911,17 +1925,23 @@ long long wgrad_chunk(long long M, int splits) {
     return (c + WPB - 1) / WPB * WPB;
 }
 
-// Sum of z split partials into n outputs (and of part2 into n2): a block per
-// output when there are few (bias gradients), else 64 or 256 outputs per block.
+// Sum of z split partials into n outputs (and of z2 of part2 into n2): a block
+// per output when there are few (a weight gradient of at most 1024 entries, a
+// bias gradient of many splits, whose chain of loads would outlast the rest),
+// else 64 or 256 outputs per block.
 static hipError_t sum_splits(const float *part, int z, long long n, float *out, int accumulate, hipStream_t s,
-                             const float *part2 = nullptr, long long n2 = 0, float *out2 = nullptr) {
-    if (n <= 1024 && z > 16 && !part2) {
+                             const float *part2 = nullptr, int z2 = 0, long long n2 = 0, float *out2 = nullptr) {
+    const bool narrow = n <= 1024 && z > 16, narrow2 = part2 && (narrow || z2 > 512);
+    if (narrow2)
+        hipLaunchKernelGGL(k_sum_splits_narrow, dim3((unsigned)n2), dim3(256), 0, s, part2, z2, n2, out2, accumulate);
+    if (narrow) {
         hipLaunchKernelGGL(k_sum_splits_narrow, dim3((unsigned)n), dim3(256), 0, s, part, z, n, out, accumulate);
         return hipGetLastError();
     }
+    if (narrow2) n2 = 0;
 #define CALL(NW, V)                                                                                              \
     hipLaunchKernelGGL((k_sum_splits<NW, V>), dim3(blocks(n, 64 * V) + blocks(n2, 64 * V)), dim3(64 * NW), 0, s, \
-                       part, z, n, out, accumulate, blocks(n, 64 * V), part2, n2, out2)
+                       part, z, n, out, accumulate, blocks(n, 64 * V), part2, z2, n2, out2)
     if (n >= 65536 && ((n | n2) & 3) == 0 && (((uintptr_t)part | (uintptr_t)part2) & 15) == 0) CALL(4, 4);
     else if (z > 32) CALL(16, 1);
     else CALL(4, 1);
@@ -1976,8 +1996,8 @@ static hipError_t launch_wgrad_rows(int shape, const ConvArgs &a, const uint16_t
     return hipGetLastError();
 }
 
-// Weight gradient and (db) the bias gradient of the same G: from the row
-// kernel, else by a pass of its own.
+// Weight gradient and (db) the bias gradient of the same G, whose partials
+// follow the weight gradient's.
 hipError_t wgrad(const ConvArgs &a, const uint16_t *g, int g_cs, int g_co, int rows, float *part, int splits,
                  float *dw, float *db, int accumulate, hipStream_t s) {
     const long long chunk = wgrad_chunk(a.M, splits), n = (long long)rows * a.K;
@@ -1987,24 +2007,33 @@ hipError_t wgrad(const ConvArgs &a, const uint16_t *g, int g_cs, int g_co, int r
                           : (a.w > 16 ? launch_wgrad_rows<32, false> : launch_wgrad_rows<16, false>);
         const hipError_t e = f(shape, a, g, g_cs, g_co, rows, part, z, s);
         if (e != hipSuccess) return e;
-        return db ? sum_splits(part, z, n, dw, accumulate, s, part + z * n, rows, db) : sum_splits(part, z, n, dw, accumulate, s);
-    }
-    if (rows <= 32) {
-        const dim3 grid(1u, (unsigned)((a.K + 127) / 128), (unsigned)z);
-        hipLaunchKernelGGL(k_wgrad<true>, grid, dim3(256), 0, s, a, g, g_cs, g_co, rows, part, chunk);
     } else {
-        const dim3 grid((unsigned)((rows + BM - 1) / BM), (unsigned)((a.K + BN - 1) / BN), (unsigned)z);
-        hipLaunchKernelGGL(k_wgrad<false>, grid, dim3(256), 0, s, a, g, g_cs, g_co, rows, part, chunk);
+        const dim3 grid(rows <= 32 ? 1u : (unsigned)((rows + BM - 1) / BM),
+                        rows <= 32 ? (unsigned)((a.K + 127) / 128) : (unsigned)((a.K + BN - 1) / BN), (unsigned)z);
+        float *bpart = part + z * n;
+#define CALL(NARROW, SUMS) \
+    hipLaunchKernelGGL((k_wgrad<NARROW, SUMS>), grid, dim3(256), 0, s, a, g, g_cs, g_co, rows, part, bpart, chunk)
+        // at most 32 rows: a pass of its own for the bias gradient (16 x 256^2, 8 rows: 54 us with it, 66 us with the
+        // sums in the weight gradient); more rows: 128 x 64 entries 48 us with the sums, 70 us with a pass
+        if (rows <= 32) CALL(true, false);
+        else if (db) CALL(false, true);
+        else CALL(false, false);
+#undef CALL
+        if (db && rows <= 32) {
+            const hipError_t e = sum_splits(part, z, n, dw, accumulate, s);
+            if (e != hipSuccess) return e;
+            const int fine = (a.flags & FLAG_S2D_G) ? a.dims : 0;
+            const long long pixels = a.M << fine;
+            const int C = rows >> fine;
+            // about 16K elements (32 KB) of G per split, within the z rows floats that the workspace holds
+            long long sp = (pixels * C + 16383) / 16384;
+            if (sp > ((long long)z << fine)) sp = (long long)z << fine;
+            return bias_grad(g, g_cs, g_co, pixels, C, bpart, (int)(sp < 1 ? 1 : sp), db, accumulate, s);
+        }
     }
-    const hipError_t e = sum_splits(part, z, n, dw, accumulate, s);
-    if (!db || e != hipSuccess) return e;
-    const int fine = (a.flags & FLAG_S2D_G) ? a.dims : 0;         // rows = sub * C + co over the finer grid's pixels
-    const long long pixels = a.M << fine;
-    const int C = rows >> fine;
-    // about 16K elements (32 KB) of G per split, within the z rows floats that the workspace holds
-    long long sp = (pixels * C + 16383) / 16384;
-    if (sp > ((long long)z << fine)) sp = (long long)z << fine;
-    return bias_grad(g, g_cs, g_co, pixels, C, part + z * n, (int)(sp < 1 ? 1 : sp), db, accumulate, s);
+    if (!db) return sum_splits(part, z, n, dw, accumulate, s);
+    const int fine = (a.flags & FLAG_S2D_G) ? a.dims : 0;         // rows = sub * C + co: a sub is a split more
+    return sum_splits(part, z, n, dw, accumulate, s, part + z * n, z << fine, rows >> fine, db);
 }
 
 bool bias_grad8_ok(const void *g, int cs, int co, int C) {
