@@ -200,7 +200,12 @@ __device__ inline long long out_index(const ConvArgs &a, long long m, int c, int
 // SPLIT: blockIdx.z takes K steps [z sper, (z + 1) sper) and the block
 // stores its raw FP32 products to part[z][m][c] (k_conv_reduce adds the
 // splits and applies the epilogue).
-template <int TBM, int TBN, bool SPLIT = false>
+// TAPS: cin % 128 == 0, so that two or more K steps lie in one tap (or S2D
+// sub-pixel): its place is found once and pointers advance by 64 channels in
+// between, instead of divisions and tests per load (16 x 32^2, 256 -> 256 43 ->
+// 37 us, four images of 64^2, 256 -> 128 32 -> 27 us; at 64 channels, one step
+// a tap, 13 -> 15 us at 256^2, 64 -> 32).
+template <int TBM, int TBN, bool TAPS, bool SPLIT = false>
 __global__ void __launch_bounds__(256) k_conv(ConvArgs a, float *__restrict__ part = nullptr, int sper = 0) {
     constexpr int KB = 64;
     constexpr int WM = TBM / 2, WN = TBN / 2;
@@ -221,7 +226,48 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a, float *__restrict__ pa
 #pragma unroll
     for (int l = 0; l < AL; ++l) row[l] = row_of(a, m0 + (t >> 3) + 32 * l);
     uint4 ra[AL], rb[BL];
+    const int s0 = SPLIT ? (int)blockIdx.z * sper : 0;
+    const int steps = SPLIT ? min((a.K + KB - 1) / KB, s0 + sper) : (a.K + KB - 1) / KB;
+    int tap = 0, ci = 0;
+    const uint16_t *pa[AL], *pb[BL];
+    bool oka[AL];
+    auto place = [&] {
+        const KOff o = koff_of(a, tap * a.cin);
+#pragma unroll
+        for (int l = 0; l < AL; ++l) {
+            const unsigned xs = (unsigned)(row[l].x + o.dx), ys = (unsigned)(row[l].y + o.dy), zs = (unsigned)(row[l].z + o.dz);
+            oka[l] = row[l].valid && o.valid &&
+                     ((a.flags & FLAG_S2D) || (xs < (unsigned)a.w && ys < (unsigned)a.h && zs < (unsigned)a.d));
+            pa[l] = a.in + row[l].base + o.delta + ci + kq;
+        }
+    };
+    if (TAPS) {
+        tap = s0 * KB / a.cin;
+        ci = s0 * KB - tap * a.cin;
+        place();
+#pragma unroll
+        for (int l = 0; l < BL; ++l) pb[l] = a.wt + (long long)(n0 + (t >> 3) + 32 * l) * a.K + s0 * KB + kq;
+    }
     auto load = [&](int k0) {
+        if (TAPS) {
+#pragma unroll
+            for (int l = 0; l < AL; ++l) {
+                ra[l] = oka[l] ? *(const uint4 *)pa[l] : make_uint4(0, 0, 0, 0);
+                pa[l] += KB;
+            }
+#pragma unroll
+            for (int l = 0; l < BL; ++l) {
+                rb[l] = n0 + (t >> 3) + 32 * l < a.ncols ? *(const uint4 *)pb[l] : make_uint4(0, 0, 0, 0);
+                pb[l] += KB;
+            }
+            ci += KB;
+            if (ci == a.cin) {
+                ci = 0;
+                ++tap;
+                place();
+            }
+            return;
+        }
         const int k = k0 + kq;
         const bool kval = k < a.K;
         const KOff ko = koff_of(a, k);
@@ -244,8 +290,6 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a, float *__restrict__ pa
     for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int j = 0; j < TJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int s0 = SPLIT ? (int)blockIdx.z * sper : 0;
-    const int steps = SPLIT ? min((a.K + KB - 1) / KB, s0 + sper) : (a.K + KB - 1) / KB;
     load(s0 * KB);
     stash(s0 & 1);
     __syncthreads();
@@ -1843,13 +1887,15 @@ hipError_t conv_split(const ConvArgs &a, float *part, int S, hipStream_t s) {
     const int steps = (a.K + 63) / 64, sper = (steps + S - 1) / S;
     unsigned in_bytes;
     if (direct_ok(a, S, &in_bytes)) return conv_direct(a, S, sper, in_bytes, s);
-    if (a.ncols <= 32) {
-        dim3 grid(blocks(a.M, 64), (unsigned)((a.ncols + 31) / 32), (unsigned)S);
-        hipLaunchKernelGGL((k_conv<64, 32, true>), grid, dim3(256), 0, s, a, part, sper);
-    } else {
-        dim3 grid(blocks(a.M, 64), (unsigned)((a.ncols + 63) / 64), (unsigned)S);
-        hipLaunchKernelGGL((k_conv<64, 64, true>), grid, dim3(256), 0, s, a, part, sper);
-    }
+    const int tbn = a.ncols <= 32 ? 32 : 64;
+    const dim3 grid(blocks(a.M, 64), (unsigned)((a.ncols + tbn - 1) / tbn), (unsigned)S);
+    const bool taps = a.cin % 128 == 0;
+#define CALL(TBN, TAPS) hipLaunchKernelGGL((k_conv<64, TBN, TAPS, true>), grid, dim3(256), 0, s, a, part, sper)
+    if (tbn == 32 && taps) CALL(32, true);
+    else if (tbn == 32) CALL(32, false);
+    else if (taps) CALL(64, true);
+    else CALL(64, false);
+#undef CALL
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_conv_reduce, dim3(blocks(a.M * a.ncols, 256)), dim3(256), 0, s, a, part, S);
@@ -1898,25 +1944,31 @@ hipError_t conv(const ConvArgs &a, hipStream_t s) {
         // as many blocks as are resident together (5, 4 or 3 per CU), in multiples of 8 along x, so that the blocks
         // of a pixel group fall on one XCD (twice as many: 30 instead of 28 us at 64 -> 4 x 32)
         long long gx = (256 * (steps <= 1 ? 5 : steps <= 2 ? 4 : 3) / gy + 7) / 8 * 8;
-        if (gx > want) gx = want;
-        const dim3 grid((unsigned)gx, (unsigned)gy);
+        // four K steps in one to four rounds of pixel groups per wavefront: k_conv (four images of 64^2, 128 -> 4 x 64
+        // 9.6 us, here 10.7; one image 5.8 and 4.6, sixteen 29 and 25)
+        if (steps <= 2 || want <= gx || want >= 4 * gx) {
+            if (gx > want) gx = want;
+            const dim3 grid((unsigned)gx, (unsigned)gy);
 #define CALL(KS, PT) hipLaunchKernelGGL((k_conv1x1<KS, PT>), grid, dim3(256), 0, s, a, gw)
-        if (steps <= 1) CALL(1, 4);
-        else if (steps <= 2) CALL(2, 2);
-        else CALL(4, 2);
+            if (steps <= 1) CALL(1, 4);
+            else if (steps <= 2) CALL(2, 2);
+            else CALL(4, 2);
 #undef CALL
-        return hipGetLastError();
+            return hipGetLastError();
+        }
     }
     unsigned in_bytes;
     if (a.ks == 3 && direct_ok(a, 1, &in_bytes))
         return conv_direct(a, 1, (a.K + 63) / 64, in_bytes, s);
-    if (a.ncols <= 32) {
-        dim3 grid(blocks(a.M, 64), (unsigned)((a.ncols + 31) / 32));
-        hipLaunchKernelGGL((k_conv<64, 32>), grid, dim3(256), 0, s, a);
-    } else {
-        dim3 grid(blocks(a.M, 64), (unsigned)((a.ncols + 63) / 64));
-        hipLaunchKernelGGL((k_conv<64, 64>), grid, dim3(256), 0, s, a);
-    }
+    const int tbn = a.ncols <= 32 ? 32 : 64;
+    const dim3 grid(blocks(a.M, 64), (unsigned)((a.ncols + tbn - 1) / tbn));
+    const bool taps = a.cin % 128 == 0;
+#define CALL(TBN, TAPS) hipLaunchKernelGGL((k_conv<64, TBN, TAPS>), grid, dim3(256), 0, s, a)
+    if (tbn == 32 && taps) CALL(32, true);
+    else if (tbn == 32) CALL(32, false);
+    else if (taps) CALL(64, true);
+    else CALL(64, false);
+#undef CALL
     return hipGetLastError();
 }
 
