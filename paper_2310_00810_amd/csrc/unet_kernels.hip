@@ -1313,26 +1313,28 @@ k_wgrad_rows(ConvArgs a, const uint16_t *__restrict__ g, int g_cs, int g_co, int
         if (st + 1 < total) stash((st + 1) & 1);
     }
     // the groups' sums: the upper half of the groups adds to the lower half until one is left
-    float *sum = (float *)S + lane;
+    f32x4 *sum = (f32x4 *)S + lane;
 #pragma unroll
     for (int half = WK / 2; half > 0; half >>= 1) {
         __syncthreads();
-        float *w = sum + (((kg - half) * WR * WC + wave % (WR * WC)) * NA) * 64;
+        f32x4 *w = sum + (((kg - half) * WR * WC + wave % (WR * WC)) * (NA / 4)) * 64;
         if (kg >= half && kg < 2 * half) {
 #pragma unroll
-            for (int j = 0; j < 72; ++j) w[64 * j] = acc[j >> 3][(j >> 2) & 1][j & 3];
-            if (SUMS)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) w[64 * (72 + j)] = accb[j >> 2][j & 3];
+            for (int j = 0; j < 18; ++j) w[64 * j] = acc[j >> 1][j & 1];
+            if (SUMS) {
+                w[64 * 18] = accb[0];
+                w[64 * 19] = accb[1];
+            }
         }
         __syncthreads();
-        w = sum + ((kg * WR * WC + wave % (WR * WC)) * NA) * 64;
+        w = sum + ((kg * WR * WC + wave % (WR * WC)) * (NA / 4)) * 64;
         if (kg < half) {
 #pragma unroll
-            for (int j = 0; j < 72; ++j) acc[j >> 3][(j >> 2) & 1][j & 3] += w[64 * j];
-            if (SUMS)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) accb[j >> 2][j & 3] += w[64 * (72 + j)];
+            for (int j = 0; j < 18; ++j) acc[j >> 1][j & 1] += w[64 * j];
+            if (SUMS) {
+                accb[0] += w[64 * 18];
+                accb[1] += w[64 * 19];
+            }
         }
     }
     if (kg) return;
@@ -1863,17 +1865,19 @@ int conv_splits(const ConvArgs &a) {
 
 // The direct kernel's conditions; its splits are the wavefronts of a block.
 // It reads every operand from the caches for each 32 x 32 tile, so it pays while
-// launches and latency dominate, up to about 1.3e9 multiply-adds with splits
-// (us, direct against partials and k_conv_reduce: 128^2, 64 -> 64 and 32^2, 256
-// -> 256 11 : 16, 128^2, 128 -> 64 19 : 22, 64^2, 256 -> 128 19 : 21, 16^3, 128
-// -> 128 26 : 23, four images of 32^2, 256 -> 256 35 : 24) and half as many
-// without (256^2, 32 -> 32 8.5 : 9.7, 64 -> 32 20 : 14; 1 x 1 32^2, 256 -> 512
-// 7.3 : 6.9).
+// launches and latency dominate (us, direct against partials and k_conv_reduce):
+// with splits up to 1.3e9 multiply-adds (128^2, 64 -> 64 and 32^2, 256 -> 256 11
+// : 16, 128^2, 128 -> 64 19 : 22, 64^2, 256 -> 128 19 : 21, 16^3, 128 -> 128 26 :
+// 23, four images of 32^2, 256 -> 256 35 : 24), up to 0.5e9 for 32 channels or
+// fewer (6000 pixels, 256 -> 32 11 : 15, 8400 19 : 15); without splits up to
+// 0.67e9 and 10 steps, which one wavefront walks alone (256^2, 32 -> 32 8.5 :
+// 9.7; 36000 pixels, 64 -> 8 15 : 11; 1 x 1 32^2, 256 -> 512 7.3 : 6.9).
 static bool direct_ok(const ConvArgs &a, int S, unsigned *in_bytes) {
     const uintptr_t ob = a.out32 ? (uintptr_t)a.out32 : (uintptr_t)a.out;
     const long long bytes = 2 * a.M * a.in_cs;
     *in_bytes = (unsigned)bytes;
-    return S <= 16 && a.M * a.ncols <= (S > 1 ? 5LL << 28 : 5LL << 27) / a.K && a.cin % 32 == 0 && !(a.flags & FLAG_S2D) && bytes < (1LL << 31) && 2LL * a.ncols * a.K < (1LL << 31) && ((a.out_cs | a.out_co) & 7) == 0 &&
+    const long long most = S == 1 ? (a.K <= 320 ? 5LL << 27 : 0) : a.ncols <= 32 ? 1LL << 29 : 5LL << 28;
+    return S <= 16 && a.M * ((a.ncols + 31) / 32 * 32) <= most / a.K && a.cin % 32 == 0 && !(a.flags & FLAG_S2D) && bytes < (1LL << 31) && 2LL * a.ncols * a.K < (1LL << 31) && ((a.out_cs | a.out_co) & 7) == 0 &&
            (ob & 15) == 0;
 }
 static hipError_t conv_direct(const ConvArgs &a, int S, int sper, unsigned in_bytes, hipStream_t s) {
