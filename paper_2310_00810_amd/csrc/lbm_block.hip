@@ -383,7 +383,7 @@ __global__ void __launch_bounds__(NT) k_adj_steps(const uint2 *__restrict__ list
                 const float jb = abb_adj<9>(lam, in, out, drho_b[j], m.rho, um, nuo);
                 if (in || out) gface[j] += (double)jb;
             }
-            const float dt = collide_adj(G, I.omega, I.inv_tau2, m, g[j], lam, a[j]);
+            const float dt = collide_adj<lam_first(BCX, SEED)>(G, I.omega, I.inv_tau2, m, g[j], lam, a[j]);
             if (t + j * NT < owned) st.dtau[s][I.poff + v[j].x] = dt;
             if constexpr (SEED)
                 seed_adj<9>(st.target + I.poff * 2 + v[j].x, I.plane, roi[I.poff + v[j].x] * I.loss_scale, kind, m, a[j]);

@@ -777,7 +777,16 @@ __device__ inline void abb(float (&g)[Q], bool in, bool out, float drho_b, const
 //   d g_u / d F_opp(u) = -1,
 //   d g_u / d F_j      = 2 w_u rho_w (9 (u.c_u) c_u - 3 u) . (c_j - u) / rho,
 //   d g_u / d drho_b   = 2 w_u E_u.
-template <int Q>
+// ROUND_USQ: E_u with its last product rounded, as D3Q19 adjoint steps take
+// it, else fused (spelled out: left to the compiler, the kernels of one
+// lattice came to differ in the last bits of dL/d(drho_b)).
+template <bool ROUND_USQ>
+__device__ inline float abb_e(float cu, float usq) {
+#pragma clang fp contract(off)
+    const float e = fmaf(4.5f * cu, cu, 1.0f);
+    return ROUND_USQ ? e - 1.5f * usq : fmaf(-1.5f, usq, e);
+}
+template <int Q, bool ROUND_USQ = false>
 __device__ inline float abb_adj(float (&lam)[Q], bool in, bool out, float drho_b, float rho, const float (&u)[3],
                                 const float (&nu)[Q]) {
     using V = Vel<Q>;
@@ -792,7 +801,7 @@ __device__ inline float abb_adj(float (&lam)[Q], bool in, bool out, float drho_b
         const float nu_u = in ? nu[p] : (out ? nu[m] : 0.f);
         lam[m] -= in ? nu_u : 0.f;
         lam[p] -= out ? nu_u : 0.f;
-        gb += nu_u * 2.0f * V::w(p) * (1.0f + 4.5f * cu * cu - 1.5f * usq);
+        gb += nu_u * 2.0f * V::w(p) * abb_e<ROUND_USQ>(cu, usq);
         const float s = nu_u * 2.0f * V::w(p) * rw;
         Vx += s * (9.0f * cu - 3.0f * u[0]);
         Vy += s * ((V::cy(p) ? 9.0f * cu * V::cy(p) : 0.f) - 3.0f * u[1]);
@@ -825,12 +834,24 @@ __device__ inline void collide(const Geo &G, float om, const Moments &m, const f
 }
 
 // Transpose of the D2Q9 collision at the populations g (moments m) applied to
-// lam = S^T nu^{k+1}, as k_adj_step computes it: a = C'(g)^T lam; returns
-// dL/dtau of the node.  Which product of a sum is fused is spelled out where
-// the compiler's choice would depend on the surrounding code, so that both
-// kernels round alike.
+// lam = S^T nu^{k+1}: a = C'(g)^T lam; returns dL/dtau of the node.  With the
+// moments of w lam (S0, S_a, S_ab),  a_i = (1 - omega) lam_i + omega (A + B . c_i):
+//   A   = sum_k lam_k dfeq_k/drho = S0 (1 + 1.5 u.u) - 4.5 u.S2.u,
+//   B_a = sum_k lam_k dfeq_k/dj_a = 3 S_a + 9 (S2 u)_a - 3 u_a S0.
+// The equilibrium part acts on mu: BGK mu = lam; MRT mu = M^-1 S M lam (the
+// update matrix is symmetric), with dL/dtau from the two stress rates only.
+//
+// The single-step and the time-blocked adjoint kernels both call it, and
+// their gradients are the same bits: so which product of a sum is fused is
+// spelled out, not left to the compiler, whose choice depends on the code
+// around (one sum was fused the other way in each kernel and cost the last
+// bits).  LAM_FIRST: the last sum rounds (1 - omega) lam_i and fuses
+// omega eq, otherwise the other way round.
+constexpr bool lam_first(int bcx, bool seed) { return zouhe_faces(bcx) && (seed || bcx == BC_VELOCITY); }
+template <bool LAM_FIRST>
 __device__ inline float collide_adj(const Geo &G, float omega, float inv_tau2, const Moments &m, const float (&g)[9],
                                     const float (&lam)[9], float (&a)[9]) {
+#pragma clang fp contract(off)
     using V = Vel<9>;
     float dtau = 0.f;
     float mu[9];
@@ -845,7 +866,8 @@ __device__ inline float collide_adj(const Geo &G, float omega, float inv_tau2, c
             if (mrt_m(7, i)) { y7 += mrt_m(7, i) * lam[i]; d7 += mrt_m(7, i) * dq; }
             if (mrt_m(8, i)) { y8 += mrt_m(8, i) * lam[i]; d8 += mrt_m(8, i) * dq; }
         }
-        dtau = (y7 * d7 / (float)mrt_norm(7) + y8 * d8 / (float)mrt_norm(8)) * inv_tau2;
+        static_assert(mrt_norm(7) == 4 && mrt_norm(8) == 4, "exact quarters");
+        dtau = fmaf(y7 * d7, 0.25f, y8 * d8 * 0.25f) * inv_tau2;
     }
     if (!mrt) {
 #pragma unroll
@@ -855,27 +877,32 @@ __device__ inline float collide_adj(const Geo &G, float omega, float inv_tau2, c
 #pragma unroll
     for (int q = 0; q < 9; ++q) {
         const int cx = V::cx(q), cy = V::cy(q);
-        const float wl = V::w(q) * mu[q];
-        S0 += wl;
-        if (cx) { Sx += cx * wl; Sxx += wl; }
-        if (cy) { Sy += cy * wl; Syy += wl; }
-        if (cx && cy) Sxy += cx * cy * wl;
-        if (!mrt) dtau += lam[q] * g[q];
+        const float w = V::w(q);
+        S0 = fmaf(w, mu[q], S0);
+        if (cx) { Sx = fmaf(cx * w, mu[q], Sx); Sxx = fmaf(w, mu[q], Sxx); }
+        if (cy) { Sy = fmaf(cy * w, mu[q], Sy); Syy = fmaf(w, mu[q], Syy); }
+        if (cx && cy) Sxy = fmaf(cx * cy * w, mu[q], Sxy);
+        if (!mrt) dtau = fmaf(lam[q], g[q], dtau);
     }
     const float ux = m.ux, uy = m.uy;
     const float usq = fmaf(ux, ux, uy * uy);
     const float S2ux = fmaf(Sxy, uy, Sxx * ux), S2uy = fmaf(Sxy, ux, Syy * uy);
     const float uSu = fmaf(uy, S2uy, ux * S2ux);
-    const float A1 = 1.5f * usq * S0 - 4.5f * uSu;
+    const float A1 = fmaf(1.5f * usq, S0, -(4.5f * uSu));   // A - S0
     const float A = S0 + A1;
-    const float Bx = 3.0f * Sx + 9.0f * S2ux - 3.0f * ux * S0;
-    const float By = 3.0f * Sy + 9.0f * S2uy - 3.0f * uy * S0;
-    if (!mrt) dtau = (dtau - (m.drho * S0 + m.rho * (A1 + ux * Bx + uy * By))) * inv_tau2;
+    const float Bx = fmaf(-(3.0f * ux), S0, fmaf(3.0f, Sx, 9.0f * S2ux));
+    const float By = fmaf(-(3.0f * uy), S0, fmaf(3.0f, Sy, 9.0f * S2uy));
+    // BGK: dL/dtau = (1/tau^2) sum_q lam_q (g_q - f_eq,q).  f_eq is homogeneous of degree 1 in
+    // (rho, j), so sum_q lam_q f_eq,q = rho A + j.B; in shifted form, without cancelling S0:
+    //   sum_q lam_q (f_eq,q - w_q) = drho S0 + rho (A - S0 + u.B)
+    if (!mrt) dtau = (dtau - fmaf(m.drho, S0, m.rho * fmaf(uy, By, fmaf(ux, Bx, A1)))) * inv_tau2;
     const float om = mrt ? 1.0f : omega, om1 = 1.0f - omega;
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
         const float eq = A + (V::cx(i) ? V::cx(i) * Bx : 0.f) + (V::cy(i) ? V::cy(i) * By : 0.f);
-        a[i] = mrt ? lam[i] - mu[i] + eq : om1 * lam[i] + om * eq;
+        // MRT: lam - mu + J^T mu
+        a[i] = mrt ? lam[i] - mu[i] + eq
+                   : LAM_FIRST ? fmaf(om, eq, om1 * lam[i]) : fmaf(om1, lam[i], om * eq);
     }
     return dtau;
 }

@@ -231,11 +231,8 @@ __global__ void __launch_bounds__(FT) k_adj_seed(Geo G, const float *__restrict_
 // Adjoint step k: reads F^{k-1} (to rebuild g^k) and nu^{k+1}, writes nu^k;
 // accumulates dL/dtau per tile and dL/d(drho_b) per face node.  SEED: g^k
 // carries a frame of a time-windowed loss (target), whose dl/dg^k joins the
-// collision transpose's output before the boundary transpose.  With
-// lam = S^T nu^{k+1} and the moments of w lam (S0, S_a, S_ab), the
-// collision transpose is  a_i = (1 - omega) lam_i + omega (A + B . c_i)  with
-//   A   = sum_k lam_k dfeq_k/drho = S0 (1 + 1.5 u.u) - 4.5 u.S2.u,
-//   B_a = sum_k lam_k dfeq_k/dj_a = 3 S_a + 9 (S2 u)_a - 3 u_a S0.
+// collision transpose's output before the boundary transpose (collide_adj's
+// formulas; D3Q19 has the BGK ones in line).
 template <int Q, int BCX, bool SEED, bool NT>
 __global__ void __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(6))) k_adj_step(const FTileDesc *__restrict__ fblk, const InstDev *__restrict__ inst,
                                                  const uint2 *__restrict__ rw, int n_ftiles, int bc,
@@ -283,84 +280,50 @@ __global__ void __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(6))) k_
             // g^{k+1}'s unknowns at this face node were built from F^k, whose
             // moments are those of g^k
             const float um[3] = {m.ux, m.uy, m.uz};
-            const float jb = abb_adj<Q>(lam, in, out, drho_b, m.rho, um, nuo);
+            const float jb = abb_adj<Q, Q == 19>(lam, in, out, drho_b, m.rho, um, nuo);
             if (in) grad_in[I.face_off + n.r] += (double)jb;
             else if (out) grad_out[I.face_off + n.r] += (double)jb;
         }
-        // the equilibrium part of the collision transpose acts on mu:
-        // BGK mu = omega lam; MRT mu = M^-1 S M lam (the update matrix is
-        // symmetric), with dL/dtau from the two stress rates only
-        float mu[Q];
-        bool mrt = false;
-        if constexpr (Q == 9) mrt = GM.coll == COLL_MRT;
+        float a[Q];
         if constexpr (Q == 9) {
-            if (mrt) {
-                mrt_relax(lam, GM.mrt, I.omega, mu);
-                float y7 = 0.f, y8 = 0.f, d7 = 0.f, d8 = 0.f, feq[9];
-                feq_all<Q>(m, feq);
+            dtau = collide_adj<lam_first(BCX, SEED)>(GM, I.omega, I.inv_tau2, m, g, lam, a);
+        } else {
+            float S0 = 0.f, Sx = 0.f, Sy = 0.f, Sz = 0.f;
+            float Sxx = 0.f, Syy = 0.f, Szz = 0.f, Sxy = 0.f, Sxz = 0.f, Syz = 0.f;
 #pragma unroll
-                for (int i = 0; i < 9; ++i) {
-                    const float dq = g[i] - feq[i];
-                    if (mrt_m(7, i)) { y7 += mrt_m(7, i) * lam[i]; d7 += mrt_m(7, i) * dq; }
-                    if (mrt_m(8, i)) { y8 += mrt_m(8, i) * lam[i]; d8 += mrt_m(8, i) * dq; }
-                }
-                dtau = (y7 * d7 / (float)mrt_norm(7) + y8 * d8 / (float)mrt_norm(8)) * I.inv_tau2;
+            for (int q = 0; q < Q; ++q) {
+                const int cx = V::cx(q), cy = V::cy(q), cz = V::cz(q);
+                const float wl = V::w(q) * lam[q];
+                S0 += wl;
+                if (cx) { Sx += cx * wl; Sxx += wl; }
+                if (cy) { Sy += cy * wl; Syy += wl; }
+                if (cz) { Sz += cz * wl; Szz += wl; }
+                if (cx && cy) Sxy += cx * cy * wl;
+                if (cx && cz) Sxz += cx * cz * wl;
+                if (cy && cz) Syz += cy * cz * wl;
+                dtau += lam[q] * g[q];
+            }
+            const float ux = m.ux, uy = m.uy, uz = m.uz;
+            const float usq = ux * ux + uy * uy + uz * uz;
+            const float S2ux = Sxx * ux + Sxy * uy + Sxz * uz;
+            const float S2uy = Sxy * ux + Syy * uy + Syz * uz;
+            const float S2uz = Sxz * ux + Syz * uy + Szz * uz;
+            const float A1 = 1.5f * usq * S0 - 4.5f * (ux * S2ux + uy * S2uy + uz * S2uz);   // A - S0
+            const float A = S0 + A1;
+            const float Bx = 3.0f * Sx + 9.0f * S2ux - 3.0f * ux * S0;
+            const float By = 3.0f * Sy + 9.0f * S2uy - 3.0f * uy * S0;
+            const float Bz = 3.0f * Sz + 9.0f * S2uz - 3.0f * uz * S0;
+            dtau = (dtau - (m.drho * S0 + m.rho * (A1 + ux * Bx + uy * By + uz * Bz))) * I.inv_tau2;
+            const float om = I.omega, om1 = 1.0f - om;
+#pragma unroll
+            for (int i = 0; i < Q; ++i) {
+                const float eq = A + (V::cx(i) ? V::cx(i) * Bx : 0.f) + (V::cy(i) ? V::cy(i) * By : 0.f) +
+                                 (V::cz(i) ? V::cz(i) * Bz : 0.f);
+                a[i] = om1 * lam[i] + om * eq;
             }
         }
-        if (!mrt) {
-#pragma unroll
-            for (int q = 0; q < Q; ++q) mu[q] = lam[q];
-        }
-        float S0 = 0.f, Sx = 0.f, Sy = 0.f, Sz = 0.f;
-        float Sxx = 0.f, Syy = 0.f, Szz = 0.f, Sxy = 0.f, Sxz = 0.f, Syz = 0.f;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int cx = V::cx(q), cy = V::cy(q), cz = V::cz(q);
-            const float wl = V::w(q) * mu[q];
-            S0 += wl;
-            if (cx) { Sx += cx * wl; Sxx += wl; }
-            if (cy) { Sy += cy * wl; Syy += wl; }
-            if (cz) { Sz += cz * wl; Szz += wl; }
-            if (cx && cy) Sxy += cx * cy * wl;
-            if (cx && cz) Sxz += cx * cz * wl;
-            if (cy && cz) Syz += cy * cz * wl;
-            if (!mrt) dtau += lam[q] * g[q];
-        }
-        const float ux = m.ux, uy = m.uy, uz = m.uz;
-        const float usq = ux * ux + uy * uy + uz * uz;
-        const float S2ux = Sxx * ux + Sxy * uy + Sxz * uz;
-        const float S2uy = Sxy * ux + Syy * uy + Syz * uz;
-        const float S2uz = Sxz * ux + Syz * uy + Szz * uz;
-        const float A1 = 1.5f * usq * S0 - 4.5f * (ux * S2ux + uy * S2uy + uz * S2uz);   // A - S0
-        const float A = S0 + A1;
-        const float Bx = 3.0f * Sx + 9.0f * S2ux - 3.0f * ux * S0;
-        const float By = 3.0f * Sy + 9.0f * S2uy - 3.0f * uy * S0;
-        const float Bz = 3.0f * Sz + 9.0f * S2uz - 3.0f * uz * S0;
-        // BGK: dL/dtau = (1/tau^2) sum_q lam_q (g_q - f_eq,q).  f_eq is homogeneous of degree 1 in
-        // (rho, j), so sum_q lam_q f_eq,q = rho A + j.B; in shifted form, without cancelling S0:
-        //   sum_q lam_q (f_eq,q - w_q) = drho S0 + rho (A - S0 + u.B)
-        if (!mrt) dtau = (dtau - (m.drho * S0 + m.rho * (A1 + ux * Bx + uy * By + uz * Bz))) * I.inv_tau2;
-        const float om = mrt ? 1.0f : I.omega, om1 = 1.0f - I.omega;
-        float a[Q];
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            const float eq = A + (V::cx(i) ? V::cx(i) * Bx : 0.f) + (V::cy(i) ? V::cy(i) * By : 0.f) +
-                             (V::cz(i) ? V::cz(i) * Bz : 0.f);
-            // BGK: (1 - omega) lam + omega J^T lam;  MRT: lam - mu + J^T mu
-            a[i] = mrt ? lam[i] - mu[i] + eq : om1 * lam[i] + om * eq;
-        }
-        if constexpr (SEED) {
-            const float u[3] = {ux, uy, uz};
-            float tg[3] = {0.f, 0.f, 0.f}, dldu[3] = {0.f, 0.f, 0.f};
-#pragma unroll
-            for (int d = 0; d < D; ++d) tg[d] = target[I.poff * D + (long long)d * I.plane + n.id];
-            loss_node<D>(kind, roi[I.poff + n.id] * I.loss_scale, u, tg, dldu);
-            const float inv = 1.0f / m.rho;
-#pragma unroll
-            for (int i = 0; i < Q; ++i)
-                a[i] += inv * (dldu[0] * (V::cx(i) - ux) + dldu[1] * (V::cy(i) - uy) +
-                               (D == 3 ? dldu[2] * (V::cz(i) - uz) : 0.f));
-        }
+        if constexpr (SEED)
+            seed_adj<Q>(target + I.poff * D + n.id, I.plane, roi[I.poff + n.id] * I.loss_scale, kind, m, a);
         if (zouhe_faces(BCX)) {
             const float jb = zouhe_adj<Q>(a, in, out, g, drho_b, BCX == BC_VELOCITY);
             if (in) grad_in[I.face_off + n.r] += (double)jb;

@@ -116,3 +116,48 @@ def test_block_residual_steps_match_single_forward():
         n, _ = s.run_to_residual(0.8, 0.004, 0.0, tol=1e-12, max_steps=36, check_every=check)
         assert n == 36
         assert torch.equal(s.get_populations(), ref) and torch.equal(s.macro(mean2=True)[1], um)
+
+
+def _solver(lattice, insts, bc, T, **kw):
+    from paper_2310_00810_amd.lbm import Solver
+    return Solver(lattice, insts, bc=bc, steps=T, tape=True, **kw)
+
+
+def _gradient(s, drho, u, tau, din):
+    s.set_initial(torch.from_numpy(drho).cuda().reshape(-1), torch.from_numpy(u).cuda().reshape(-1, s.D))
+    loss = s.forward(tau, din, 0.0, record_tape=True)
+    s.adjoint()
+    g = s.grad()
+    return loss, g["drho_in"], g["dtau"], g["drho_out"], s.get_populations("adjoint").cpu().numpy()
+
+
+def _batch_equals_single(lattice, nxyz, n, bc, T, frames, collision):
+    """The gradients of a batch against those of its first and last instance alone, bit for bit."""
+    from paper_2310_00810_amd.lbm import Instance
+    nx, ny, nz = nxyz
+    D, sh = (2 if lattice == 9 else 3), (nz, ny, nx)
+    rng = np.random.default_rng(17)
+    solid = (rng.random((n,) + sh) < 0.1).astype(np.uint8)
+    solid[..., 0] = solid[..., -1] = 0
+    drho = (0.01 * rng.standard_normal((n,) + sh, dtype=np.float32)).astype(np.float32)
+    u = (0.02 * rng.standard_normal((n,) + sh + (D,), dtype=np.float32)).astype(np.float32)
+    tgt = (0.02 * rng.standard_normal((n, frames) + sh + (D,), dtype=np.float32)).astype(np.float32)
+    insts = [Instance(nx, ny, nz, solid=solid[b], target_u=tgt[b]) for b in range(n)]
+    tau = 0.7 + 0.02 * np.arange(n)
+    din = (0.05 if bc[0] == "velocity" else 0.006) * (1 + 0.1 * np.arange(n))
+    kw = dict(ckpt_interval=5, collision=collision, loss_frames=frames, loss_stride=2)
+    all_ = _gradient(_solver(lattice, insts, bc, T, **kw), drho, u, tau, din)
+    k = lattice * nx * ny * nz
+    for b in (0, n - 1):
+        one = _gradient(_solver(lattice, [insts[b]], bc, T, **kw), drho[b], u[b], tau[b], din[b])
+        for x, y in zip(all_[:4], one[:4]):
+            assert np.array_equal(x[b:b + 1], y)
+        assert np.array_equal(all_[4][b * k:(b + 1) * k], one[4])
+
+
+@pytest.mark.parametrize("collision", ["bgk", "mrt"])
+@pytest.mark.parametrize("frames", [1, 3])
+@pytest.mark.parametrize("bcx", ["pressure", "abb", "velocity", "wall", "periodic"])
+def test_single_step_and_blocked_adjoint_are_the_same_bits(bcx, frames, collision):
+    """462 000 nodes take single adjoint steps, one instance of them the time-blocked ones."""
+    _batch_equals_single(9, (300, 220, 1), 7, (bcx, "wall", "periodic"), 13, frames, collision)
