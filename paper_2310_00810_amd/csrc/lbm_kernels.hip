@@ -25,9 +25,10 @@ namespace lbm {
 // loaded beside the tile's, not after it, which saves the usual
 // single-instance problem a scalar load's latency (64^3 step 8.3 -> 7.8 us);
 // kernels of states beyond the Infinity Cache, bound by memory, lose 0.8 % by
-// it (256^3).  Not for D2Q9, whose single-step adjoint has to contract its
-// products as the time-blocked one does (a batch and its single instances give
-// the same bits).
+// it (256^3).  Not for D2Q9 (compiled with the copy, its adjoint step fused
+// other products than before), nor for adjoint steps with anti-bounce-back
+// faces, whose gradient would differ in the last bits from that of the kernel
+// for larger states: a batch and its instances alone give the same bits.
 #define FLUID_PROLOGUE(EARLY)                                               \
     constexpr int D = Vel<Q>::D;                                            \
     __shared__ TileLds L;                                                   \
@@ -249,7 +250,7 @@ __global__ void __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(6))) k_
     const Geo G = geo_of(fblk, inst, rw, n_ftiles, bc);   // GM: the collision model (D2Q9)
     using V = Vel<Q>;
     __shared__ double red[4];
-    FLUID_PROLOGUE(Q == 19 && !NT);
+    FLUID_PROLOGUE(Q == 19 && !NT && BCX != BC_ABB);
     float dtau = 0.f;
     if (n.active) {
         const bool in = density_faces(BCX) && n.x == 0, out = density_faces(BCX) && n.x == I.nx - 1;

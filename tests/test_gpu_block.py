@@ -161,3 +161,10 @@ def _batch_equals_single(lattice, nxyz, n, bc, T, frames, collision):
 def test_single_step_and_blocked_adjoint_are_the_same_bits(bcx, frames, collision):
     """462 000 nodes take single adjoint steps, one instance of them the time-blocked ones."""
     _batch_equals_single(9, (300, 220, 1), 7, (bcx, "wall", "periodic"), 13, frames, collision)
+
+
+@pytest.mark.parametrize("frames", [1, 2])
+@pytest.mark.parametrize("bcx", ["pressure", "abb", "velocity"])
+def test_d3q19_states_beyond_the_cache_are_the_same_bits(bcx, frames):
+    """Two states of 2.1 M nodes exceed the Infinity Cache (streaming kernels), those of one instance do not."""
+    _batch_equals_single(19, (96, 64, 68), 5, (bcx, "wall", "periodic"), 5, frames, "bgk")
