@@ -43,23 +43,6 @@ namespace {
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// A set of tiles of the time-blocked kernels: steps per launch at most (0:
-// single-step kernels), large region, number of tiles.
-struct Blocks {
-    int ms = 0, big = 0, n_tiles = 0;
-    long long n_entries = 0;  // list entries at most
-    size_t off_tile = 0, off_list = 0;
-    int ex() const { return big ? 64 : 32; }
-    int ey() const { return big ? 32 : 16; }
-    int tx() const { return ex() - 2 * ms; }
-    int ty() const { return ey() - 2 * ms; }
-    // nodes along one axis of n nodes within ms of the tile of t nodes at v
-    int extent(int v, int n, int t, bool periodic) const {
-        const int lo = v - ms, hi = std::min(v + t, n) + ms;
-        return periodic ? hi - lo : std::min(hi, n) - std::max(lo, 0);
-    }
-};
-
 // Device workspace layout of one problem.
 struct Layout {
     int q = 9, D = 2, n_inst = 0;
@@ -67,7 +50,7 @@ struct Layout {
     int R = 1;                // resident segments: the last R segments' states are kept by the forward
     int frames = 1, stride = 1;   // loss frames: the states after steps T - (frames - 1 - m) stride
     int n_tiles = 0, n_ftiles = 0;
-    Blocks fwd, adj;          // time-blocked kernels of the forward and of the adjoint steps
+    lbm::Blocks fwd, adj;     // time-blocked kernels of the forward and of the adjoint steps
     long long total_poff = 0, total_nodes = 0, total_face = 0, total_words = 0;
     long long S = 0;          // floats per state buffer
     int n_states = 0;
@@ -173,17 +156,9 @@ void plan_blocks(Layout &L, long long nodes, int bcx, int bcy) {
     L.fwd.big = nodes > 200000;
     L.fwd.ms = L.fwd.big ? 5 : small;
     L.adj.ms = nodes <= 200000 ? small : nodes <= 400000 ? 3 : 0;
-    for (Blocks *B : {&L.fwd, &L.adj}) {
-        if (!B->ms) continue;
-        for (const InstDev &I : L.inst) {
-            long long lx = 0, ly = 0;     // region nodes of all tiles = (sum of widths) x (sum of heights)
-            int tx = 0, ty = 0;
-            for (int x = 0; x < I.nx; x += B->tx(), ++tx) lx += B->extent(x, I.nx, B->tx(), bcx == LBM_BC_PERIODIC);
-            for (int y = 0; y < I.ny; y += B->ty(), ++ty) ly += B->extent(y, I.ny, B->ty(), bcy == LBM_BC_PERIODIC);
-            B->n_tiles += tx * ty;
-            B->n_entries += lx * ly;
-        }
-    }
+    for (lbm::Blocks *B : {&L.fwd, &L.adj})
+        for (const InstDev &I : L.inst)
+            if (B->ms) B->count(I.nx, I.ny, bcx == LBM_BC_PERIODIC, bcy == LBM_BC_PERIODIC);
 }
 
 void plan(const lbm_problem *p, Layout &L) {
@@ -255,7 +230,7 @@ void plan(const lbm_problem *p, Layout &L) {
     L.off_red = take(sizeof(double) * 2 * p->n_inst);
     L.off_fblk = take(sizeof(lbm::FTileDesc) * std::max(1, L.n_ftiles));
     // the forward and the adjoint kernels share one set of tiles where they are alike
-    for (Blocks *B : {&L.fwd, &L.adj}) {
+    for (lbm::Blocks *B : {&L.fwd, &L.adj}) {
         if (B == &L.adj && B->ms == L.fwd.ms && B->big == L.fwd.big) {
             *B = L.fwd;
             continue;
@@ -545,18 +520,9 @@ int lbm_init(lbm_handle **out, const lbm_problem *p, void *d_workspace, size_t b
     }
     std::vector<lbm::MTileDesc> tiles[2];
     for (int k = 0; k < 2; ++k) {
-        const Blocks &B = k ? L.adj : L.fwd;
+        const lbm::Blocks &B = k ? L.adj : L.fwd;
         if (!B.ms || (k && B.off_tile == L.fwd.off_tile)) continue;
-        int at = 0;
-        for (int b = 0; b < L.n_inst; ++b)
-            for (int y = 0; y < h->hinst[b].ny; y += B.ty())
-                for (int x = 0; x < h->hinst[b].nx; x += B.tx()) {
-                    lbm::MTileDesc e{};
-                    e.b = b; e.x0 = x; e.y0 = y; e.list = at;
-                    at += B.extent(x, h->hinst[b].nx, B.tx(), p->bc_x == LBM_BC_PERIODIC) *
-                          B.extent(y, h->hinst[b].ny, B.ty(), p->bc_y == LBM_BC_PERIODIC);
-                    tiles[k].push_back(e);
-                }
+        tiles[k] = lbm::tile_table(B, h->hinst, p->bc_x == LBM_BC_PERIODIC, p->bc_y == LBM_BC_PERIODIC);
     }
     auto cp = [&](size_t off, const void *src, size_t n) -> int {
         if (!n) return LBM_OK;
@@ -589,7 +555,7 @@ int lbm_init(lbm_handle **out, const lbm_problem *p, void *d_workspace, size_t b
     h->G.fblk = h->at<lbm::FTileDesc>(L.off_fblk);
     hipError_t he = lbm::launch_init_eq(L.q, h->G, h->init(), nullptr, nullptr, h->stream);
     for (int k = 0; k < 2 && he == hipSuccess; ++k) {
-        const Blocks &B = k ? L.adj : L.fwd;
+        const lbm::Blocks &B = k ? L.adj : L.fwd;
         lbm::BlockGeo &T = k ? h->adj : h->fwd;
         T.ms = B.ms; T.big = B.big; T.n_tiles = B.n_tiles;
         T.tile = h->at<lbm::MTileDesc>(B.off_tile);

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "lbm_tiles.hpp"
+
 namespace lbm {
 
 enum { BC_PRESSURE = 0, BC_PERIODIC = 1, BC_WALL = 2, BC_ABB = 3, BC_VELOCITY = 4 };
@@ -131,15 +133,7 @@ struct FTileDesc {
 };
 
 // Time-blocked D2Q9 kernels: a region of 32 x 16 (big: 64 x 32) nodes per
-// block, i.e. a tile with a halo of ms nodes, ms = steps per launch at most.  Per tile: instance, first column and row, and the number of the
-// list's nodes within distance d of the tile.
-constexpr int MS_MAX = 6;
-struct MTileDesc {
-    int b, x0, y0;
-    int list;              // first entry of the tile's list
-    int cnt[MS_MAX + 1];
-    int pad[5];
-};
+// block, i.e. a tile with a halo of ms nodes, ms = steps per launch at most.
 struct BlockGeo {
     int ms, big, n_tiles;
     const MTileDesc *tile;
