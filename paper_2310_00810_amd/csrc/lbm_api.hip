@@ -51,6 +51,7 @@ struct Layout {
     int frames = 1, stride = 1;   // loss frames: the states after steps T - (frames - 1 - m) stride
     int n_tiles = 0, n_ftiles = 0;
     lbm::Blocks fwd, adj;     // time-blocked kernels of the forward and of the adjoint steps
+    bool lone_steps = false;  // a launch of one step takes the single-step kernel
     long long total_poff = 0, total_nodes = 0, total_face = 0, total_words = 0;
     long long S = 0;          // floats per state buffer
     int n_states = 0;
@@ -150,15 +151,34 @@ long long count_fluid(const lbm_instance &S) {
 // region with 3 steps (800 x 320: 6.5 us, single-step 8.0) up to 400000 nodes;
 // beyond, its registers leave too few wavefronts (1024 x 512: 11.8 against
 // 11.7; 3 x 1024 x 512: 31.7 against 26.0) and it runs single steps.
+//
+// A launch costs about 6 us (adjoint: 7) per round of resident tiles (512, or
+// 1024 of the small region) even where a tile owns few nodes, a single step
+// about 4.2 + 10.8 us per million nodes, at least 1.4 us per 1000 blocks
+// (adjoint: 5 + 24.5, 3).  So batches of many tiny or thin lattices run single
+// steps: 500 of 3 x 1000 25 us a step (time-blocked 64), 23437 of 8 x 8 41 (62),
+// 18750 of 4 x 4 31 (50); while 200 of 1000 x 3 12 (11), 5859 of 16 x 16 23 (19).
+// And a launch of one step, before a loss frame or the last state, takes the
+// single-step kernel above 100000 nodes: 800 x 320 9.8 us a step (time-blocked
+// 11.5), 1024 x 600 15.6 (22); 300 x 200 no difference.
 void plan_blocks(Layout &L, long long nodes, int bcx, int bcy) {
     if (L.q != 9) return;
     const int small = nodes <= 32000 ? 6 : nodes <= 100000 ? 5 : 4;
     L.fwd.big = nodes > 200000;
     L.fwd.ms = L.fwd.big ? 5 : small;
     L.adj.ms = nodes <= 200000 ? small : nodes <= 400000 ? 3 : 0;
+    L.lone_steps = nodes > 100000;
+    double fluid = 0;
+    for (const InstDev &I : L.inst) fluid += I.n_fluid;
+    auto pays = [&](const lbm::Blocks &B, double round, double resident, double base, double node, double block) {
+        return B.n_tiles / resident * round / B.ms < base + std::max(node * fluid, block * L.n_ftiles);
+    };
     for (lbm::Blocks *B : {&L.fwd, &L.adj})
         for (const InstDev &I : L.inst)
             if (B->ms) B->count(I.nx, I.ny, bcx == LBM_BC_PERIODIC, bcy == LBM_BC_PERIODIC);
+    if (!pays(L.fwd, 6.0, L.fwd.big ? 512 : 1024, 4.2, 10.8e-6, 1.4e-3)) L.fwd = L.adj = lbm::Blocks{};
+    // (the time-blocked adjoint keeps its dL/dtau where single recomputed steps would put the state to compare)
+    if (L.adj.ms && !pays(L.adj, 7.0, 512, 5.0, 24.5e-6, 3e-3)) L.adj = lbm::Blocks{};
 }
 
 void plan(const lbm_problem *p, Layout &L) {
@@ -363,8 +383,10 @@ int run_length(const lbm_handle *h) { return std::max(1, h->L.fwd.ms); }
 // sweep, long after it would have left the cache.
 int steps(lbm_handle *h, const float *src, const lbm::StepRun &r, hipStream_t s) {
     const float *fin = h->at<float>(h->L.off_face_in), *fout = h->at<float>(h->L.off_face_out);
-    if (h->L.fwd.ms) HIP_TRY(lbm::launch_steps(h->G, h->fwd, src, r, fin, fout, s));
-    else HIP_TRY(lbm::launch_step(h->G, src, r.dst[0], fin, fout, !h->is_pp(r.dst[0]), s));
+    if (!h->L.fwd.ms || (r.n == 1 && !r.check && h->L.lone_steps))
+        HIP_TRY(lbm::launch_step(h->L.q, h->G, src, r.dst[0], fin, fout, !h->is_pp(r.dst[0]), s));
+    else
+        HIP_TRY(lbm::launch_steps(h->G, h->fwd, src, r, fin, fout, s));
     return LBM_OK;
 }
 
@@ -824,7 +846,7 @@ static int enqueue_reverse(lbm_handle *h, bool resident, const float *seed, hipS
             if ((rc = steps(h, j == 0 ? h->ckpt(c) : h->seg(r, j), f, st))) return rc;
             j += f.n;
         }
-        if (verify && !L.fwd.ms) HIP_TRY(lbm::launch_compare(h->G, spare, h->ckpt(c + 1), flag, st));
+        if (verify && !L.fwd.ms) HIP_TRY(lbm::launch_compare(q, h->G, spare, h->ckpt(c + 1), flag, st));
         return LBM_OK;
     };
     auto kept = [&](int k) { return resident && k < L.R; };          // k-th segment of the sweep, c = n_seg - 1 - k

@@ -82,7 +82,8 @@ __device__ inline void face_unknown_adjoints(__amdgpu_buffer_rsrc_t rn, int plan
         if (V::cx(i) != 0 && (V::cx(i) > 0 ? in : out)) nuo[i] = bload(rn, own + (unsigned)(i * plane) * 4u);
 }
 
-// One step of a D3Q19 problem (D2Q9 steps are time-blocked: k_steps).
+// One step (of a D2Q9 problem where the time-blocked k_steps does not pay;
+// GM: its collision model).
 // NTM: 0 default cache policy, 1 non-temporal stores (a destination that no
 // later step reads while it could still be cached: a tape state, or any
 // state when two exceed the Infinity Cache), 2 non-temporal gathers too
@@ -92,9 +93,9 @@ __global__ void __launch_bounds__(FT) k_step(const FTileDesc *__restrict__ fblk,
                                              const uint2 *__restrict__ rw, int n_ftiles, int bc,
                                              const float *__restrict__ src, float *__restrict__ dst,
                                              const float *__restrict__ face_in,
-                                             const float *__restrict__ face_out) {
+                                             const float *__restrict__ face_out, Geo GM) {
     const Geo G = geo_of(fblk, inst, rw, n_ftiles, bc);
-    FLUID_PROLOGUE(NTM < 2);
+    FLUID_PROLOGUE(Q == 19 && NTM < 2);
     if (!n.active) return;
     const bool in = density_faces(BCX) && n.x == 0, out = density_faces(BCX) && n.x == I.nx - 1;
     const float drho_b = face_density<BCX>(I, n, in, out, face_in, face_out);
@@ -112,10 +113,17 @@ __global__ void __launch_bounds__(FT) k_step(const FTileDesc *__restrict__ fblk,
     const float om = I.omega;
     const __amdgpu_buffer_rsrc_t rd = planes_rsrc(dst + I.st_off, Q, I.plane);
     const unsigned own = (unsigned)n.id * 4u;
-    float feq[Q];
-    feq_all<Q>(m, feq);
+    if constexpr (Q == 9) {
+        float f[Q];
+        collide(GM, om, m, g, f);
 #pragma unroll
-    for (int i = 0; i < Q; ++i) bstore<(NTM >= 1)>(rd, g[i] + om * (feq[i] - g[i]), own, plane_off(i, plane));
+        for (int i = 0; i < Q; ++i) bstore<(NTM >= 1)>(rd, f[i], own, plane_off(i, plane));
+    } else {
+        float feq[Q];
+        feq_all<Q>(m, feq);
+#pragma unroll
+        for (int i = 0; i < Q; ++i) bstore<(NTM >= 1)>(rd, g[i] + om * (feq[i] - g[i]), own, plane_off(i, plane));
+    }
 }
 
 // Bit-for-bit comparison of two states over the fluid nodes of every
@@ -549,14 +557,6 @@ static inline dim3 grid_of(const Geo &G) { return dim3((unsigned)G.n_tiles); }
 static inline dim3 fgrid_of(const Geo &G) { return dim3((unsigned)G.n_ftiles); }
 
 // Fluid-tile kernels take the x boundary kind as a template parameter.
-#define DISPATCH_BCX19(bcx, CALL)                                                          \
-    do {                                                                                   \
-        if (bcx == BC_PRESSURE) CALL(19, BC_PRESSURE);                                     \
-        else if (bcx == BC_PERIODIC) CALL(19, BC_PERIODIC);                                \
-        else if (bcx == BC_WALL) CALL(19, BC_WALL);                                        \
-        else if (bcx == BC_ABB) CALL(19, BC_ABB);                                          \
-        else CALL(19, BC_VELOCITY);                                                        \
-    } while (0)
 #define DISPATCH_BCX(q, bcx, CALL)                                                         \
     do {                                                                                   \
         if (q == 9) {                                                                      \
@@ -566,31 +566,37 @@ static inline dim3 fgrid_of(const Geo &G) { return dim3((unsigned)G.n_ftiles); }
             else if (bcx == BC_ABB) CALL(9, BC_ABB);                                       \
             else CALL(9, BC_VELOCITY);                                                     \
         } else {                                                                           \
-            DISPATCH_BCX19(bcx, CALL);                                                     \
+            if (bcx == BC_PRESSURE) CALL(19, BC_PRESSURE);                                 \
+            else if (bcx == BC_PERIODIC) CALL(19, BC_PERIODIC);                            \
+            else if (bcx == BC_WALL) CALL(19, BC_WALL);                                    \
+            else if (bcx == BC_ABB) CALL(19, BC_ABB);                                      \
+            else CALL(19, BC_VELOCITY);                                                    \
         }                                                                                  \
     } while (0)
 
-hipError_t launch_step(const Geo &G, const float *src, float *dst, const float *fin, const float *fout, bool tape,
-                       hipStream_t s) {
+hipError_t launch_step(int q, const Geo &G, const float *src, float *dst, const float *fin, const float *fout,
+                       bool tape, hipStream_t s) {
     if (G.n_ftiles == 0) return hipSuccess;
-    // beyond the Infinity Cache every step streams, gathers included; a step
-    // into the tape streams its stores
-    const int ntm = G.nt ? 2 : (tape ? 1 : 0);
+    // beyond the Infinity Cache every step streams, and D3Q19 gathers read
+    // non-temporal too (D2Q9 ones do not: other blocks reread their
+    // neighbouring rows' lines); a step into the tape streams its stores
+    const int ntm = G.nt ? (q == 19 ? 2 : 1) : (tape ? 1 : 0);
 #define PRE G.fblk, G.inst, G.rw, G.n_ftiles, packed_bc(G)
 #define CALL(Q, B)                                                                                 \
     do {                                                                                           \
-        if (ntm == 2) hipLaunchKernelGGL((k_step<Q, B, 2>), fgrid_of(G), dim3(FT), 0, s, PRE, src, dst, fin, fout); \
-        else if (ntm == 1) hipLaunchKernelGGL((k_step<Q, B, 1>), fgrid_of(G), dim3(FT), 0, s, PRE, src, dst, fin, fout); \
-        else hipLaunchKernelGGL((k_step<Q, B, 0>), fgrid_of(G), dim3(FT), 0, s, PRE, src, dst, fin, fout); \
+        if (ntm == 2) hipLaunchKernelGGL((k_step<Q, B, Q == 19 ? 2 : 1>), fgrid_of(G), dim3(FT), 0, s, PRE, src, dst, fin, fout, G); \
+        else if (ntm == 1) hipLaunchKernelGGL((k_step<Q, B, 1>), fgrid_of(G), dim3(FT), 0, s, PRE, src, dst, fin, fout, G); \
+        else hipLaunchKernelGGL((k_step<Q, B, 0>), fgrid_of(G), dim3(FT), 0, s, PRE, src, dst, fin, fout, G); \
     } while (0)
-    DISPATCH_BCX19(G.bcx, CALL);
+    DISPATCH_BCX(q, G.bcx, CALL);
 #undef CALL
     return hipGetLastError();
 }
 
-hipError_t launch_compare(const Geo &G, const float *a, const float *b, unsigned *flag, hipStream_t s) {
+hipError_t launch_compare(int q, const Geo &G, const float *a, const float *b, unsigned *flag, hipStream_t s) {
     if (G.n_ftiles == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_compare<19>, fgrid_of(G), dim3(FT), 0, s, G, a, b, flag);
+    if (q == 9) hipLaunchKernelGGL(k_compare<9>, fgrid_of(G), dim3(FT), 0, s, G, a, b, flag);
+    else hipLaunchKernelGGL(k_compare<19>, fgrid_of(G), dim3(FT), 0, s, G, a, b, flag);
     return hipGetLastError();
 }
 

@@ -5,11 +5,11 @@
 
 namespace lbm {
 
-// One step of a D3Q19 problem.
-hipError_t launch_step(const Geo &G, const float *src, float *dst, const float *fin, const float *fout, bool tape,
-                       hipStream_t s);
-// Sets *flag = 1 if D3Q19 states a and b differ in any population of a fluid node.
-hipError_t launch_compare(const Geo &G, const float *a, const float *b, unsigned *flag, hipStream_t s);
+// tape: dst is a state that only the reverse sweep reads again.
+hipError_t launch_step(int q, const Geo &G, const float *src, float *dst, const float *fin, const float *fout,
+                       bool tape, hipStream_t s);
+// Sets *flag = 1 if states a and b differ in any population of a fluid node.
+hipError_t launch_compare(int q, const Geo &G, const float *a, const float *b, unsigned *flag, hipStream_t s);
 // acc: add to the partials (the later frames of a time-windowed loss).
 hipError_t launch_loss(int q, const Geo &G, const float *F, const float *roi, const float *target,
                        int kind, double *part, int acc, hipStream_t s);

@@ -131,7 +131,7 @@ def _gradient(s, drho, u, tau, din):
     return loss, g["drho_in"], g["dtau"], g["drho_out"], s.get_populations("adjoint").cpu().numpy()
 
 
-def _batch_equals_single(lattice, nxyz, n, bc, T, frames, collision):
+def _batch_equals_single(lattice, nxyz, n, bc, T, frames, collision, spread=0.1):
     """The gradients of a batch against those of its first and last instance alone, bit for bit."""
     from paper_2310_00810_amd.lbm import Instance
     nx, ny, nz = nxyz
@@ -144,7 +144,7 @@ def _batch_equals_single(lattice, nxyz, n, bc, T, frames, collision):
     tgt = (0.02 * rng.standard_normal((n, frames) + sh + (D,), dtype=np.float32)).astype(np.float32)
     insts = [Instance(nx, ny, nz, solid=solid[b], target_u=tgt[b]) for b in range(n)]
     tau = 0.7 + 0.02 * np.arange(n)
-    din = (0.05 if bc[0] == "velocity" else 0.006) * (1 + 0.1 * np.arange(n))
+    din = (0.05 if bc[0] == "velocity" else 0.006) * (1 + spread * np.arange(n))
     kw = dict(ckpt_interval=5, collision=collision, loss_frames=frames, loss_stride=2)
     all_ = _gradient(_solver(lattice, insts, bc, T, **kw), drho, u, tau, din)
     k = lattice * nx * ny * nz
@@ -168,3 +168,10 @@ def test_single_step_and_blocked_adjoint_are_the_same_bits(bcx, frames, collisio
 def test_d3q19_states_beyond_the_cache_are_the_same_bits(bcx, frames):
     """Two states of 2.1 M nodes exceed the Infinity Cache (streaming kernels), those of one instance do not."""
     _batch_equals_single(19, (96, 64, 68), 5, (bcx, "wall", "periodic"), 5, frames, "bgk")
+
+
+@pytest.mark.parametrize("bcx,bcy,collision", [("pressure", "wall", "bgk"), ("abb", "periodic", "mrt"),
+                                               ("velocity", "wall", "mrt"), ("periodic", "periodic", "bgk")])
+def test_thin_lattices_step_singly_with_the_same_bits(bcx, bcy, collision):
+    """60 lattices of 3 x 700 take single steps (a tile would own 24 nodes), one of them time-blocked ones."""
+    _batch_equals_single(9, (3, 700, 1), 60, (bcx, bcy, "periodic"), 13, 3, collision, spread=0.005)
