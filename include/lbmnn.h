@@ -124,9 +124,9 @@ int lbmnn_conv_wgrad_noalloc(const lbmnn_conv_desc *c, const void *g, int g_cstr
  * input-gradient weights of a convolution; flip = 0, taps = 1 transposes a
  * [rows][cols] matrix. */
 int lbmnn_weight_transpose(const void *w, void *wt, int rows, int taps, int cols, int flip, void *stream);
-/* lbmnn_weight_transpose of n layers of a weight buffer in one launch (per 64):
- * layer i, rows[i] x taps[i] x cols[i] at element off[i] of w, goes to the same
- * offset of wt; fewer than 2^25 elements a layer.  The five arrays are host
+/* lbmnn_weight_transpose of n layers of a weight buffer in one launch (per 64
+ * layers or 2^20 tiles of 32 x 32): layer i, rows[i] x taps[i] x cols[i] at
+ * element off[i] of w, goes to the same offset of wt.  The five arrays are host
  * memory, read before the call returns. */
 int lbmnn_weight_transpose_layers(const void *w, void *wt, int n, const int *off, const int *rows, const int *taps,
                                   const int *cols, const int *flip, void *stream);

@@ -243,22 +243,35 @@ int lbmnn_weight_transpose_layers(const void *w, void *wt, int n, const int *off
     if (!w || !wt || n < 0 || !off || !rows || !taps || !cols || !flip)
         return lbm_fail(LBM_EINVAL, "bad transpose arguments");
     for (int i = 0; i < n; ++i)
-        if (off[i] < 0 || rows[i] < 1 || taps[i] < 1 || cols[i] < 1 ||
-            (long long)rows[i] * taps[i] >= (1LL << 31) || (long long)rows[i] * taps[i] * cols[i] >= (1LL << 25))
+        if (off[i] < 0 || rows[i] < 1 || taps[i] < 1 || cols[i] < 1)
             return lbm_fail(LBM_EINVAL, "bad shape of layer %d", i);
-    for (int i = 0; i < n; i += nn::WtransLayers::MAX) {
-        nn::WtransLayers L{};
-        L.n = n - i < nn::WtransLayers::MAX ? n - i : nn::WtransLayers::MAX;
-        for (int k = 0; k < L.n; ++k) {
-            L.off[k] = off[i + k];
-            L.rows[k] = rows[i + k];
-            L.taps[k] = taps[i + k];
-            L.cols[k] = cols[i + k];
-            L.flip[k] = flip[i + k];
-        }
+    nn::WtransLayers L{};
+    auto flush = [&]() -> int {
         NN_TRY(nn::wtrans_layers((const uint16_t *)w, (uint16_t *)wt, L, (hipStream_t)stream));
+        L = nn::WtransLayers{};
+        return LBM_OK;
+    };
+    for (int i = 0; i < n; ++i) {
+        const long long tiles = nn::wtrans_tiles(rows[i], cols[i]), nb = tiles * taps[i];
+        if (tiles > nn::WtransLayers::MAX_BLOCKS || nb > nn::WtransLayers::MAX_BLOCKS) {
+            // (as a layer by itself; the launch counts its threads in 32 bits)
+            const int rc = lbmnn_weight_transpose((const uint16_t *)w + off[i], (uint16_t *)wt + off[i], rows[i], taps[i],
+                                                  cols[i], flip[i], stream);
+            if (rc) return rc;
+            continue;
+        }
+        if (L.n == nn::WtransLayers::MAX || L.blocks + nb > nn::WtransLayers::MAX_BLOCKS)
+            if (const int rc = flush()) return rc;
+        const int k = L.n++;
+        L.first[k] = L.blocks;
+        L.blocks += (int)nb;
+        L.off[k] = off[i];
+        L.rows[k] = rows[i];
+        L.taps[k] = taps[i];
+        L.cols[k] = cols[i];
+        L.flip[k] = flip[i];
     }
-    return LBM_OK;
+    return flush();
 }
 
 int lbmnn_bias_grad(const void *g, int cstride, int coff, long long pixels, int C, float *db, int accumulate,

@@ -2270,14 +2270,9 @@ hipError_t wtrans(const uint16_t *w, uint16_t *wt, int rows, int taps, int cols,
     return hipGetLastError();
 }
 
-hipError_t wtrans_layers(const uint16_t *w, uint16_t *wt, WtransLayers L, hipStream_t s) {
-    long long n = 0;
-    for (int l = 0; l < L.n; ++l) {
-        L.first[l] = (int)n;
-        n += (long long)L.taps[l] * ((L.rows[l] + 31) / 32) * ((L.cols[l] + 31) / 32);
-    }
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_wtrans_layers, dim3((unsigned)n), dim3(256), 0, s, w, wt, L);
+hipError_t wtrans_layers(const uint16_t *w, uint16_t *wt, const WtransLayers &L, hipStream_t s) {
+    if (L.blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_wtrans_layers, dim3((unsigned)L.blocks), dim3(256), 0, s, w, wt, L);
     return hipGetLastError();
 }
 

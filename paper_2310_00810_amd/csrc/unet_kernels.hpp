@@ -67,13 +67,15 @@ hipError_t denormalize(const float *pred, int pcs, const uint8_t *solid, const f
 
 namespace nn {
 // Up to MAX layers of a weight buffer to transpose in one launch: element
-// offset (the same in both buffers) and shape of each; first (a layer's first
-// block) is filled in.
+// offset (the same in both buffers), shape and first block of each, a block
+// per 32 x 32 tile of a tap; at most MAX_BLOCKS blocks.
 struct WtransLayers {
     static constexpr int MAX = 64;                  // lanes of a wavefront
-    int n;
+    static constexpr int MAX_BLOCKS = 1 << 20;
+    int n, blocks;
     int first[MAX], off[MAX], rows[MAX], taps[MAX], cols[MAX], flip[MAX];
 };
-hipError_t wtrans_layers(const uint16_t *w, uint16_t *wt, WtransLayers L, hipStream_t s);
+inline long long wtrans_tiles(int rows, int cols) { return ((rows + 31LL) / 32) * ((cols + 31LL) / 32); }
+hipError_t wtrans_layers(const uint16_t *w, uint16_t *wt, const WtransLayers &L, hipStream_t s);
 hipError_t wtrans(const uint16_t *w, uint16_t *wt, int rows, int taps, int cols, int flip, hipStream_t s);
 }

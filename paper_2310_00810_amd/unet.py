@@ -63,10 +63,13 @@ class UNet:
             self.boff[name] = off
             off += co
         self.n_params = off
-        # (offset, rows, taps, cols, flip) of the layers' transposes, as five int arrays:
-        # conv flips the taps and swaps cin / cout, tconv [sub*co + c][ci] -> [ci][sub*co + c]
+        # (offset, rows, taps, cols, flip) of the layers' transposes, as five int arrays (offsets
+        # past 31 bits: one by one): conv flips the taps and swaps cin / cout, tconv
+        # [sub*co + c][ci] -> [ci][sub*co + c]
         shapes = [(self.woff[k], self.wshape[k][0], 1 if kind == "tconv" else ks ** dims, ci, int(kind != "tconv"))
                   for k, (kind, ci, co, ks) in self.layers.items()]
+        self._wt_far = [v for v in shapes if v[0] >= 1 << 31]
+        shapes = [v for v in shapes if v[0] < 1 << 31]
         self._wt_shapes = [(ctypes.c_int * len(shapes))(*v) for v in zip(*shapes)]
         n8 = (off + 7) // 8 * 8
         dev = self.device
@@ -331,8 +334,11 @@ class UNet:
 
     # ------------------------------------------------------------- backward --
     def _transpose_weights(self):
-        C.check(self.L.lbmnn_weight_transpose_layers(_ptr(self.wbf), _ptr(self.wT), len(self.layers), *self._wt_shapes,
-                                                     self._stream()), "lbmnn_weight_transpose_layers")
+        C.check(self.L.lbmnn_weight_transpose_layers(_ptr(self.wbf), _ptr(self.wT), len(self._wt_shapes[0]),
+                                                     *self._wt_shapes, self._stream()), "lbmnn_weight_transpose_layers")
+        for off, *shape in self._wt_far:
+            C.check(self.L.lbmnn_weight_transpose(_ptr(self.wbf, off), _ptr(self.wT, off), *shape, self._stream()),
+                    "lbmnn_weight_transpose")
 
     def backward(self, g_head):
         """Gradients of <head, g_head> into self.grad (overwritten)."""

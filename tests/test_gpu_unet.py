@@ -716,3 +716,37 @@ def test_direct_kernel_edges(dims, ks, grid, cin, cout):
             assert np.array_equal(got[..., :8], old[..., :8]) and np.array_equal(got[..., 8 + cout:], old[..., 8 + cout:])
             # FP32 accumulation of up to 4,608 products of unit-variance sums; BF16 outputs add one rounding
             assert np.all(np.abs(got[..., 8:8 + cout] - exp) <= (0 if out32 else 2 ** -7) * np.abs(exp) + 2e-5)
+
+
+@pytest.mark.parametrize("shapes", [
+    [(64, 9, 32, 1), (2048, 9, 2048, 1), (32, 1, 8, 0)],                 # a layer of more than 2^25 weights
+    [(1 << 20, 1, 1, 0)] * 40 + [(40, 27, 24, 1)],                       # more tiles than one launch takes
+    [((1 << 25) + 32, 1, 1, 0), (33, 3, 65, 1)],                         # a layer of more tiles than that
+])
+def test_layer_transposes_of_any_size(shapes):
+    C = C_()
+    n = [r * t * c for r, t, c, _ in shapes]
+    off = np.concatenate([[0], np.cumsum(n)])
+    w = torch.randint(-32768, 32767, (int(off[-1]),), dtype=torch.int16, device="cuda",
+                      generator=torch.Generator(device="cuda").manual_seed(1))
+    wt = torch.zeros_like(w)
+    args = [(ctypes.c_int * len(shapes))(*[int(x) for x in v]) for v in (off[:-1], *zip(*shapes))]
+    C.check(C.nnlib().lbmnn_weight_transpose_layers(w.data_ptr(), wt.data_ptr(), len(shapes), *args, stream()), "layers")
+    for o, m, (r, t, c, flip) in zip(off, n, shapes):
+        src = w[o:o + m].view(r, t, c)
+        assert torch.equal(wt[o:o + m].view(c, t, r), (src.flip(1) if flip else src).permute(2, 1, 0))
+
+
+def test_wide_network_trains():
+    """The deepest layer, 2048 x 9 x 2048, has more than 2^25 weights."""
+    from paper_2310_00810_amd.unet import UNet
+    net = UNet(2, base=128, levels=5, seed=1)
+    x = torch.randn((1, 1, 16, 16, 8), device="cuda").to(torch.bfloat16)
+    tgt = torch.randn((1, 1, 16, 16, 3), device="cuda")
+    loss = net.train_step(x, tgt, torch.ones((1, 1, 16, 16), device="cuda"), 1e-4, n_fluid=256)
+    assert torch.isfinite(torch.as_tensor(loss)).all() and torch.isfinite(net.grad).all()
+    co, k = net.wshape["e4c1"]
+    o = net.woff["e4c1"]
+    assert net.grad[o:o + co * k].abs().max() > 0
+    # the transposes of the weights before the step's update
+    assert co * k > 1 << 25 and net.wT[o:o + co * k].abs().max() > 0
