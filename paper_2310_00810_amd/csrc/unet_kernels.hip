@@ -1131,7 +1131,9 @@ __device__ inline bf16x8 tr_operand(const uint16_t *p0, const uint16_t *p1) {
 // of `len` rows; walker v (block part z, group k: v = z WK + k) takes the
 // segments v per .. v per + per - 1.  Step k of a segment that starts at row y0
 // meets input row y0 - 1 + k with rows y0 + k, y0 + k - 1 and y0 + k - 2 of G;
-// G reads 0 outside the segment, the input outside the plane.  WG_NR steps are
+// the input reads 0 outside the plane.  Rows of G outside the segment are left
+// out (wavefront-uniform branches: zeros in their place would turn a non-finite
+// input into NaN, also in taps that it does not reach).  WG_NR steps are
 // staged at a time: the next ones are loaded while the current ones multiply,
 // and go to the other LDS buffer.
 //
@@ -1268,15 +1270,19 @@ k_wgrad_rows(ConvArgs a, const uint16_t *__restrict__ g, int g_cs, int g_co, int
     int sg = (zp * WK + kg) * wk.per, left = wk.sps;   // (segments past the last one hold no rows)
     const int total = wk.per * wk.sps;
     segment(sg);
+    int gs = 0, gl = max(yend - y, 0);                 // the stage's first G row in its segment, the segment's rows
     load();
     stash(0);
     for (int st = 0; st < total; ++st) {
-        const int o = (st & 1) * BUF;
+        const int o = (st & 1) * BUF, s0 = gs, sl = gl;
         __syncthreads();
         if (st + 1 < total) {
+            gs += NR;
             if (--left == 0) {
                 left = wk.sps;
                 segment(++sg);
+                gs = 0;
+                gl = max(yend - y, 0);
             }
             load();
         }
@@ -1297,6 +1303,7 @@ k_wgrad_rows(ConvArgs a, const uint16_t *__restrict__ g, int g_cs, int g_co, int
                     if (k + 1 < NR) read_row(k + 1);
                     __builtin_amdgcn_sched_barrier(0);
                 }
+                if (__builtin_expect((unsigned)(s0 + k - dy) >= (unsigned)sl, 0)) continue;
 #pragma unroll
                 for (int dx = 0; dx < 3; ++dx)
 #pragma unroll

@@ -750,3 +750,46 @@ def test_wide_network_trains():
     assert net.grad[o:o + co * k].abs().max() > 0
     # the transposes of the weights before the step's update
     assert co * k > 1 << 25 and net.wT[o:o + co * k].abs().max() > 0
+
+
+# (rows, cin) of every block shape of the row kernel, planes wider and narrower than its strips; 2D heights that are
+# cut into segments (a walker per segment), 3D planes
+@pytest.mark.parametrize("dims,shape", [(2, (1, 1, 16, 16)), (2, (1, 1, 64, 32)), (3, (1, 4, 16, 32))])
+@pytest.mark.parametrize("rows,cin", [(64, 32), (32, 64), (32, 32), (32, 8)])
+def test_wgrad_reaches_no_further_than_its_taps(dims, shape, rows, cin):
+    """A non-finite activation makes exactly the entries non-finite that a product with it enters: one in the first
+    row of a plane enters no product with the (absent) gradient row above."""
+    C = C_()
+    n, d, h, w = shape
+    rng = np.random.default_rng(3)
+    x = bf(rng.standard_normal(shape + (cin,)))
+    g = bf(rng.standard_normal(shape + (rows,)))
+    g[g == 0] = 1.0
+    x[0, 0, 0, 5, 2] = np.inf
+    x[0, d - 1, h - 1, 9, 1] = np.nan
+    x[0, d // 2, 8, 0, cin - 1] = -np.inf
+    K, M = cin * 3 ** dims, n * d * h * w
+    xd, gd = dev_bf(x), dev_bf(g)
+    dw = torch.zeros((rows, K), device="cuda")
+    desc = C.lbmnn_conv_desc(n, d, h, w, dims, 3, cin, rows, 0, xd.data_ptr(), cin, 0, None, None, rows, 0)
+    for splits in (1, max(1, M // 512)):
+        need = C.nnlib().lbmnn_wgrad_workspace_bytes(M, rows, K, splits)
+        ws = torch.empty(need // 4 + 4, device="cuda")
+        C.check(C.nnlib().lbmnn_conv_wgrad(ctypes.byref(desc), gd.data_ptr(), rows, 0, rows, dw.data_ptr(), 0,
+                                           ws.data_ptr(), need, splits, stream()), "wgrad")
+        # products that exist: gradient pixel m, input pixel m + tap inside the plane
+        ref = np.zeros((rows, 3 ** dims, cin))
+        offs = [(dz, dy, dx) for dz in ((-1, 0, 1) if dims == 3 else (0,)) for dy in (-1, 0, 1) for dx in (-1, 0, 1)]
+        with np.errstate(all="ignore"):
+            for t, off in enumerate(offs):
+                lo = [max(0, -o) for o in off]
+                hi = [s - max(0, o) for s, o in zip(shape[1:], off)]
+                gs = g[(slice(None),) + tuple(slice(a, b) for a, b in zip(lo, hi))].reshape(-1, rows)
+                xs = x[(slice(None),) + tuple(slice(a + o, b + o) for a, b, o in zip(lo, hi, off))].reshape(-1, cin)
+                for c in range(cin):
+                    ref[:, t, c] = (gs.astype(np.float64) * xs[:, c:c + 1].astype(np.float64)).sum(0)
+        got = dw.cpu().numpy().reshape(ref.shape)
+        assert np.array_equal(np.isfinite(got), np.isfinite(ref))
+        ok = np.isfinite(ref)
+        # M products of magnitude about 1 summed in FP32
+        assert np.abs(got[ok] - ref[ok]).max() <= 2.0 ** -23 * M * np.abs(ref[ok]).max()
