@@ -1879,7 +1879,15 @@ int conv_splits(const ConvArgs &a) {
 // fewer (6000 pixels, 256 -> 32 11 : 15, 8400 19 : 15); without splits up to
 // 0.67e9 and 10 steps, which one wavefront walks alone (256^2, 32 -> 32 8.5 :
 // 9.7; 36000 pixels, 64 -> 8 15 : 11; 1 x 1 32^2, 256 -> 512 7.3 : 6.9).
+// From nine splits on, a CU holds one block, and pixels and weight rows that lie
+// a multiple of 256 bytes apart load slowly: with those, one round of blocks,
+// and not a few blocks of eleven splits or more (4 x 6 x 6 x 32, 128 -> 64, 288
+// blocks 25 : 20; 5 x 14 x 37, 256 -> 128, 324 blocks 20 : 18; 8^3, 128 -> 64,
+// 32 blocks 14.5 : 12.7; 12^3, 128 -> 64, 108 blocks 15 : 13.8, 128 -> 128, 216
+// blocks 15.2 : 17.8; 16^2, 256 -> 32, 8 blocks of nine 11.0 : 10.3).
 static bool direct_ok(const ConvArgs &a, int S, unsigned *in_bytes) {
+    const long long tiles = (a.M + 31) / 32 * ((a.ncols + 31) / 32);
+    if (S >= 9 && a.cin % 128 == 0 && (tiles > 256 || tiles < (S >= 11 ? 128 : 16))) return false;
     const uintptr_t ob = a.out32 ? (uintptr_t)a.out32 : (uintptr_t)a.out;
     const long long bytes = 2 * a.M * a.in_cs;
     *in_bytes = (unsigned)bytes;
