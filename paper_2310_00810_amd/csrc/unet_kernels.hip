@@ -1167,7 +1167,7 @@ k_wgrad_rows(ConvArgs a, const uint16_t *__restrict__ g, int g_cs, int g_co, int
     constexpr int XN = (XE + TG - 1) / TG, GN = (GE + TG - 1) / TG;
     constexpr int XB = NR * HT * CB, GB = NR * 32 * RB + (WR > 1 ? 64 : 0);  // halfwords of a stage
     constexpr int NA = SUMS ? 80 : 72;                                   // a lane's sums
-    constexpr int SUM = NA * 64 * 2 * WR * WC * (WK / 2);                // halfwords of the groups' sums
+    constexpr int SUM = NA * 64 * 2 * (WK > 2 ? 8 : 4);                  // halfwords of the sums handed over
     constexpr int NL = 2 * WK * (XB + GB) > SUM ? 2 * WK * (XB + GB) : SUM;
     static_assert(NR == 3, "the G rows rotate through 3 operands");
     __shared__ __align__(16) uint16_t S[NL];
@@ -1319,47 +1319,56 @@ k_wgrad_rows(ConvArgs a, const uint16_t *__restrict__ g, int g_cs, int g_co, int
                 for (int i = 0; i < 2; ++i) accb[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fg[k][i], ones, accb[i], 0, 0, 0);
         if (st + 1 < total) stash((st + 1) & 1);
     }
-    // the groups' sums: the upper half of the groups adds to the lower half until one is left
-    f32x4 *sum = (f32x4 *)S + lane;
+    // The groups' sums, the upper half of them added to the lower half until one is left.  Two groups: the second
+    // hands its sums over, the first adds and stores.  More: all hand theirs over, and group k adds and stores every
+    // WK'th operand (a barrier a halving, the last group storing alone: 1 us more; for two groups 0.5 us less).
+    f32x4 *sum = (f32x4 *)S + lane;                        // [wavefront][operand][lane]
+    constexpr int NO = NA / 4;
+    const int wp = wave % (WR * WC);
+    __syncthreads();
+    if (WK > 2 || kg == 1) {
+        f32x4 *w = sum + (WK > 2 ? wave : wp) * NO * 64;
 #pragma unroll
-    for (int half = WK / 2; half > 0; half >>= 1) {
-        __syncthreads();
-        f32x4 *w = sum + (((kg - half) * WR * WC + wave % (WR * WC)) * (NA / 4)) * 64;
-        if (kg >= half && kg < 2 * half) {
-#pragma unroll
-            for (int j = 0; j < 18; ++j) w[64 * j] = acc[j >> 1][j & 1];
-            if (SUMS) {
-                w[64 * 18] = accb[0];
-                w[64 * 19] = accb[1];
-            }
-        }
-        __syncthreads();
-        w = sum + ((kg * WR * WC + wave % (WR * WC)) * (NA / 4)) * 64;
-        if (kg < half) {
-#pragma unroll
-            for (int j = 0; j < 18; ++j) acc[j >> 1][j & 1] += w[64 * j];
-            if (SUMS) {
-                accb[0] += w[64 * 18];
-                accb[1] += w[64 * 19];
-            }
+        for (int j = 0; j < 18; ++j) w[j * 64] = acc[j >> 1][j & 1];
+        if (SUMS) {
+            w[18 * 64] = accb[0];
+            w[19 * 64] = accb[1];
         }
     }
-    if (kg) return;
-    if (sums && (lane & 15) == 0)                          // accb[i][q]: row r0 + 32 wr + 16 i + 4 (lane >> 4) + q
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            bpart[(long long)zp * rows + r0 + 32 * wr + 16 * (j >> 2) + 4 * (lane >> 4) + (j & 3)] = accb[j >> 2][j & 3];
-    // acc[j][i][q]: row r0 + 32 wr + 16 i + 4 (lane >> 4) + q, channel ci0 + 16 wc + (lane & 15), tap j
+    __syncthreads();
+    // operand j, element q: tap j / 2, row r0 + 32 wr + 16 (j & 1) + 4 (lane >> 4) + q, channel ci0 + 16 wc + (lane & 15);
+    // 18 and 19: the rows' sums
     float *dst = part + (long long)zp * rows * a.K + (a.dims == 3 ? 9 * (dz + 1) * a.cin : 0) + ci0 + 16 * wc + (lane & 15);
-    if (C8 && (lane & 15) >= 8) return;
+    auto store = [&](int j, f32x4 v) {
+        const int rr = r0 + 32 * wr + 16 * (j & 1) + 4 * (lane >> 4);
+        if (SUMS && j >= 18) {
+            if ((lane & 15) == 0)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+                for (int q = 0; q < 4; ++q) bpart[(long long)zp * rows + rr + q] = v[q];
+        } else if (!C8 || (lane & 15) < 8) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            float *d = dst + (long long)(r0 + 32 * wr + 16 * i + 4 * (lane >> 4) + q) * a.K;
-#pragma unroll
-            for (int j = 0; j < 9; ++j) d[j * a.cin] = acc[j][i][q];
+            for (int q = 0; q < 4; ++q) dst[(long long)(rr + q) * a.K + (j >> 1) * a.cin] = v[q];
         }
+    };
+    if constexpr (WK == 2) {
+        if (kg) return;
+#pragma unroll
+        for (int j = 0; j < 18; ++j) store(j, acc[j >> 1][j & 1] + sum[(wp * NO + j) * 64]);
+        if (sums)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) store(18 + j, accb[j] + sum[(wp * NO + 18 + j) * 64]);
+        return;
+    }
+    for (int j = kg; j < (sums ? NO : 18); j += WK) {
+        f32x4 v[WK];
+#pragma unroll
+        for (int k = 0; k < WK; ++k) v[k] = sum[((k * WR * WC + wp) * NO + j) * 64];
+#pragma unroll
+        for (int half = WK / 2; half > 0; half >>= 1)
+#pragma unroll
+            for (int k = 0; k < half; ++k) v[k] += v[k + half];
+        store(j, v[0]);
+    }
 }
 
 // Sum of split partials: a block takes 64 V outputs (V per lane, one load), its
@@ -2027,6 +2036,10 @@ static int rows_shape(const ConvArgs &a, int rows, int g_cs) {
     if (a.ks != 3 || (a.flags & (FLAG_S2D | FLAG_D2S | FLAG_S2D_G)) || a.w < 16) return 0;
     const long long reach = ((a.w <= 16 ? a.h : 0) + WG_NR + 1LL) * a.w + 34;
     if (2 * reach * (a.in_cs > g_cs ? a.in_cs : g_cs) >= (1LL << 31)) return 0;
+    // small layers are launch, first loads and sums, and the im2col kernel's four wavefronts have less of those
+    // (rows of 64: 16^2, 64 -> 64 8.4 us, here 12; 64^2 11.5 : 12.5; 2 x 64 x 96 13.5 : 14.2; 16 x 17 x 23, 128 ->
+    // 128 16.2 : 18.2; beyond it falls behind: 5 x 32 x 96, 128 -> 128 25.7 : 19.4)
+    if (rows % 64 == 0 && (double)a.M * rows * a.K <= 0.7e9) return 0;
     if (rows % 64 == 0 && a.cin % 32 == 0) return 22;
     if (rows % 32 == 0 && a.cin % 64 == 0) return 14;
     if (rows % 32 == 0 && a.cin % 32 == 0) return 12;
@@ -2036,25 +2049,36 @@ static int rows_shape(const ConvArgs &a, int rows, int g_cs) {
 
 template <int PW, bool SUMS>
 static hipError_t launch_wgrad_rows(int shape, const ConvArgs &a, const uint16_t *g, int g_cs, int g_co, int rows,
-                                    float *part, int &z, hipStream_t s) {
+                                    float *part, int &z, float *dw1, float *db1, hipStream_t s) {
     const int RB = shape == 22 ? 64 : 32, CB = shape == 11 ? 8 : shape == 14 ? 64 : 32;
     const int WK = shape == 11 ? 8 : shape == 12 ? 4 : 2;
     const long long tiles = (long long)(rows / RB) * (a.cin / CB) * (a.dims == 3 ? 3 : 1);
     const long long npx = (a.w + PW - 1) / PW, strips = ((long long)a.n * a.d * npx + 32 / PW - 1) / (32 / PW);
-    // one block per CU, within the partials that the workspace holds; the cut of the strips into segments
-    // that gives the longest walk the fewest stages (a segment costs two steps more than it has rows)
-    const long long zt = tiles >= 256 ? 1 : 256 / tiles, walkers = (zt < z ? zt : z) * WK;
+    // one block per CU at most, within the partials that the workspace holds; of the cuts of the strips into
+    // segments (a segment costs two steps more than it has rows) and the numbers of walkers the one with the least
+    // time: 1.2 us a stage of the longest walk, 1.8 us for a million floats of partials written and summed (128^2,
+    // 128 -> 128 with 32 parts 21.5 us, with 16 19.7; 16 x 32 x 96, 64 -> 64 with 96 22, with 48 19)
+    const long long zt = tiles >= 256 ? 1 : 256 / tiles, zmax = zt < z ? zt : z, n = (long long)rows * a.K;
     WgradWalk k{};
-    long long best = 0;
-    for (int pieces = 1; pieces <= 64 && (pieces == 1 || a.h >= 4 * pieces); ++pieces) {
-        const int len = (a.h + pieces - 1) / pieces, sps = (len + 2 + WG_NR - 1) / WG_NR;
-        const long long per = (strips * pieces + walkers - 1) / walkers;
-        if (pieces > 1 && per * sps >= best) continue;
-        best = per * sps;
-        k = WgradWalk{len, pieces, (int)per, sps, (int)((strips * pieces + per * WK - 1) / (per * WK))};
+    double best = 0;
+    for (int f = 4; f >= 1; --f) {
+        const long long walkers = (zmax * f + 3) / 4 * WK;
+        for (int pieces = 1; pieces <= 64 && (pieces == 1 || a.h >= 4 * pieces); ++pieces) {
+            const int len = (a.h + pieces - 1) / pieces, sps = (len + 2 + WG_NR - 1) / WG_NR;
+            const long long per = (strips * pieces + walkers - 1) / walkers;
+            const long long parts = (strips * pieces + per * WK - 1) / (per * WK);
+            const double cost = 1.2 * (double)(per * sps) + 1.8e-6 * (double)(parts * n);
+            if (k.len && cost >= best) continue;
+            best = cost;
+            k = WgradWalk{len, pieces, (int)per, sps, (int)parts};
+        }
     }
     z = k.z;
-    float *bpart = part + (long long)z * rows * a.K;
+    float *bpart = part + z * n;
+    if (z == 1 && dw1) {                       // a single part is the gradient itself
+        part = dw1;
+        bpart = db1;
+    }
     const dim3 grid((unsigned)(tiles * z));
     if (shape == 22)
         hipLaunchKernelGGL((k_wgrad_rows<PW, 2, 2, false, SUMS>), grid, dim3(512), 0, s, a, g, g_cs, g_co, rows, part, bpart, k);
@@ -2076,12 +2100,15 @@ hipError_t wgrad(const ConvArgs &a, const uint16_t *g, int g_cs, int g_co, int r
     if (const int shape = rows_shape(a, rows, g_cs)) {
         const auto f = db ? (a.w > 16 ? launch_wgrad_rows<32, true> : launch_wgrad_rows<16, true>)
                           : (a.w > 16 ? launch_wgrad_rows<32, false> : launch_wgrad_rows<16, false>);
-        const hipError_t e = f(shape, a, g, g_cs, g_co, rows, part, z, s);
-        if (e != hipSuccess) return e;
+        const hipError_t e = f(shape, a, g, g_cs, g_co, rows, part, z, accumulate ? nullptr : dw, db, s);
+        if (e != hipSuccess || (z == 1 && !accumulate)) return e;
     } else {
         const dim3 grid(rows <= 32 ? 1u : (unsigned)((rows + BM - 1) / BM),
                         rows <= 32 ? (unsigned)((a.K + 127) / 128) : (unsigned)((a.K + BN - 1) / BN), (unsigned)z);
-        float *bpart = part + z * n;
+        // a single part is the gradient itself
+        const bool one = z == 1 && !accumulate && !(db && (a.flags & FLAG_S2D_G) && rows > 32);
+        float *bpart = one && db && rows > 32 ? db : part + z * n;
+        if (one) part = dw;
 #define CALL(NARROW, SUMS) \
     hipLaunchKernelGGL((k_wgrad<NARROW, SUMS>), grid, dim3(256), 0, s, a, g, g_cs, g_co, rows, part, bpart, chunk)
         // at most 32 rows: a pass of its own for the bias gradient (16 x 256^2, 8 rows: 54 us with it, 66 us with the
@@ -2090,8 +2117,10 @@ hipError_t wgrad(const ConvArgs &a, const uint16_t *g, int g_cs, int g_co, int r
         else if (db) CALL(false, true);
         else CALL(false, false);
 #undef CALL
+        if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+        if (one && (!db || rows > 32)) return hipSuccess;
         if (db && rows <= 32) {
-            const hipError_t e = sum_splits(part, z, n, dw, accumulate, s);
+            const hipError_t e = one ? hipSuccess : sum_splits(part, z, n, dw, accumulate, s);
             if (e != hipSuccess) return e;
             const int fine = (a.flags & FLAG_S2D_G) ? a.dims : 0;
             const long long pixels = a.M << fine;

@@ -793,3 +793,71 @@ def test_wgrad_reaches_no_further_than_its_taps(dims, shape, rows, cin):
         ok = np.isfinite(ref)
         # M products of magnitude about 1 summed in FP32
         assert np.abs(got[ok] - ref[ok]).max() <= 2.0 ** -23 * M * np.abs(ref[ok]).max()
+
+
+# the 64-row blocks of the row kernel take layers of more than 0.7e9 products (smaller ones the im2col kernel):
+# ragged planes cut into segments, planes 16 wide in pairs, 3D
+@pytest.mark.parametrize("dims,grid,rows,cin", [
+    (2, (2, 1, 159, 131), 64, 32), (2, (20, 1, 131, 16), 64, 32), (3, (1, 7, 43, 47), 64, 32),
+    (2, (5, 1, 32, 96), 128, 128)])
+def test_wgrad_of_64_rows(dims, grid, rows, cin):
+    C = C_()
+    n, d, h, w = grid
+    K, M = cin * 3 ** dims, n * d * h * w
+    assert M * rows * K > 0.7e9
+    rng = np.random.default_rng(21)
+    x, g = bf(rng.standard_normal(grid + (cin,))), bf(rng.standard_normal(grid + (rows,)))
+    xd, gd = dev_bf(x), dev_bf(g)
+    dw, db = torch.empty((rows, K), device="cuda"), torch.empty(rows, device="cuda")
+    desc = C.lbmnn_conv_desc(n, d, h, w, dims, 3, cin, 0, 0, xd.data_ptr(), cin, 0, None, None, 0, 0)
+    offs = [(dz, dy, dx) for dz in ((-1, 0, 1) if dims == 3 else (0,)) for dy in (-1, 0, 1) for dx in (-1, 0, 1)]
+    ref = np.zeros((rows, 3 ** dims, cin))
+    for t, off in enumerate(offs):
+        a = [slice(max(0, -o), s - max(0, o)) for o, s in zip(off, grid[1:])]
+        b = [slice(max(0, o), s - max(0, -o)) for o, s in zip(off, grid[1:])]
+        ref[:, t] = g[(slice(None), *a)].reshape(-1, rows).T @ x[(slice(None), *b)].reshape(-1, cin)
+    for splits in (1, 3, 40):
+        need = C.nnlib().lbmnn_wgrad_workspace_bytes(M, rows, K + 1, splits)
+        ws = torch.empty(need // 4 + 4, device="cuda")
+        C.check(C.nnlib().lbmnn_conv_wgrad_bias(ctypes.byref(desc), gd.data_ptr(), rows, 0, rows, dw.data_ptr(),
+                                                db.data_ptr(), 0, ws.data_ptr(), need, splits, stream()), "wgrad_bias")
+        # M products of two BF16 (exact in FP32) summed in FP32
+        assert rel(dw.cpu().numpy(), ref.reshape(rows, K)) <= 2.0 ** -24 * M ** 0.5
+        gs = g.reshape(-1, rows).sum(0)
+        assert np.abs(db.cpu().numpy() - gs).max() <= 2.0 ** -23 * np.abs(g).reshape(-1, rows).sum(0).max()
+
+
+@pytest.mark.parametrize("dims,ks,grid,cin,rows,flags", [
+    (2, 3, (1, 1, 16, 16), 64, 64, 0), (2, 3, (1, 1, 20, 33), 32, 32, 0), (2, 3, (1, 1, 17, 24), 8, 32, 0),
+    (2, 3, (1, 1, 9, 12), 16, 24, 0), (2, 1, (1, 1, 10, 12), 64, 128, 16), (3, 1, (1, 2, 6, 5), 32, 64, 16),
+    (2, 1, (1, 1, 10, 12), 64, 32, 16)])
+@pytest.mark.parametrize("accumulate", [0, 1])
+def test_single_part_is_the_gradient(dims, ks, grid, cin, rows, flags, accumulate):
+    """One part goes straight into the gradient, with the result of the sum over parts; accumulated gradients and
+    their surroundings stay."""
+    C = C_()
+    L = C.nnlib()
+    n, d, h, w = grid
+    f = 2 if flags else 1
+    gch = rows >> dims if flags else rows
+    rng = np.random.default_rng(22)
+    # integers small enough that every sum is exact in FP32
+    x = dev_bf(rng.integers(-4, 5, grid + (cin,)))
+    g = dev_bf(rng.integers(-4, 5, (n, d * (f if dims == 3 else 1), h * f, w * f, gch)))
+    K, M = cin * ks ** dims, n * d * h * w
+    desc = C.lbmnn_conv_desc(n, d, h, w, dims, ks, cin, 0, flags, x.data_ptr(), cin, 0, None, None, 0, 0)
+    out = []
+    for splits in (1, max(2, M // 64)):
+        need = L.lbmnn_wgrad_workspace_bytes(M, rows, K + 1, splits)
+        ws = torch.full((need // 4 + 4,), 7.0, device="cuda")
+        for bias in (0, 1):
+            dw, db = torch.full((rows * K + 8,), 3.0, device="cuda"), torch.full((gch + 8,), 5.0, device="cuda")
+            args = (ctypes.byref(desc), g.data_ptr(), gch, 0, rows, dw.data_ptr())
+            tail = (accumulate, ws.data_ptr(), need, splits, stream())
+            C.check(L.lbmnn_conv_wgrad_bias(*args, db.data_ptr(), *tail) if bias else L.lbmnn_conv_wgrad(*args, *tail), "wgrad")
+            assert (dw[rows * K:] == 3).all() and (db[gch:] == 5).all() and (bias or (db == 5).all())
+            out.append((dw, db if bias else None))
+    for dw, db in out[1:]:
+        assert torch.equal(dw, out[0][0])
+    assert torch.equal(out[1][1], out[3][1])
+    assert out[0][0].abs().max() > 5
