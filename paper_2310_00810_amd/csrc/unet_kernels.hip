@@ -1879,6 +1879,13 @@ int conv_splits(const ConvArgs &a) {
     return (steps + sper - 1) / sper;
 }
 
+// A 1 x 1 convolution over its own input (the output's channels among the
+// input's): k_conv reads all channels of its pixels before it writes them (up
+// to 64 columns, or split), the kernels whose wavefronts share pixels do not.
+static bool in_place(const ConvArgs &a) {
+    return a.ks == 1 && a.in == a.out && !a.out32 && a.in_co < a.out_co + a.ncols && a.out_co < a.in_co + a.cin;
+}
+
 // The direct kernel's conditions; its splits are the wavefronts of a block.
 // It reads every operand from the caches for each 32 x 32 tile, so it pays while
 // launches and latency dominate (us, direct against partials and k_conv_reduce):
@@ -1896,6 +1903,7 @@ int conv_splits(const ConvArgs &a) {
 // blocks 15.2 : 17.8; 16^2, 256 -> 32, 8 blocks of nine 11.0 : 10.3).
 static bool direct_ok(const ConvArgs &a, int S, unsigned *in_bytes) {
     const long long tiles = (a.M + 31) / 32 * ((a.ncols + 31) / 32);
+    if (in_place(a)) return false;
     if (S >= 9 && a.cin % 128 == 0 && (tiles > 256 || tiles < (S >= 11 ? 128 : 16))) return false;
     const uintptr_t ob = a.out32 ? (uintptr_t)a.out32 : (uintptr_t)a.out;
     const long long bytes = 2 * a.M * a.in_cs;
@@ -1965,7 +1973,7 @@ hipError_t conv(const ConvArgs &a, hipStream_t s) {
     const uintptr_t ob = a.out32 ? (uintptr_t)a.out32 : (uintptr_t)a.out;
     // From 256 input channels on (K steps of a wavefront's weights: 64 registers) too few pixel groups are in
     // flight: 16 x 32^2, 256 -> 4 x 128 33 us against 20 us in k_conv; S2D at K = 128 gains nothing (33 us both).
-    if (a.ks == 1 && a.K <= 128 && !(a.flags & FLAG_S2D) && ((a.out_cs | a.out_co) & 7) == 0 && (ob & 15) == 0) {
+    if (a.ks == 1 && a.K <= 128 && !(a.flags & FLAG_S2D) && !in_place(a) && ((a.out_cs | a.out_co) & 7) == 0 && (ob & 15) == 0) {
         const int steps = (a.K + 31) / 32, groups = (a.ncols + 31) / 32, gw = groups >= 3 ? 4 : groups;
         const int gy = (groups + gw - 1) / gw, pt = steps <= 1 ? 4 : 2;
         const long long want = (a.M + 16 * pt * (4 / gw) - 1) / (16 * pt * (4 / gw));
