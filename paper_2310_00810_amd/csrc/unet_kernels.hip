@@ -164,6 +164,20 @@ __device__ inline void cursor_inc(Cursor &c, const ConvArgs &a) { cursor_add(c, 
 
 __device__ inline bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 
+// 8 FP32 values to a 16-byte aligned place, or added to those there.
+__device__ inline void store8(float *p, const float (&v)[8], bool add) {
+    float4 *dst = (float4 *)p;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        float4 x = make_float4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
+        if (add) {
+            const float4 old = dst[k];
+            x = make_float4(old.x + x.x, old.y + x.y, old.z + x.z, old.w + x.w);
+        }
+        dst[k] = x;
+    }
+}
+
 // ReLU backward: v[k] = 0 where the 8 activations y (NaN included) are not > 0.
 __device__ inline void relu_mask(float (&v)[8], uint4 y) {
     float f[8];
@@ -557,8 +571,7 @@ __global__ void __launch_bounds__(1024) k_conv_direct(ConvArgs a, int S, int spe
             if (a.flags & FLAG_RELU) v[q] = v[q] > 0.f ? v[q] : 0.f;
         }
         if (a.out32) {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) a.out32[o + q] = (a.flags & FLAG_ACC) ? a.out32[o + q] + v[q] : v[q];
+            store8(a.out32 + o, v, (a.flags & FLAG_ACC) != 0);
             continue;
         }
         uint16_t *dst = a.out + o;
@@ -886,16 +899,7 @@ __global__ void __launch_bounds__(256) k_conv1x1(ConvArgs a, int gw) {
                     if (a.flags & FLAG_RELU) v[k] = v[k] > 0.f ? v[k] : 0.f;
                 }
                 if (a.out32) {
-                    float4 *dst = (float4 *)(a.out32 + o);
-#pragma unroll
-                    for (int k = 0; k < 2; ++k) {
-                        float4 x = make_float4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
-                        if (a.flags & FLAG_ACC) {
-                            const float4 old = dst[k];
-                            x = make_float4(old.x + x.x, old.y + x.y, old.z + x.z, old.w + x.w);
-                        }
-                        dst[k] = x;
-                    }
+                    store8(a.out32 + o, v, (a.flags & FLAG_ACC) != 0);
                 } else {
                     uint16_t *dst = a.out + o;
                     if (a.flags & FLAG_ACC) {
@@ -2047,8 +2051,7 @@ static int rows_shape(const ConvArgs &a, int rows, int g_cs) {
     // small layers are launch, first loads and sums, and the im2col kernel's four wavefronts have less of those
     // (rows of 64: 16^2, 64 -> 64 8.4 us, here 12; 64^2 11.5 : 12.5; 2 x 64 x 96 13.5 : 14.2; 16 x 17 x 23, 128 ->
     // 128 16.2 : 18.2; beyond it falls behind: 5 x 32 x 96, 128 -> 128 25.7 : 19.4)
-    if (rows % 64 == 0 && (double)a.M * rows * a.K <= 0.7e9) return 0;
-    if (rows % 64 == 0 && a.cin % 32 == 0) return 22;
+    if (rows % 64 == 0 && a.cin % 32 == 0) return (double)a.M * rows * a.K <= 0.7e9 ? 0 : 22;
     if (rows % 32 == 0 && a.cin % 64 == 0) return 14;
     if (rows % 32 == 0 && a.cin % 32 == 0) return 12;
     if (rows % 32 == 0 && a.cin == 8) return 11;
