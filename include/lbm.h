@@ -147,13 +147,15 @@ typedef struct lbm_params {
 } lbm_params;
 
 /* Elapsed device time per phase of the most recent calls (HIP events on the
- * library stream), filled when timing was enabled with lbm_set_timing(). */
+ * library stream), filled when timing was enabled with lbm_set_timing().  The
+ * counts are time steps: one kernel launch each in D3Q19, where a D2Q9 launch
+ * may take several. */
 typedef struct lbm_timing {
-    double forward_ms;       /* lbm_forward step launches */
+    double forward_ms;       /* steps of lbm_forward */
     long forward_launches;
-    double recompute_ms;     /* segment recompute launches inside lbm_adjoint */
+    double recompute_ms;     /* steps of the segments recomputed inside lbm_adjoint */
     long recompute_launches;
-    double adjoint_ms;       /* adjoint step launches inside lbm_adjoint */
+    double adjoint_ms;       /* adjoint steps inside lbm_adjoint */
     long adjoint_launches;
 } lbm_timing;
 
@@ -191,8 +193,8 @@ int lbm_set_populations(lbm_handle *h, const float *d_fbar);
  * Solid nodes read as 0. */
 int lbm_get_populations(lbm_handle *h, int which, float *d_out);
 
-/* The forward map (Section 2.1): T steps from the initial state, each one
- * fused launch of streaming (Eq. 3, pull form), halfway bounce-back on walls
+/* The forward map (Section 2.1): T steps from the initial state, each the
+ * fused sequence of streaming (Eq. 3, pull form), halfway bounce-back on walls
  * and solid nodes, the x-face closure (Zou-He, or anti-bounce-back, Eq. 6)
  * and the collision (BGK, Eq. 4, towards the equilibrium of Eq. 5 with the
  * moments of Eq. 1-2; or MRT, Eq. 16-18), then the velocity-mismatch loss of

@@ -66,9 +66,10 @@ int lbmnn_conv(const lbmnn_conv_desc *c, const void *w, const float *bias, void 
 /* lbmnn_conv with a workspace for the layers whose implicit GEMM has too few
  * output tiles to fill the GPU (the deep, low-resolution levels, whose long
  * K = taps x cin loop would otherwise run on a few CUs): their contraction is
- * split into K ranges whose FP32 products go to ws, summed in range order
- * (deterministic) by a second kernel that applies the bias, ReLU /
- * accumulate and output layout of lbmnn_conv.  Every other layer runs as
+ * split into K ranges whose FP32 products are summed in range order
+ * (deterministic) before the bias, ReLU / accumulate and output layout of
+ * lbmnn_conv: through ws and a second kernel, or inside one for small layers,
+ * whose ws is asked for alike and left alone.  Every other layer runs as
  * lbmnn_conv and ignores ws.  ws: device memory of at least
  * lbmnn_conv_workspace_bytes(c) bytes (0 when the layer is not split; c is
  * validated as by lbmnn_conv, 0 for an invalid c); LBM_EINVAL for a NULL ws

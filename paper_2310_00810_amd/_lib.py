@@ -138,7 +138,6 @@ class lbmnn_layer(ctypes.Structure):
 _nn_ready = False
 
 
-
 def nnlib():
     """liblbm.so with the lbmnn_* signatures declared."""
     global _nn_ready

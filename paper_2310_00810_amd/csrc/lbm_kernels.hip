@@ -4,7 +4,8 @@
 // F = f* - w.  One step (Section 2.1, Eq. 3-5; stage list of Section 2.2)
 //   g^t = Z(S(F^{t-1}))   pull streaming with halfway bounce-back, Zou-He
 //   F^t = C(g^t)          BGK collision towards the second-order equilibrium
-// is one kernel launch; the loss (Eq. 7, Eq. 15) is evaluated on g^T.
+// is one kernel launch here; the time-blocked D2Q9 kernels take up to six steps
+// a launch.  The loss (Eq. 7, Eq. 15) is evaluated on g^T.
 //
 // Reverse sweep (exact derivative of the discrete map, the function the
 // paper's tape replay computes, Section 2.2):
@@ -243,18 +244,12 @@ __global__ void __launch_bounds__(FT) k_adj_seed(Geo G, const float *__restrict_
 // collision transpose's output before the boundary transpose (collide_adj's
 // formulas; D3Q19 has the BGK ones in line).
 template <int Q, int BCX, bool SEED, bool NT>
-__global__ void __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(6))) k_adj_step(const FTileDesc *__restrict__ fblk, const InstDev *__restrict__ inst,
-                                                 const uint2 *__restrict__ rw, int n_ftiles, int bc,
-                                                 const float *__restrict__ Fprev,
-                                                 const float *__restrict__ nu_in,
-                                                 float *__restrict__ nu_out,
-                                                 const float *__restrict__ face_in,
-                                                 const float *__restrict__ face_out,
-                                                 double *__restrict__ grad_in,
-                                                 double *__restrict__ grad_out,
-                                                 double *__restrict__ dtau_part,
-                                                 const float *__restrict__ roi,
-                                                 const float *__restrict__ target, int kind, Geo GM) {
+__global__ void __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(6)))
+k_adj_step(const FTileDesc *__restrict__ fblk, const InstDev *__restrict__ inst, const uint2 *__restrict__ rw,
+           int n_ftiles, int bc, const float *__restrict__ Fprev, const float *__restrict__ nu_in,
+           float *__restrict__ nu_out, const float *__restrict__ face_in, const float *__restrict__ face_out,
+           double *__restrict__ grad_in, double *__restrict__ grad_out, double *__restrict__ dtau_part,
+           const float *__restrict__ roi, const float *__restrict__ target, int kind, Geo GM) {
     const Geo G = geo_of(fblk, inst, rw, n_ftiles, bc);   // GM: the collision model (D2Q9)
     using V = Vel<Q>;
     __shared__ double red[4];
@@ -582,14 +577,17 @@ hipError_t launch_step(int q, const Geo &G, const float *src, float *dst, const 
     // neighbouring rows' lines); a step into the tape streams its stores
     const int ntm = G.nt ? (q == 19 ? 2 : 1) : (tape ? 1 : 0);
 #define PRE G.fblk, G.inst, G.rw, G.n_ftiles, packed_bc(G)
+#define LAUNCH(Q, B, NTM)                                                                          \
+    hipLaunchKernelGGL((k_step<Q, B, NTM>), fgrid_of(G), dim3(FT), 0, s, PRE, src, dst, fin, fout, G)
 #define CALL(Q, B)                                                                                 \
     do {                                                                                           \
-        if (ntm == 2) hipLaunchKernelGGL((k_step<Q, B, Q == 19 ? 2 : 1>), fgrid_of(G), dim3(FT), 0, s, PRE, src, dst, fin, fout, G); \
-        else if (ntm == 1) hipLaunchKernelGGL((k_step<Q, B, 1>), fgrid_of(G), dim3(FT), 0, s, PRE, src, dst, fin, fout, G); \
-        else hipLaunchKernelGGL((k_step<Q, B, 0>), fgrid_of(G), dim3(FT), 0, s, PRE, src, dst, fin, fout, G); \
+        if (ntm == 2) LAUNCH(Q, B, Q == 19 ? 2 : 1);                                               \
+        else if (ntm == 1) LAUNCH(Q, B, 1);                                                        \
+        else LAUNCH(Q, B, 0);                                                                      \
     } while (0)
     DISPATCH_BCX(q, G.bcx, CALL);
 #undef CALL
+#undef LAUNCH
     return hipGetLastError();
 }
 

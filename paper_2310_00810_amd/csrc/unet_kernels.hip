@@ -345,7 +345,8 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a, float *__restrict__ pa
     const bool d2s = (a.flags & FLAG_D2S) != 0;
     const int cr = d2s ? a.ncols >> a.dims : a.ncols;      // D2S: columns sub * cr + co
     const uintptr_t base = a.out32 ? (uintptr_t)a.out32 : (uintptr_t)a.out;
-    if (((a.out_cs | a.out_co | a.mask_cs | a.mask_co) & 7) == 0 && ((uintptr_t)a.mask & 15) == 0 && (!d2s || (cr & 7) == 0) && (base & 15) == 0) {
+    if (((a.out_cs | a.out_co | a.mask_cs | a.mask_co) & 7) == 0 && (!d2s || (cr & 7) == 0) &&
+        ((base | (uintptr_t)a.mask) & 15) == 0) {
         // the tile goes through LDS (the buffers are free after the last barrier) so that each
         // thread stores 8 consecutive channels of a pixel (of the fine pixel for D2S, whose
         // 8-column groups stay inside one sub-pixel) with 16-byte writes
@@ -1834,8 +1835,8 @@ static bool halo_ok(const ConvArgs &a) {
     return (a.dims == 2 || a.dims == 3) && a.ks == 3 && !(a.flags & (FLAG_S2D | FLAG_D2S)) && a.cin % 8 == 0 &&
            a.h % HY == 0 &&
            a.w % HX == 0 && ((a.in_cs | a.in_co | a.out_cs | a.out_co) & 7) == 0 && ((uintptr_t)a.in & 15) == 0 &&
-           (ob & 15) == 0 && ((a.mask_cs | a.mask_co) & 7) == 0 && ((uintptr_t)a.mask & 15) == 0 && 18LL * a.w * a.in_cs < (1LL << 31) && (long long)a.ncols * a.K < (1LL << 31) &&
-           a.M < (1LL << 31);
+           ((ob | (uintptr_t)a.mask) & 15) == 0 && ((a.mask_cs | a.mask_co) & 7) == 0 &&
+           18LL * a.w * a.in_cs < (1LL << 31) && (long long)a.ncols * a.K < (1LL << 31) && a.M < (1LL << 31);
 }
 
 // Sum of the K splits of a convolution, in split order, then the epilogue
@@ -1913,7 +1914,8 @@ static bool direct_ok(const ConvArgs &a, int S, unsigned *in_bytes) {
     const long long bytes = 2 * a.M * a.in_cs;
     *in_bytes = (unsigned)bytes;
     const long long most = S == 1 ? (a.K <= 320 ? 5LL << 27 : 0) : a.ncols <= 32 ? 1LL << 29 : 5LL << 28;
-    return S <= 16 && a.M * ((a.ncols + 31) / 32 * 32) <= most / a.K && a.cin % 32 == 0 && !(a.flags & FLAG_S2D) && bytes < (1LL << 31) && 2LL * a.ncols * a.K < (1LL << 31) && ((a.out_cs | a.out_co) & 7) == 0 &&
+    return S <= 16 && a.M * ((a.ncols + 31) / 32 * 32) <= most / a.K && a.cin % 32 == 0 && !(a.flags & FLAG_S2D) &&
+           bytes < (1LL << 31) && 2LL * a.ncols * a.K < (1LL << 31) && ((a.out_cs | a.out_co) & 7) == 0 &&
            (ob & 15) == 0;
 }
 static hipError_t conv_direct(const ConvArgs &a, int S, int sper, unsigned in_bytes, hipStream_t s) {
@@ -2049,8 +2051,8 @@ static int rows_shape(const ConvArgs &a, int rows, int g_cs) {
     const long long reach = ((a.w <= 16 ? a.h : 0) + WG_NR + 1LL) * a.w + 34;
     if (2 * reach * (a.in_cs > g_cs ? a.in_cs : g_cs) >= (1LL << 31)) return 0;
     // small layers are launch, first loads and sums, and the im2col kernel's four wavefronts have less of those
-    // (rows of 64: 16^2, 64 -> 64 8.4 us, here 12; 64^2 11.5 : 12.5; 2 x 64 x 96 13.5 : 14.2; 16 x 17 x 23, 128 ->
-    // 128 16.2 : 18.2; beyond it falls behind: 5 x 32 x 96, 128 -> 128 25.7 : 19.4)
+    // (us with the sum of the partials, im2col : here; 64 -> 64: 16^2 8.4 : 12, 64^2 11.5 : 12.5, 2 x 64 x 96 13.5 :
+    // 14.2; 16 x 17 x 23, 128 -> 128 16.2 : 18.2; beyond it falls behind: 5 x 32 x 96, 128 -> 128 25.7 : 19.4)
     if (rows % 64 == 0 && a.cin % 32 == 0) return (double)a.M * rows * a.K <= 0.7e9 ? 0 : 22;
     if (rows % 32 == 0 && a.cin % 64 == 0) return 14;
     if (rows % 32 == 0 && a.cin % 32 == 0) return 12;
