@@ -1888,7 +1888,8 @@ int conv_splits(const ConvArgs &a) {
 // input's): k_conv reads all channels of its pixels before it writes them (up
 // to 64 columns, or split), the kernels whose wavefronts share pixels do not.
 static bool in_place(const ConvArgs &a) {
-    return a.ks == 1 && a.in == a.out && !a.out32 && a.in_co < a.out_co + a.ncols && a.out_co < a.in_co + a.cin;
+    const long long d = ((intptr_t)a.out - (intptr_t)a.in) / 2 + a.out_co - a.in_co;
+    return a.ks == 1 && !a.out32 && a.in_cs == a.out_cs && d > -(long long)a.ncols && d < a.cin;
 }
 
 // The direct kernel's conditions; its splits are the wavefronts of a block.

@@ -863,9 +863,10 @@ def test_single_part_is_the_gradient(dims, ks, grid, cin, rows, flags, accumulat
     assert out[0][0].abs().max() > 5
 
 
+@pytest.mark.parametrize("by_pointer", [0, 1])
 @pytest.mark.parametrize("shape,cin,cout,co", [((1, 1, 40, 50), 64, 64, 0), ((3, 1, 64, 96), 128, 64, 32),
                                                ((1, 1, 30, 40), 512, 512, 0), ((2, 1, 16, 24), 1024, 256, 128)])
-def test_pointwise_convolution_over_its_input(shape, cin, cout, co):
+def test_pointwise_convolution_over_its_input(shape, cin, cout, co, by_pointer):
     """In place (up to 64 columns, or with split contractions), the result of the convolution into another buffer."""
     C = C_()
     L = C.nnlib()
@@ -875,7 +876,8 @@ def test_pointwise_convolution_over_its_input(shape, cin, cout, co):
     b = torch.randn(cout, generator=g, device="cuda")
     out = [x.clone(), x.clone()]
     for src, dst in ((x, out[0]), (out[1], out[1])):
-        desc = C.lbmnn_conv_desc(*shape, 2, 1, cin, cout, 1, src.data_ptr(), cin, 0, dst.data_ptr(), None, cin, co)
+        where = (dst.data_ptr() + 2 * co, None, cin, 0) if by_pointer else (dst.data_ptr(), None, cin, co)
+        desc = C.lbmnn_conv_desc(*shape, 2, 1, cin, cout, 1, src.data_ptr(), cin, 0, *where)
         need = L.lbmnn_conv_workspace_bytes(ctypes.byref(desc))
         assert need > 0 or cout <= 64
         ws = torch.empty(need // 4 + 4, device="cuda")
